@@ -23,7 +23,7 @@
 
 #include "device_common.h"
 #include "solve_core.h"
-#include "solve_row.h"
+#include "solve_reg.h"
 #include "sp_internal.h"
 
 namespace sp {
@@ -262,25 +262,17 @@ __global__ void __launch_bounds__(256)
 // inverse of I - dt L) in the Chebyshev-tau / influence-matrix form.
 // out = S(g): velocity of (1/Re) Lap phi - phi/dt - grad p = -g, div phi = 0,
 // walls (wall_upper, wall_lower) for the (0,0) mode when inhomogeneous, else 0.
-// One 64-lane wave per mode, four 16-lane rows (solve_row.h):
+// One 64-lane wave per mode, four 16-lane rows (solve_reg.h):
 //   rows 0, 1: the coupled (v, p) chain with v of parity r (p of the other),
 //   rows 2, 3: the decoupled u_perp Helmholtz problem on parity r - 2, swept in
 //              the same instruction stream as the Poisson sweep of rows 0, 1.
 // (0,0) mode: rows 0, 1 solve for u (parity r), rows 2, 3 for w (parity r - 2).
-// Rows without work in a step run it on a dummy array.
+// Rows without work in a step run it on values that nobody reads.
 // ---------------------------------------------------------------------------
 // Orders one wave's LDS accesses between two steps of the solve when no other
 // wave of the block takes part: a workgroup-scope fence waits for the wave's
 // LDS operations and keeps the compiler from moving any across it.
 __device__ inline void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup"); }
-
-#define SP_ROW_PAR(par, body)                       \
-  _Pragma("unroll") for (int e_ = 0; e_ < E; ++e_) { \
-    const int n = (par) + 2 * (l * E + e_);          \
-    if (n <= N) {                                    \
-      body                                           \
-    }                                                \
-  }
 
 // AN = 0: the right-hand side g is read from a canonical field. AN = 1 (FP64)
 // or 2 (FP32 transform path): g = Tinv nv + xa x is formed here from the
@@ -299,7 +291,7 @@ template <int E, int AN, bool RES = false>
 __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
     __attribute__((amdgpu_waves_per_eu(AN != 0 ? 3 : 1)))
     k_stokes_solve(const double2* __restrict__ g, double2* __restrict__ out,
-                   const double* __restrict__ modedata, const double* __restrict__ hw_g,
+                   const double* __restrict__ modedata, const double* __restrict__ hwp_g,
                    int stride, int nx, int ny, int nzh, double alpha, double gamma, double re,
                    double inv_dt, double wu, double wl, int inhomogeneous,
                    const void* __restrict__ nv_raw, const void* __restrict__ tinv_raw,
@@ -308,31 +300,29 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
   extern __shared__ unsigned char smem_raw[];
   const int N = ny - 1;
   const int n1 = ny;
+  // the mode record and the weights; by coefficient n: the right-hand side on its way into the rows' registers
+  // (F_v, F_par, -F_perp), then the solution on its way out (v, A = D v, u_perp)
   double* rec = reinterpret_cast<double*>(smem_raw);
-  double* hw = rec + stride;
-  cd* Fpar = reinterpret_cast<cd*>(hw + 3 * n1);
-  cd* Fv = Fpar + n1;
-  cd* A = Fv + n1;
-  cd* divF = A + n1;
-  cd* P = divF + n1;
-  cd* Rv = P + n1;
-  cd* V = Rv + n1;
-  cd* Rp = V + n1;
-  cd* U = Rp + n1;
-  cd* Dm = U + n1;  // output of the idle rows
+  double* hwp = rec + stride;
+  cd* Fv = reinterpret_cast<cd*>(rec + ((stride + 3 * hwp_row(n1) + 1) & ~1));
+  cd* Fpar = Fv + n1;
+  cd* Rp = Fpar + n1;
+  cd* V = Fv;
+  cd* A = Fpar;
+  cd* U = Rp;
   const int jh = (ny - 1) / 2 + 1;  // folded column length (AN != 0)
   const int jh8 = (jh + 7) & ~7;    // padded with zeros to whole groups of 8
-  // The folded columns of the analysis share the space of the ten arrays
+  // The folded columns of the analysis share the space of the three arrays
   // above: both waves read them only before the analysis' last barrier, and
   // the arrays are first written after it.
-  cd* colE = Fpar;  // [3][jh8] even halves f_j + f_{N-j}
+  cd* colE = Fv;  // [3][jh8] even halves f_j + f_{N-j}
   // odd halves f_j - f_{N-j} ([3][jh8]), 64 bytes past the even ones so that
   // the two addresses an analysis load broadcasts fall in different banks
   cd* colO = colE + 3 * jh8 + 4;
-  const int shared_len = (10 * n1 > 6 * jh8 + 4) ? 10 * n1 : 6 * jh8 + 4;
+  const int shared_len = (3 * n1 > 6 * jh8 + 4) ? 3 * n1 : 6 * jh8 + 4;
   // [6][64] partial sums of wave 1 (which may still read them after the
   // analysis' last barrier, so they have space of their own)
-  double* part_raw = reinterpret_cast<double*>(Fpar + shared_len);
+  double* part_raw = reinterpret_cast<double*>(Fv + shared_len);
   // x at n <= N for the residual form ([3][n1]), past wave 1's partial sums
   cd* Yx = reinterpret_cast<cd*>(part_raw + 6 * 64);
 
@@ -342,9 +332,9 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
   const int j = lo / nx;
   const int i = lo - j * nx;
   const int mode = i * nzh + j;
-  // With the fused analysis (AN != 0) a mode has two waves: wave 1 loads half of
-  // the record and sums half of the analysis' terms, hands its partial sums to
-  // wave 0 and leaves; wave 0 does everything else.
+  // With the fused analysis (AN != 0) a mode has two waves: wave 1 sums half of
+  // the analysis' terms, hands its partial sums to wave 0 and leaves; wave 0 does
+  // everything else.
   constexpr int NW = (AN != 0) ? 2 : 1;
   const int tid = threadIdx.x & 63;
   const bool shadow = (threadIdx.x >> 6) != 0;
@@ -426,41 +416,41 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
       }
     }
   }
-  // mode record and weights (contiguous in LDS: hw = rec + stride) in one round
+  // mode record and weights (contiguous in LDS: hwp = rec + stride) in one round
   // trip: all loads are issued before the first LDS store
+  constexpr int RPL = (solve_record_loads(E) + NW - 1) / NW;
+  const int tot = stride + 3 * hwp_row(n1);
+  double rv[RPL];
   {
-    constexpr int RPL = (solve_record_loads(E) + NW - 1) / NW;
     const double* src = modedata + (size_t)mode * stride;
-    const int tot = stride + 3 * n1;
-    double rv[RPL];
 #pragma unroll
     for (int q = 0; q < RPL; ++q) {
       const int t = threadIdx.x + 64 * NW * q;
       const int tc = t < tot ? t : tot - 1;
-      rv[q] = (tc < stride) ? src[tc] : hw_g[tc - stride];
+      rv[q] = (tc < stride) ? src[tc] : hwp_g[tc - stride];
     }
-    if constexpr (AN != 0) {
-      // even / odd halves, zero padded to jh8 entries
+  }
+  if constexpr (AN != 0) {
+    // even / odd halves, zero padded to jh8 entries
 #pragma unroll
-      for (int q = 0; q < QF; ++q) {
-        const int jj = tid + 64 * q;
-        if (jj < jh8 && !shadow) {
-          const double in = jj < jh ? 1.0 : 0.0;
-          const double same = (jj == N - jj) ? 0.0 : 1.0;  // middle point counted once
+    for (int q = 0; q < QF; ++q) {
+      const int jj = tid + 64 * q;
+      if (jj < jh8 && !shadow) {
+        const double in = jj < jh ? 1.0 : 0.0;
+        const double same = (jj == N - jj) ? 0.0 : 1.0;  // middle point counted once
 #pragma unroll
-          for (int c = 0; c < 3; ++c) {
-            const double ar = fa[q][c].x, ai = fa[q][c].y, br = fb[q][c].x, bi = fb[q][c].y;
-            colE[c * jh8 + jj] = cd((ar + same * br) * in, (ai + same * bi) * in);
-            colO[c * jh8 + jj] = cd((ar - br) * same * in, (ai - bi) * same * in);
-          }
+        for (int c = 0; c < 3; ++c) {
+          const double ar = fa[q][c].x, ai = fa[q][c].y, br = fb[q][c].x, bi = fb[q][c].y;
+          colE[c * jh8 + jj] = cd((ar + same * br) * in, (ai + same * bi) * in);
+          colO[c * jh8 + jj] = cd((ar - br) * same * in, (ai - bi) * same * in);
         }
       }
     }
+  }
 #pragma unroll
-    for (int q = 0; q < RPL; ++q) {
-      const int t = threadIdx.x + 64 * NW * q;
-      if (t < tot) rec[t] = rv[q];
-    }
+  for (int q = 0; q < RPL; ++q) {
+    const int t = threadIdx.x + 64 * NW * q;
+    if (t < tot) rec[t] = rv[q];
   }
   if constexpr (AN != 0) {
     // g_n = sum_j Tinv[n][j] f_j + xa x_n for n <= N-2 (the tau rows), one n per lane
@@ -568,8 +558,9 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
         const cd fv(re * gb[t].x, re * gb[t].y);
         const cd fw(re * gc[t].x, re * gc[t].y);
         if (mean) {
-          Rv[n] = -fu;  // (0,0): u and w solve Dirichlet Helmholtz problems
+          Fv[n] = -fu;  // (0,0): u and w solve Dirichlet Helmholtz problems
           Rp[n] = -fw;
+          Fpar[n] = cd(0.0);
         } else {
           Fpar[n] = (fu * kx + fw * kz) * ik;
           Rp[n] = -((fu * kz - fw * kx) * ik);  // -F_perp
@@ -579,59 +570,103 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
     }
   }
   lds_order();
-  const ModeLayout L{n1};
-  const SweepRec helm(rec + L.helm(), n1, lam);
-  const SweepRec pois(rec + L.pois(), n1, k2);
   const bool vrow = row < 2;
   const int pv = row & 1;  // v parity (rows 0, 1), u_perp / w parity (rows 2, 3)
-  const int po = 1 - pv;
+  const ModeLayout L{n1};
+  // positions n = pv + 2 k of v's (u_perp's) chain and nP = pv - 1 + 2 k of P's;
+  // entries past the chains are zeros
+  cd f0[E], r[E], v[E], c[E];
+  const cd* F0 = vrow ? Fv : Rp;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int n = pv + 2 * (l * E + e);
+    const int nP = n - 1;
+    const double keep = mask(n <= N), keepP = mask(nP >= 0 && nP <= N);
+    f0[e] = F0[n <= N ? n : N] * keep;
+    r[e] = Fpar[nP < 0 ? 0 : (nP <= N ? nP : N)] * (k * keepP);
+  }
+  lds_order();  // the solution goes into the same arrays
   if (mean) {
     cd bu(0.0);
     if (inhomogeneous && vrow) bu = cd(pv == 0 ? 0.5 * (wu + wl) : 0.5 * (wu - wl));
-    wsweep<E>(helm, hw, N, pv, vrow ? Rv : Rp, bu, vrow ? P : U, l);
-  } else {
-    // divF = i k F_par + D F_v on rows 0, 1, formed as the derivative is stored
-    // (rows 2, 3 differentiate into the idle array: a per-lane select, no branch)
-    wderiv<E>(N, pv, vrow ? Fv : Rp, vrow ? divF : Dm, l, [&](int m, cd v) {
-      const cd t = mul_i(Fpar[m] * k) + v;
-      return vrow ? t : v;
-    });
-    lds_order();
-    // P = Pois(div F) on rows 0, 1; U = Helm(-F_perp) on rows 2, 3
-    wsweep<E>(vrow ? pois : helm, hw, N, vrow ? po : pv, vrow ? divF : Rp, cd(0.0), vrow ? P : U,
-              l);
-    lds_order();
-    // Rv = D P - F_v on rows 0, 1, formed as the derivative is stored
-    wderiv<E>(N, po, vrow ? P : Rp, vrow ? Rv : Dm, l, [&](int m, cd v) {
-      const cd t = v - Fv[m];
-      return vrow ? t : v;
-    });
-    lds_order();
-    wsweep<E>(helm, hw, N, pv, vrow ? Rv : Rp, cd(0.0), vrow ? V : Dm, l);
-    lds_order();
-    // influence correction: (c_delta, c_b) = -Minv (D v(1), tau definition)
-    cd ca(0.0), cb(0.0);
-    {
-      cd la(0.0);
-      SP_ROW_PAR(pv, la = la + V[n] * ((double)n * n);)
-      la = row_sum(la);
-      const int m = (N % 2 == pv) ? N : N - 1;
-      cd lb = V[m] * lam;
-      if (m == N - 1) lb = lb + P[N] * (2.0 * N);
-      const double* Mi = rec + L.minv() + 4 * pv;
-      ca = -(la * Mi[0] + lb * Mi[1]);
-      cb = -(la * Mi[2] + lb * Mi[3]);
+    rsweep<E>(RegSweep<E>(hwp, rec + L.helm(), N, pv, lam, l), f0, bu, v);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int n = pv + 2 * (l * E + e);
+      if (n <= N) (vrow ? V : U)[n] = v[e];
     }
-    const double* vdel = rec + L.vdel();
-    const double* vb = rec + L.vb();
-    lds_order();
-    // V += c_delta vdel + c_b vb on rows 0, 1, taken as the derivative loads V (the
-    // lane that owns n updates it and stores it back for the output)
-    wderiv<E>(N, pv, vrow ? V : Rp, vrow ? A : Dm, l, StoreDeriv(), [&](int n, cd v, bool own) {
-      const cd t = v + ca * vdel[n] + cb * vb[n];
-      if (vrow && own) V[n] = t;
-      return vrow ? t : v;
-    });
+  } else {
+    // weights 2 n of D on the two chains (zero outside), and c_0 = 2
+    double dv[E], dP[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int n = pv + 2 * (l * E + e);
+      dv[e] = (n <= N) ? 2.0 * n : 0.0;
+      dP[e] = (n >= 1 && n - 1 <= N) ? 2.0 * (n - 1) : 0.0;
+    }
+    const double halfP = (l == 0 && pv == 1) ? 0.5 : 1.0;  // position 0 of P's chain is n = 0
+    const double halfv = (l == 0 && pv == 0) ? 0.5 : 1.0;  // position 0 of v's chain is n = 0
+    // div F = i k F_par + D F_v on rows 0, 1; rows 2, 3 take -F_perp as it is
+#pragma unroll
+    for (int e = 0; e < E; ++e) c[e] = f0[e] * dv[e];
+    suffix_sum<E>(c, c);
+    c[0] = c[0] * halfP;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const cd t = mul_i(r[e]) + c[e];
+      r[e] = pick(vrow, t, f0[e]);
+    }
+    // P = Pois(div F) on rows 0, 1; U = Helm(-F_perp) on rows 2, 3
+    cd P[E];
+    rsweep<E>(RegSweep<E>(hwp, rec + (vrow ? L.pois() : L.helm()), N, vrow ? pv - 1 : pv,
+                          vrow ? k2 : lam, l),
+              r, cd(0.0), P);
+    // Rv = D P - F_v on rows 0, 1 (D P at position k: the sum from k + 1)
+#pragma unroll
+    for (int e = 0; e < E; ++e) c[e] = P[e] * dP[e];
+    suffix_sum<E>(c, c);
+    {
+      const cd next = cd_dpp<kDppRowShl | 1>(c[0]);
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        cd t = pick(e == E - 1, next, c[e < E - 1 ? e + 1 : 0]);
+        if (e == 0) t = t * halfv;
+        r[e] = t - f0[e];
+      }
+    }
+    rsweep<E>(RegSweep<E>(hwp, rec + L.helm(), N, pv, lam, l), r, cd(0.0), v);
+    // influence correction: (c_delta, c_b) = -Minv (D v(1), tau definition)
+    const int m = (N % 2 == pv) ? N : N - 1;
+    cd la(0.0), lb(0.0);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int n = pv + 2 * (l * E + e);
+      la = la + v[e] * ((n <= N) ? (double)n * n : 0.0);
+      lb = lb + v[e] * ((n == m) ? lam : 0.0);
+      lb = lb + P[e] * ((n - 1 == N && m == N - 1) ? 2.0 * N : 0.0);
+    }
+    la = row_sum(la);
+    lb = row_sum(lb);
+    const double* Mi = rec + L.minv() + 4 * pv;
+    const cd ca = -(la * Mi[0] + lb * Mi[1]);
+    const cd cb = -(la * Mi[2] + lb * Mi[3]);
+    // V += c_delta vdel + c_b vb, then A = D V (u_par = i A / k)
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int n = pv + 2 * (l * E + e);
+      const int nc = n <= N ? n : N;
+      v[e] = v[e] + ca * rec[L.vdel() + nc] + cb * rec[L.vb() + nc];
+      c[e] = v[e] * dv[e];
+    }
+    suffix_sum<E>(c, c);
+    c[0] = c[0] * halfP;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int n = pv + 2 * (l * E + e);
+      const cd gv = pick(vrow, v[e], P[e]);
+      if (n <= N) (vrow ? V : U)[n] = gv;
+      if (vrow && n >= 1 && n - 1 <= N) A[n - 1] = c[e];
+    }
   }
   lds_order();
   // n1 <= 32 E coefficients: a fixed, unrolled pass count, so the LDS reads of
@@ -642,7 +677,7 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
     if (n >= n1) break;
     cd uo, vo, wo;
     if (mean) {
-      uo = P[n];
+      uo = V[n];
       wo = U[n];
     } else {
       const cd upar = mul_i(A[n]) * ik;
@@ -906,15 +941,15 @@ int solve_lanes_per_chain(int ny) { return ((ny - 1) / 2 + 1 + 15) / 16; }
 static size_t solve_lds_bytes(const sp_plan* p, bool fused, bool res = false) {
   const Dims& d = p->d;
   const size_t jh8 = (((d.ny - 1) / 2 + 1) + 7) & ~7;
-  // ten arrays of ny entries, which the fused analysis' folded columns share
-  const size_t arrays = fused ? std::max<size_t>(10 * (size_t)d.ny, 6 * jh8 + 4) : 10 * (size_t)d.ny;
-  return (size_t)p->mode_stride * sizeof(double) + 3 * (size_t)d.ny * sizeof(double) +
-         arrays * sizeof(cd) + (fused ? 6 * 64 * sizeof(double) : 0) +
+  // three arrays of ny entries, which the fused analysis' folded columns share
+  const size_t arrays = fused ? std::max<size_t>(3 * (size_t)d.ny, 6 * jh8 + 4) : 3 * (size_t)d.ny;
+  const size_t rec = ((size_t)p->mode_stride + 3 * hwp_row(d.ny) + 1) / 2 * 2;
+  return rec * sizeof(double) + arrays * sizeof(cd) + (fused ? 6 * 64 * sizeof(double) : 0) +
          (res ? 3 * (size_t)d.ny * sizeof(cd) : 0);
 }
 
 #define SP_SOLVE_DISPATCH(LAUNCH)                   \
-  switch (solve_lanes_per_chain(p->d.ny)) {         \
+  switch (solve_reg_elems(p->d.ny)) {               \
     case 1: LAUNCH(1); break;                       \
     case 2: LAUNCH(2); break;                       \
     case 3: LAUNCH(3); break;                       \
@@ -928,7 +963,7 @@ hipError_t launch_stokes_solve(sp_plan* p, const double2* g, double2* out, int i
   SP_PROF_BEGIN(p, KID_SOLVE);
 #define SP_SOLVE_LAUNCH(EV)                                                                     \
   hipLaunchKernelGGL((k_stokes_solve<EV, 0>), dim3(d.nx * d.nzh), dim3(64), sh, p->stream, g,   \
-                     out, p->d_mode, p->d_hw, p->mode_stride, d.nx, d.ny, d.nzh, d.alpha,       \
+                     out, p->d_mode, p->d_hwp, p->mode_stride, d.nx, d.ny, d.nzh, d.alpha,       \
                      d.gamma, d.re, d.inv_dt, d.wall_upper, d.wall_lower, inhomogeneous, nullptr, \
                      nullptr, nullptr, 0.0)
   SP_SOLVE_DISPATCH(SP_SOLVE_LAUNCH)
@@ -946,12 +981,12 @@ hipError_t launch_analysis_solve(sp_plan* p, const double2* x, double xa, double
 #define SP_SOLVE_LAUNCH(EV)                                                                       \
   if (fp32)                                                                                       \
     hipLaunchKernelGGL((k_stokes_solve<EV, 2>), dim3(d.nx * d.nzh), dim3(128), sh, p->stream,      \
-                       nullptr, out, p->d_mode, p->d_hw, p->mode_stride, d.nx, d.ny, d.nzh,      \
+                       nullptr, out, p->d_mode, p->d_hwp, p->mode_stride, d.nx, d.ny, d.nzh,      \
                        d.alpha, d.gamma, d.re, d.inv_dt, d.wall_upper, d.wall_lower,             \
                        inhomogeneous, p->nv, p->f_tinv_th, x, xa, 1.0, 0.0);                         \
   else                                                                                            \
     hipLaunchKernelGGL((k_stokes_solve<EV, 1>), dim3(d.nx * d.nzh), dim3(128), sh, p->stream,      \
-                       nullptr, out, p->d_mode, p->d_hw, p->mode_stride, d.nx, d.ny, d.nzh,      \
+                       nullptr, out, p->d_mode, p->d_hwp, p->mode_stride, d.nx, d.ny, d.nzh,      \
                        d.alpha, d.gamma, d.re, d.inv_dt, d.wall_upper, d.wall_lower,             \
                        inhomogeneous, p->nv, p->d_tinv_th, x, xa, 1.0, 0.0)
   SP_SOLVE_DISPATCH(SP_SOLVE_LAUNCH)
@@ -970,12 +1005,12 @@ hipError_t launch_analysis_solve_res(sp_plan* p, const double2* x, double xa, do
 #define SP_SOLVE_LAUNCH(EV)                                                                       \
   if (fp32)                                                                                       \
     hipLaunchKernelGGL((k_stokes_solve<EV, 2, true>), dim3(d.nx * d.nzh), dim3(128), sh,           \
-                       p->stream, nullptr, out, p->d_mode, p->d_hw, p->mode_stride, d.nx, d.ny,  \
+                       p->stream, nullptr, out, p->d_mode, p->d_hwp, p->mode_stride, d.nx, d.ny,  \
                        d.nzh, d.alpha, d.gamma, d.re, d.inv_dt, d.wall_upper, d.wall_lower, 0,   \
                        p->nv, p->f_tinv_th, x, xa, oa, ob);                                      \
   else                                                                                            \
     hipLaunchKernelGGL((k_stokes_solve<EV, 1, true>), dim3(d.nx * d.nzh), dim3(128), sh,           \
-                       p->stream, nullptr, out, p->d_mode, p->d_hw, p->mode_stride, d.nx, d.ny,  \
+                       p->stream, nullptr, out, p->d_mode, p->d_hwp, p->mode_stride, d.nx, d.ny,  \
                        d.nzh, d.alpha, d.gamma, d.re, d.inv_dt, d.wall_upper, d.wall_lower, 0,   \
                        p->nv, p->d_tinv_th, x, xa, oa, ob)
   SP_SOLVE_DISPATCH(SP_SOLVE_LAUNCH)

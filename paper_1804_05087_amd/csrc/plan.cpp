@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "solve_core.h"
+#include "solve_reg.h"
 #include "sp_internal.h"
 
 namespace sp {
@@ -202,12 +203,24 @@ sp_status build_mode_data(sp_plan* p) {
   s = hip_check(p, hipMemcpy(p->d_hw, hw.data(), hw.size() * sizeof(double), hipMemcpyHostToDevice),
                 "upload hw");
   if (s) return s;
+  if (!p->d_hwp) {
+    std::vector<double> hwp(3 * hwp_row(n1), 0.0);
+    for (int w = 0; w < 3; ++w)
+      for (int n = 0; n < n1; ++n) hwp[w * hwp_row(n1) + n + 1] = hw[w * n1 + n];
+    s = hip_check(p, hipMalloc(&p->d_hwp, hwp.size() * sizeof(double)), "hipMalloc(hwp)");
+    if (s) return s;
+    s = hip_check(p, hipMemcpy(p->d_hwp, hwp.data(), hwp.size() * sizeof(double),
+                               hipMemcpyHostToDevice),
+                  "upload hwp");
+    if (s) return s;
+  }
   {
     // the solve kernels stage record + weights with solve_record_loads(E)
     // doubles per lane (E = elements per lane and parity chain, at most 5)
-    int E = solve_lanes_per_chain(p->d.ny);
+    int E = solve_lanes_per_chain(p->d.ny);  // the adjoint solve's
     if (E > 5) E = 5;
-    if (stride + 3 * p->d.ny > 64 * solve_record_loads(E))
+    if (stride + 3 * p->d.ny > 64 * solve_record_loads(E) ||
+        stride + 3 * hwp_row(p->d.ny) > 64 * solve_record_loads(solve_reg_elems(p->d.ny)))
       return set_error(p, SP_ERR_SHAPE, "mode record does not fit the solve kernels' loads");
   }
   p->mode_stride = stride;
@@ -230,7 +243,7 @@ static std::vector<F> convert(const std::vector<D>& v) {
 static void free_plan(sp_plan* p) {
   void* ptrs[] = {p->d_T,   p->d_TD,  p->d_Tinv, p->d_G,    p->d_hw,   p->d_mode, p->d_twx,
                   p->d_twz, p->f_twx, p->f_twz,  p->f_T,    p->f_TD,   p->f_Tinv, p->d_scratch,
-                  p->d_yfrag, p->f_yfrag, p->d_tinv_th, p->f_tinv_th};
+                  p->d_yfrag, p->f_yfrag, p->d_tinv_th, p->f_tinv_th, p->d_hwp};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
   if (p->h_partial) (void)hipHostFree(p->h_partial);

@@ -1,4 +1,5 @@
-// Row-parallel building blocks of the per-mode Chebyshev-tau solve.
+// Row-parallel building blocks of the per-mode Chebyshev-tau solve: the row scans
+// (used by the forward solve too, solve_reg.h) and the adjoint's transposed steps.
 //
 // Every sequential piece of the solve is a first-order linear recurrence along
 // one parity chain n = p, p+2, ..., (chain position k, n = p + 2k):
@@ -125,102 +126,6 @@ struct SweepRec {
   __device__ SweepRec(const double* base, int n1, double lam_)
       : inv_den(base), Q(base + n1), inv_sum(base + 2 * n1), lam(lam_) {}
 };
-
-// Parity-p part of (D^2 - lam) g = r (rows 0..N-2), sum_{n = p mod 2} g_n = beta.
-template <int E>
-__device__ inline void wsweep(SweepRec sw, const double* __restrict__ hw, int N, int p,
-                              const cd* r, cd beta, cd* g, int l) {
-  const int n1 = N + 1;
-  const int nmax = top_index(N, p);
-  const int M = (nmax - p) / 2;
-  const double inv_sum = sw.inv_sum[p];
-  cd a[E], x[E], P[E];
-  double b[E], qv[E], Qv[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int k = l * E + e;
-    const int n = p + 2 * k;
-    const double act = mask(k >= 1 && k <= M);
-    const int nc = (k < 1) ? p + 2 : (k > M ? nmax : n);  // a valid chain element >= 2
-    const cd rm = r[nc - 2];
-    const cd r0 = r[nc];
-    const cd rp = r[nc + 2 <= nmax ? nc + 2 : nmax];  // same parity: written by the caller
-    const double w1 = hw[nc];
-    const double w2 = hw[n1 + nc] * mask(nc <= N - 2);
-    const double w3 = hw[2 * n1 + nc] * mask(nc + 2 <= N - 2);
-    const double id = sw.inv_den[nc];
-    qv[e] = sw.lam * w1 * id * act;  // q = lam w1 / den
-    Qv[e] = sw.Q[nc];
-    a[e] = (rm * w1 + r0 * w2 + rp * w3) * (id * act);
-    b[e] = fma(sw.lam * w3 * id, act, 1.0 - act);  // -cc / den = lam w3 / den on the chain, 1 elsewhere
-  }
-  rec_down<E>(a, b, cd(0.0), x);
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int k = l * E + e;
-    const double act = mask(k >= 1 && k <= M);
-    a[e] = x[e] * act;
-    b[e] = qv[e] + (1.0 - act);  // q on the chain, 1 elsewhere
-  }
-  rec_up<E>(a, b, cd(0.0), P);
-  cd s(0.0);
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int k = l * E + e;
-    s = s + P[e] * mask(k >= 1 && k <= M);
-  }
-  s = row_sum(s);
-  const cd g0 = (beta - s) * inv_sum;
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int k = l * E + e;
-    const int n = p + 2 * k;
-    if (k == 0)
-      g[n] = g0;
-    else if (k <= M)
-      g[n] = P[e] + g0 * Qv[e];
-  }
-}
-
-// Stores its argument (the plain derivative).
-struct StoreDeriv {
-  __device__ cd operator()(int, cd v) const { return v; }
-};
-
-// Uses the loaded entry as it is.
-struct LoadDeriv {
-  __device__ cd operator()(int, cd v, bool) const { return v; }
-};
-
-// b = D a for the parity-pa entries of a (b: parity 1-pa entries, b_N = 0 if it exists);
-// bout[m] receives post(m, b_m), so that an element-wise step on b is taken where
-// each entry is stored, and entry a_n enters as pre(n, a_n, own), own telling the
-// one lane that owns n (the lane of chain position (n - pa) / 2, as in SP_ROW_PAR),
-// so that an element-wise step on a is taken where each entry is loaded.
-template <int E, class Post = StoreDeriv, class Pre = LoadDeriv>
-__device__ inline void wderiv(int N, int pa, const cd* a, cd* bout, int l, Post post = Post(),
-                              Pre pre = Pre()) {
-  const int nmax = top_index(N, pa);
-  const int K = (nmax - pa) / 2;
-  cd c[E], x[E];
-  double one[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int k = l * E + e;
-    const int n = pa + 2 * k;
-    one[e] = 1.0;
-    const int nc = (k <= K) ? n : nmax;
-    c[e] = pre(nc, a[nc], k <= K) * ((2.0 * n) * mask(k <= K && n >= 1));
-  }
-  rec_down<E>(c, one, cd(0.0), x);
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int k = l * E + e;
-    const int n = pa + 2 * k;
-    if (k <= K && n >= 1) bout[n - 1] = post(n - 1, (n == 1) ? x[e] * 0.5 : x[e]);
-  }
-  if (l == 0 && nmax + 1 <= N) bout[nmax + 1] = post(nmax + 1, cd(0.0));
-}
 
 // Transposes (adjoint, beta = 0): rbar = H^T gbar on the parity-p chain.
 // db (LDS scratch indexed by n, distinct per row) receives the intermediate

@@ -140,6 +140,7 @@ struct sp_plan {
   double* d_Tinv = nullptr;   // [ny][ny] analysis
   double* d_G = nullptr;      // [ny][ny] Gram matrix int T_n T_m
   double* d_hw = nullptr;     // [3][ny] Helmholtz right-hand-side weights
+  double* d_hwp = nullptr;    // the same zero padded, [3][ny + 2] (solve_reg.h)
   double* d_mode = nullptr;   // per-mode solve records
   int mode_stride = 0;
   double2* d_twx = nullptr;   // [px] exp(-2 pi i k / px)
