@@ -274,6 +274,38 @@ __global__ void __launch_bounds__(256)
 // LDS operations and keeps the compiler from moving any across it.
 __device__ inline void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup"); }
 
+// Folded columns of the fused analysis: terms per chunk of the FP64 form, padded
+// length, offset of the odd halves (in entries), passes of 64 coefficients whose
+// partial sums wave 1 hands over at once.
+constexpr int kFoldChunk = 3;
+// sets of 32 coefficients that hold n <= ny - 3
+__host__ __device__ constexpr int fold_sets(int ny) { return (ny - 3) / 32 + 1; }
+__host__ __device__ inline int fold_pad(int ny, bool fp32) {
+  const int jh = (ny - 1) / 2 + 1;
+  return fp32 ? (jh + 7) & ~7 : 4 * ((((jh + 3) / 4 + kFoldChunk - 1) / kFoldChunk) * kFoldChunk);
+}
+// FP32: 64 bytes past the even halves' bank; FP64: 128 bytes (with quarters of a
+// multiple of three terms, the four addresses a read broadcasts, even and odd
+// halves of two quarters, then lie in four different 16-byte bank groups)
+__host__ __device__ inline int fold_odd(int ny, bool fp32) {
+  const int n = 3 * fold_pad(ny, fp32);
+  return fp32 ? n + 4 : n + ((8 - n) & 15);
+}
+__host__ __device__ inline int fold_passes(int ny, bool fp32) {
+  return fp32 ? 1 : (fold_sets(ny) + 1) / 2;
+}
+
+// a of this half-wave's lanes plus a of the other half's for lanes 0..31, b plus b
+// for lanes 32..63.
+__device__ inline double half_wave_sum(double a, double b) {
+  const long long ai = __double_as_longlong(a), bi = __double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)ai, (unsigned)bi, false, false);
+  const auto hi =
+      __builtin_amdgcn_permlane32_swap((unsigned)(ai >> 32), (unsigned)(bi >> 32), false, false);
+  return __longlong_as_double(((long long)hi[0] << 32) | (long long)lo[0]) +
+         __longlong_as_double(((long long)hi[1] << 32) | (long long)lo[1]);
+}
+
 // AN = 0: the right-hand side g is read from a canonical field. AN = 1 (FP64)
 // or 2 (FP32 transform path): g = Tinv nv + xa x is formed here from the
 // y-valued product fields nv [3][ny][nz/2][nx] of this mode and the canonical
@@ -287,7 +319,7 @@ __device__ inline void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "w
 // ob x, written in the Hermitian form: the block of an m_z = 0 mode at m_x > 0
 // also writes the conjugate at -m_x (whose block has nothing to do), and the
 // (0,0) mode is real. x's entries n <= N are kept in LDS for it.
-template <int E, int AN, bool RES = false>
+template <int E, int AN, bool RES = false, int NT = 1>
 __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
     __attribute__((amdgpu_waves_per_eu(AN != 0 ? 3 : 1)))
     k_stokes_solve(const double2* __restrict__ g, double2* __restrict__ out,
@@ -311,20 +343,23 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
   cd* A = Fpar;
   cd* U = Rp;
   const int jh = (ny - 1) / 2 + 1;  // folded column length (AN != 0)
-  const int jh8 = (jh + 7) & ~7;    // padded with zeros to whole groups of 8
+  // terms per quarter of the FP64 analysis, in whole chunks of kFoldChunk; the FP32
+  // analysis takes groups of 8. The columns are padded with zeros to jp entries
+  const int jq = (((jh + 3) / 4 + kFoldChunk - 1) / kFoldChunk) * kFoldChunk;
+  const int jp = fold_pad(ny, AN == 2);
   // The folded columns of the analysis share the space of the three arrays
   // above: both waves read them only before the analysis' last barrier, and
   // the arrays are first written after it.
-  cd* colE = Fv;  // [3][jh8] even halves f_j + f_{N-j}
-  // odd halves f_j - f_{N-j} ([3][jh8]), 64 bytes past the even ones so that
-  // the two addresses an analysis load broadcasts fall in different banks
-  cd* colO = colE + 3 * jh8 + 4;
-  const int shared_len = (3 * n1 > 6 * jh8 + 4) ? 3 * n1 : 6 * jh8 + 4;
-  // [6][64] partial sums of wave 1 (which may still read them after the
-  // analysis' last barrier, so they have space of their own)
+  cd* colE = Fv;  // [3][jp] even halves f_j + f_{N-j}
+  // odd halves f_j - f_{N-j} ([3][jp]), placed so that the addresses an analysis
+  // load broadcasts (two, FP32; four, FP64) fall in different banks
+  cd* colO = colE + fold_odd(ny, AN == 2);
+  const int shared_len = max(3 * n1, fold_odd(ny, AN == 2) + 3 * jp);
+  // partial sums of wave 1 (which may still read the columns after wave 0 wrote
+  // the arrays, so they have space of their own): [passes][6][64]
   double* part_raw = reinterpret_cast<double*>(Fv + shared_len);
   // x at n <= N for the residual form ([3][n1]), past wave 1's partial sums
-  cd* Yx = reinterpret_cast<cd*>(part_raw + 6 * 64);
+  cd* Yx = reinterpret_cast<cd*>(part_raw + fold_passes(ny, AN == 2) * 6 * 64);
 
   // logical order: x mode fastest, so the modes whose product-field entries
   // share a cache line (consecutive m_x at one m_z) run on one XCD
@@ -364,11 +399,12 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
   const double ik = mean ? 0.0 : 1.0 / k;
   const double lam = k2 + re * inv_dt;
   // right-hand side columns first (registers), then the mode record, so the
-  // global loads overlap
-  double2 ga[3], gb[3], gc[3];
+  // global loads overlap. NX passes of 64 coefficients hold ny <= 32 E - 1 of them
+  constexpr int NX = (E >= 5) ? 3 : (32 * E + 62) / 64;
+  double2 ga[NX], gb[NX], gc[NX];
   if constexpr (AN == 0) {
 #pragma unroll
-    for (int t = 0; t < 3; ++t) {  // clamped loads, masked after (no per-load branches)
+    for (int t = 0; t < NX; ++t) {  // clamped loads, masked after (no per-load branches)
       const int n = tid + 64 * t;
       const int nc = n <= N - 2 ? n : N - 2;
       const double keep = n <= N - 2 ? 1.0 : 0.0;
@@ -379,12 +415,12 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
       gb[t] = make_double2(gb[t].x * keep, gb[t].y * keep);
       gc[t] = make_double2(gc[t].x * keep, gc[t].y * keep);
     }
-  } else {
+  } else if (!shadow) {
     // u/dt part of the right-hand side: issued first, consumed after the analysis
     // (the residual form keeps x up to n = N)
     constexpr int kTop = RES ? 0 : 2;
 #pragma unroll
-    for (int t = 0; t < 3; ++t) {
+    for (int t = 0; t < NX; ++t) {
       const int n = tid + 64 * t;
       const int nc = n <= N - kTop ? n : N - kTop;
       ga[t] = x[mo + nc];
@@ -392,14 +428,16 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
       gc[t] = x[2 * cs + mo + nc];
     }
   }
-  // fold loads of the y-valued columns (AN != 0) into registers: lane jj takes
-  // f_jj and f_{N-jj}; issued before the record loads so both overlap
+  // fold loads of the y-valued columns (AN != 0) into registers, f_jj and f_{N-jj}
+  // of entry (component, jj), the entries spread over both waves: every lane's
+  // load is a cache line of its own, 64 of the CU's address cycles a load (an x-major
+  // layout that made the columns contiguous took 0.6 us off the solve at 48x65x48 and
+  // put 0.5 us on the x transform that writes them); issued before the record
+  // loads so both overlap
   using RA = typename std::conditional<AN == 2, float, double>::type;
   using CA = typename V2<RA>::T;
-  // folded column entries per lane: jj = tid + 64 q, q < QF; jh <= 64 up to
-  // ny = 128 (E <= 4), so only E = 5 needs a second set
-  constexpr int QF = (E >= 5) ? 2 : 1;
-  CA fa[QF][3], fb[QF][3];
+  constexpr int QF = (E >= 3) ? 2 : 1;  // passes of 128 entries over 3 jp
+  CA fa[QF], fb[QF];
   if constexpr (AN != 0) {
     const CA* nv = reinterpret_cast<const CA*>(nv_raw);
     const int nzm = nzh - 1;
@@ -407,12 +445,12 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
     const size_t base = (size_t)j * nx + i;
 #pragma unroll
     for (int q = 0; q < QF; ++q) {
-      const int jj = tid + 64 * q;
-      const int jc = jj < jh ? jj : jh - 1;
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        fa[q][c] = nv[c * cstride + (size_t)jc * nzm * nx + base];
-        fb[q][c] = nv[c * cstride + (size_t)(N - jc) * nzm * nx + base];
+      const int t = threadIdx.x + 128 * q;
+      if (128 * q < 3 * jp) {  // uniform
+        const int c = min((t >= jp) + (t >= 2 * jp), 2);
+        const int jj = min(t - c * jp, jh - 1);
+        fa[q] = nv[c * cstride + (size_t)jj * nzm * nx + base];
+        fb[q] = nv[c * cstride + (size_t)(N - jj) * nzm * nx + base];
       }
     }
   }
@@ -430,20 +468,41 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
       rv[q] = (tc < stride) ? src[tc] : hwp_g[tc - stride];
     }
   }
+  // table entries th[j][n] of the FP64 analysis: quarter j0 .. of the terms and the
+  // coefficients n = q32 + 32 t, kFoldRing chunks of terms ahead of their use, the
+  // first ones issued here (clamped: the padded terms meet zeros, coefficients
+  // past N - 2 are dropped). Loaded one chunk ahead, the table's L2 latency was
+  // 1.9 k cycles a chunk and most of the analysis
+  const int q32 = tid & 31;
+  const int j0 = ((shadow ? 2 : 0) + (tid >> 5)) * jq;
+  auto table = [&](int chunk, double (&o)[kFoldChunk][NT]) {
+    const double* Ti = reinterpret_cast<const double*>(tinv_raw);
+#pragma unroll
+    for (int q = 0; q < kFoldChunk; ++q) {
+      const double* r = Ti + (size_t)min(j0 + chunk * kFoldChunk + q, jh - 1) * ny;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) o[q][t] = r[min(q32 + 32 * t, N)];
+    }
+  };
+  constexpr int kFoldRing = NT >= 4 ? 2 : 3;  // as many as 168 registers hold
+  double tv[kFoldRing][kFoldChunk][NT];
+  if constexpr (AN == 1) {
+#pragma unroll
+    for (int d = 0; d < kFoldRing; ++d) table(d, tv[d]);  // past the last chunk: re-reads
+  }
   if constexpr (AN != 0) {
-    // even / odd halves, zero padded to jh8 entries
+    // even / odd halves, zero padded to jp entries
 #pragma unroll
     for (int q = 0; q < QF; ++q) {
-      const int jj = tid + 64 * q;
-      if (jj < jh8 && !shadow) {
+      const int t = threadIdx.x + 128 * q;
+      if (t < 3 * jp) {
+        const int c = (t >= jp) + (t >= 2 * jp);
+        const int jj = t - c * jp;
         const double in = jj < jh ? 1.0 : 0.0;
         const double same = (jj == N - jj) ? 0.0 : 1.0;  // middle point counted once
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          const double ar = fa[q][c].x, ai = fa[q][c].y, br = fb[q][c].x, bi = fb[q][c].y;
-          colE[c * jh8 + jj] = cd((ar + same * br) * in, (ai + same * bi) * in);
-          colO[c * jh8 + jj] = cd((ar - br) * same * in, (ai - bi) * same * in);
-        }
+        const double ar = fa[q].x, ai = fa[q].y, br = fb[q].x, bi = fb[q].y;
+        colE[t] = cd((ar + same * br) * in, (ai + same * bi) * in);
+        colO[t] = cd((ar - br) * same * in, (ai - bi) * same * in);
       }
     }
   }
@@ -452,30 +511,113 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
     const int t = threadIdx.x + 64 * NW * q;
     if (t < tot) rec[t] = rv[q];
   }
-  if constexpr (AN != 0) {
-    // g_n = sum_j Tinv[n][j] f_j + xa x_n for n <= N-2 (the tau rows), one n per lane
-    using R = typename std::conditional<AN == 2, float, double>::type;
-    const R* Ti = reinterpret_cast<const R*>(tinv_raw);
-    __syncthreads();
-    const int tmax = (N - 2) / 64 + 1;  // passes over n <= N-2 (uniform)
-    // groups of 8 folded terms: wave 0 sums [0, gsplit), wave 1 [gsplit, ng), the
-    // larger share to wave 1 (wave 0 also stores the folded columns before, and
-    // goes on with the solve after)
-    const int ng = jh8 / 8;
-    const int gsplit = (NW == 2) ? ng / 2 : ng;
-    const int gbeg = shadow ? gsplit : 0;
-    const int gend = shadow ? ng : gsplit;
-    R* part = reinterpret_cast<R*>(part_raw);  // [6][64] partial sums of wave 1
+  if constexpr (RES) {  // x for the output (read after the analysis' last barrier)
+    if (!shadow) {
 #pragma unroll
-    for (int t = 0; t < 3; ++t) {
-      if constexpr (RES) {
+      for (int t = 0; t < NX; ++t) {
         const int n = tid + 64 * t;
-        if (!shadow && n <= N) {
+        if (n <= N) {
           Yx[n] = cd(ga[t].x, ga[t].y);
           Yx[n1 + n] = cd(gb[t].x, gb[t].y);
           Yx[2 * n1 + n] = cd(gc[t].x, gc[t].y);
         }
       }
+    }
+  }
+  // g_n = sum_j Tinv[n][j] f_j + xa x_n for n <= N-2 (the tau rows)
+  if constexpr (AN == 1) {
+    // FP64: the four half-waves of the block take a quarter of the folded terms
+    // each; a lane sums the coefficients n = q + 32 t (q = lane of the half-wave,
+    // so one parity), whose operands are the same three LDS entries, broadcast.
+    // The LDS pipe bounds this step (a 16-byte read of a wave costs it eight
+    // cycles or more, whatever the number of distinct addresses), so each read
+    // serves NT coefficients: 3 jq reads a wave, where one coefficient per lane and
+    // pass took 24 reads per 8 terms. With the gather spread over both waves
+    // and the table ahead of its use, the solve fell from 11.9 to 11.0 us at
+    // 48x65x48, 7.6 to 6.5 at 32x33x32, 55 to 43.5 at 96x97x96.
+    const int nch = jq / kFoldChunk;
+    const cd* src = ((tid & 1) ? colO : colE) + j0;
+    double acc[NT][6];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int c = 0; c < 6; ++c) acc[t][c] = 0.0;
+    __syncthreads();
+    for (int cb = 0; cb < nch; cb += kFoldRing) {
+#pragma unroll
+      for (int d = 0; d < kFoldRing; ++d) {
+        if (cb + d < nch) {  // uniform
+          double tw[kFoldChunk][NT];
+#pragma unroll
+          for (int q = 0; q < kFoldChunk; ++q)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) tw[q][t] = tv[d][q][t];
+          if (cb + d + kFoldRing < nch) table(cb + d + kFoldRing, tv[d]);
+#pragma unroll
+          for (int q = 0; q < kFoldChunk; ++q) {
+            const int jb = (cb + d) * kFoldChunk + q;
+            const cd e0 = src[jb], e1 = src[jp + jb], e2 = src[2 * jp + jb];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+              acc[t][0] += tw[q][t] * e0.re;
+              acc[t][1] += tw[q][t] * e0.im;
+              acc[t][2] += tw[q][t] * e1.re;
+              acc[t][3] += tw[q][t] * e1.im;
+              acc[t][4] += tw[q][t] * e2.re;
+              acc[t][5] += tw[q][t] * e2.im;
+            }
+          }
+        }
+      }
+    }
+    // the two half-waves' sums of coefficients q + 32 (2 p) and q + 32 (2 p + 1)
+    // change places, which leaves lane tid with coefficient n = tid + 64 p
+    constexpr int NP = (NT + 1) / 2;
+    double sum[NP][6];
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+      for (int c = 0; c < 6; ++c)
+        sum[p][c] = half_wave_sum(acc[2 * p][c], 2 * p + 1 < NT ? acc[2 * p + 1 < NT ? 2 * p + 1 : 0][c] : 0.0);
+    double* part = part_raw;
+    if (shadow) {
+#pragma unroll
+      for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int c = 0; c < 6; ++c) part[(6 * p + c) * 64 + tid] = sum[p][c];
+    }
+    __syncthreads();
+    if (!shadow) {
+#pragma unroll
+      for (int t = 0; t < NX; ++t) {
+        const int n = tid + 64 * t;
+        if (t < NP) {
+          double s[6];
+#pragma unroll
+          for (int c = 0; c < 6; ++c) s[c] = sum[t < NP ? t : 0][c] + part[(6 * t + c) * 64 + tid];
+          const double keep = n <= N - 2 ? 1.0 : 0.0;
+          ga[t] = make_double2((s[0] + xa * ga[t].x) * keep, (s[1] + xa * ga[t].y) * keep);
+          gb[t] = make_double2((s[2] + xa * gb[t].x) * keep, (s[3] + xa * gb[t].y) * keep);
+          gc[t] = make_double2((s[4] + xa * gc[t].x) * keep, (s[5] + xa * gc[t].y) * keep);
+        } else {
+          ga[t] = gb[t] = gc[t] = make_double2(0.0, 0.0);
+        }
+      }
+    }
+  }
+  if constexpr (AN == 2) {
+    // FP32: one coefficient per lane and pass, FP32 sums in a fixed order
+    const float* Ti = reinterpret_cast<const float*>(tinv_raw);
+    __syncthreads();
+    const int tmax = (N - 2) / 64 + 1;  // passes over n <= N-2 (uniform)
+    // groups of 8 folded terms: wave 0 sums [0, gsplit), wave 1 [gsplit, ng)
+    const int ng = jp / 8;
+    const int gsplit = ng / 2;
+    const int gbeg = shadow ? gsplit : 0;
+    const int gend = shadow ? ng : gsplit;
+    float* part = reinterpret_cast<float*>(part_raw);  // [6][64] partial sums of wave 1
+#pragma unroll
+    for (int t = 0; t < NX; ++t) {
       if (t >= tmax) {
         ga[t] = gb[t] = gc[t] = make_double2(0.0, 0.0);
         continue;
@@ -483,13 +625,13 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
       const int n = tid + 64 * t;
       const int nc = n <= N - 2 ? n : N - 2;
       const cd* src = (nc & 1) ? colO : colE;
-      const R* col = Ti + nc;  // th[j][n]: consecutive n across lanes
-      R a0r = 0, a0i = 0, a1r = 0, a1i = 0, a2r = 0, a2i = 0;
+      const float* col = Ti + nc;  // th[j][n]: consecutive n across lanes
+      float a0r = 0, a0i = 0, a1r = 0, a1i = 0, a2r = 0, a2i = 0;
       {
         // the table entries of the next group of 8 are loaded while this group
         // is summed (indexes clamped into the table, so the last prefetch is a
         // harmless re-read)
-        R tv[8], tn[8];
+        float tv[8], tn[8];
 #pragma unroll
         for (int q = 0; q < 8; ++q)
           tv[q] = col[(size_t)(8 * gbeg + q < jh ? 8 * gbeg + q : jh - 1) * ny];
@@ -503,46 +645,46 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
               e0[q] = src[j0 + h + q];
-              e1[q] = src[jh8 + j0 + h + q];
-              e2[q] = src[2 * jh8 + j0 + h + q];
+              e1[q] = src[jp + j0 + h + q];
+              e2[q] = src[2 * jp + j0 + h + q];
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-              a0r += tv[h + q] * (R)e0[q].re;
-              a0i += tv[h + q] * (R)e0[q].im;
-              a1r += tv[h + q] * (R)e1[q].re;
-              a1i += tv[h + q] * (R)e1[q].im;
-              a2r += tv[h + q] * (R)e2[q].re;
-              a2i += tv[h + q] * (R)e2[q].im;
+              a0r += tv[h + q] * (float)e0[q].re;
+              a0i += tv[h + q] * (float)e0[q].im;
+              a1r += tv[h + q] * (float)e1[q].re;
+              a1i += tv[h + q] * (float)e1[q].im;
+              a2r += tv[h + q] * (float)e2[q].re;
+              a2i += tv[h + q] * (float)e2[q].im;
             }
           }
 #pragma unroll
           for (int q = 0; q < 8; ++q) tv[q] = tn[q];
         }
       }
-      if constexpr (NW == 2) {
-        if (shadow) {
-          part[tid] = a0r;
-          part[64 + tid] = a0i;
-          part[128 + tid] = a1r;
-          part[192 + tid] = a1i;
-          part[256 + tid] = a2r;
-          part[320 + tid] = a2i;
-        }
-        __syncthreads();
+      if (shadow) {
+        part[tid] = a0r;
+        part[64 + tid] = a0i;
+        part[128 + tid] = a1r;
+        part[192 + tid] = a1i;
+        part[256 + tid] = a2r;
+        part[320 + tid] = a2i;
+      }
+      __syncthreads();
+      if (!shadow) {
         a0r += part[tid];
         a0i += part[64 + tid];
         a1r += part[128 + tid];
         a1i += part[192 + tid];
         a2r += part[256 + tid];
         a2i += part[320 + tid];
-        if (t + 1 < tmax) __syncthreads();  // the next pass rewrites part (uniform)
+        const double keep = n <= N - 2 ? 1.0 : 0.0;
+        const double2 x0 = ga[t], x1 = gb[t], x2 = gc[t];
+        ga[t] = make_double2(((double)a0r + xa * x0.x) * keep, ((double)a0i + xa * x0.y) * keep);
+        gb[t] = make_double2(((double)a1r + xa * x1.x) * keep, ((double)a1i + xa * x1.y) * keep);
+        gc[t] = make_double2(((double)a2r + xa * x2.x) * keep, ((double)a2i + xa * x2.y) * keep);
       }
-      const double keep = n <= N - 2 ? 1.0 : 0.0;
-      const double2 x0 = ga[t], x1 = gb[t], x2 = gc[t];
-      ga[t] = make_double2(((double)a0r + xa * x0.x) * keep, ((double)a0i + xa * x0.y) * keep);
-      gb[t] = make_double2(((double)a1r + xa * x1.x) * keep, ((double)a1i + xa * x1.y) * keep);
-      gc[t] = make_double2(((double)a2r + xa * x2.x) * keep, ((double)a2i + xa * x2.y) * keep);
+      if (t + 1 < tmax) __syncthreads();  // the next pass rewrites part (uniform)
     }
   }
   // wave 1's part ended with the analysis' last barrier (it is uniform per wave):
@@ -551,7 +693,7 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
   if (shadow) return;
   {
 #pragma unroll
-    for (int t = 0; t < 3; ++t) {
+    for (int t = 0; t < NX; ++t) {
       const int n = tid + 64 * t;
       if (n < n1) {
         const cd fu(re * ga[t].x, re * ga[t].y);
@@ -938,30 +1080,37 @@ hipError_t launch_fft_x_fwd_lds(sp_plan* p, const void* in, void* out, int nfiel
 // elements per lane of a 16-lane row covering one parity chain (ny <= 129)
 int solve_lanes_per_chain(int ny) { return ((ny - 1) / 2 + 1 + 15) / 16; }
 
-static size_t solve_lds_bytes(const sp_plan* p, bool fused, bool res = false) {
-  const Dims& d = p->d;
-  const size_t jh8 = (((d.ny - 1) / 2 + 1) + 7) & ~7;
+// an: 0 (given right-hand side), 1 (fused analysis, FP64), 2 (FP32)
+static size_t solve_lds_bytes(const sp_plan* p, int an, bool res = false) {
+  const int ny = p->d.ny;
   // three arrays of ny entries, which the fused analysis' folded columns share
-  const size_t arrays = fused ? std::max<size_t>(3 * (size_t)d.ny, 6 * jh8 + 4) : 3 * (size_t)d.ny;
-  const size_t rec = ((size_t)p->mode_stride + 3 * hwp_row(d.ny) + 1) / 2 * 2;
-  return rec * sizeof(double) + arrays * sizeof(cd) + (fused ? 6 * 64 * sizeof(double) : 0) +
-         (res ? 3 * (size_t)d.ny * sizeof(cd) : 0);
+  const size_t arrays =
+      an ? std::max(3 * ny, fold_odd(ny, an == 2) + 3 * fold_pad(ny, an == 2)) : 3 * ny;
+  const size_t rec = ((size_t)p->mode_stride + 3 * hwp_row(ny) + 1) / 2 * 2;
+  return rec * sizeof(double) + arrays * sizeof(cd) +
+         (an ? fold_passes(ny, an == 2) * 6 * 64 * sizeof(double) : 0) +
+         (res ? 3 * (size_t)ny * sizeof(cd) : 0);
 }
 
-#define SP_SOLVE_DISPATCH(LAUNCH)                   \
-  switch (solve_reg_elems(p->d.ny)) {               \
-    case 1: LAUNCH(1); break;                       \
-    case 2: LAUNCH(2); break;                       \
-    case 3: LAUNCH(3); break;                       \
-    case 4: LAUNCH(4); break;                       \
-    default: LAUNCH(5); break;                      \
+// LAUNCH(E, NT): elements per lane and chain, sets of 32 coefficients of the FP64
+// analysis (ny <= 32 E - 1 and n <= ny - 3 leave NT = E - 1 or E)
+#define SP_SOLVE_DISPATCH(LAUNCH)                                        \
+  switch (10 * solve_reg_elems(p->d.ny) + fold_sets(p->d.ny)) {          \
+    case 11: LAUNCH(1, 1); break;                                        \
+    case 21: LAUNCH(2, 1); break;                                        \
+    case 22: LAUNCH(2, 2); break;                                        \
+    case 32: LAUNCH(3, 2); break;                                        \
+    case 33: LAUNCH(3, 3); break;                                        \
+    case 43: LAUNCH(4, 3); break;                                        \
+    case 44: LAUNCH(4, 4); break;                                        \
+    default: LAUNCH(5, 4); break;                                        \
   }
 
 hipError_t launch_stokes_solve(sp_plan* p, const double2* g, double2* out, int inhomogeneous) {
   const Dims& d = p->d;
-  const size_t sh = solve_lds_bytes(p, false);
+  const size_t sh = solve_lds_bytes(p, 0);
   SP_PROF_BEGIN(p, KID_SOLVE);
-#define SP_SOLVE_LAUNCH(EV)                                                                     \
+#define SP_SOLVE_LAUNCH(EV, NTV)                                                                     \
   hipLaunchKernelGGL((k_stokes_solve<EV, 0>), dim3(d.nx * d.nzh), dim3(64), sh, p->stream, g,   \
                      out, p->d_mode, p->d_hwp, p->mode_stride, d.nx, d.ny, d.nzh, d.alpha,       \
                      d.gamma, d.re, d.inv_dt, d.wall_upper, d.wall_lower, inhomogeneous, nullptr, \
@@ -976,16 +1125,16 @@ hipError_t launch_stokes_solve(sp_plan* p, const double2* g, double2* out, int i
 hipError_t launch_analysis_solve(sp_plan* p, const double2* x, double xa, double2* out,
                                  int inhomogeneous, bool fp32) {
   const Dims& d = p->d;
-  const size_t sh = solve_lds_bytes(p, true);
+  const size_t sh = solve_lds_bytes(p, fp32 ? 2 : 1);
   SP_PROF_BEGIN(p, KID_SOLVE);
-#define SP_SOLVE_LAUNCH(EV)                                                                       \
+#define SP_SOLVE_LAUNCH(EV, NTV)                                                                       \
   if (fp32)                                                                                       \
     hipLaunchKernelGGL((k_stokes_solve<EV, 2>), dim3(d.nx * d.nzh), dim3(128), sh, p->stream,      \
                        nullptr, out, p->d_mode, p->d_hwp, p->mode_stride, d.nx, d.ny, d.nzh,      \
                        d.alpha, d.gamma, d.re, d.inv_dt, d.wall_upper, d.wall_lower,             \
                        inhomogeneous, p->nv, p->f_tinv_th, x, xa, 1.0, 0.0);                         \
   else                                                                                            \
-    hipLaunchKernelGGL((k_stokes_solve<EV, 1>), dim3(d.nx * d.nzh), dim3(128), sh, p->stream,      \
+    hipLaunchKernelGGL((k_stokes_solve<EV, 1, false, NTV>), dim3(d.nx * d.nzh), dim3(128), sh, p->stream,      \
                        nullptr, out, p->d_mode, p->d_hwp, p->mode_stride, d.nx, d.ny, d.nzh,      \
                        d.alpha, d.gamma, d.re, d.inv_dt, d.wall_upper, d.wall_lower,             \
                        inhomogeneous, p->nv, p->d_tinv_th, x, xa, 1.0, 0.0)
@@ -1000,16 +1149,16 @@ hipError_t launch_analysis_solve(sp_plan* p, const double2* x, double xa, double
 hipError_t launch_analysis_solve_res(sp_plan* p, const double2* x, double xa, double oa, double ob,
                                      double2* out, bool fp32) {
   const Dims& d = p->d;
-  const size_t sh = solve_lds_bytes(p, true, true);
+  const size_t sh = solve_lds_bytes(p, fp32 ? 2 : 1, true);
   SP_PROF_BEGIN(p, KID_SOLVE);
-#define SP_SOLVE_LAUNCH(EV)                                                                       \
+#define SP_SOLVE_LAUNCH(EV, NTV)                                                                       \
   if (fp32)                                                                                       \
     hipLaunchKernelGGL((k_stokes_solve<EV, 2, true>), dim3(d.nx * d.nzh), dim3(128), sh,           \
                        p->stream, nullptr, out, p->d_mode, p->d_hwp, p->mode_stride, d.nx, d.ny,  \
                        d.nzh, d.alpha, d.gamma, d.re, d.inv_dt, d.wall_upper, d.wall_lower, 0,   \
                        p->nv, p->f_tinv_th, x, xa, oa, ob);                                      \
   else                                                                                            \
-    hipLaunchKernelGGL((k_stokes_solve<EV, 1, true>), dim3(d.nx * d.nzh), dim3(128), sh,           \
+    hipLaunchKernelGGL((k_stokes_solve<EV, 1, true, NTV>), dim3(d.nx * d.nzh), dim3(128), sh,           \
                        p->stream, nullptr, out, p->d_mode, p->d_hwp, p->mode_stride, d.nx, d.ny,  \
                        d.nzh, d.alpha, d.gamma, d.re, d.inv_dt, d.wall_upper, d.wall_lower, 0,   \
                        p->nv, p->d_tinv_th, x, xa, oa, ob)
