@@ -228,10 +228,13 @@ sp_status sp_unpack(sp_plan* plan, const double* packed, double* canonical);
  * Jacobian columns): count canonical fields stored one after another in u
  * (du) and out. sp_befe_step_batch: out_i = Phi_dt(u_i) as sp_befe_step;
  * sp_jvp_lin_batch: out_i = the Jacobian action of sp_jvp_lin on du_i about
- * the cached base state (SP_OP_RESIDUAL only for the one-step operator). Up to
- * nstreams (1..8) members run concurrently (3 fill, with the plan's own
- * stream, the 4 hardware queues a process gets by default), each with its own intermediates
- * (about 10 canonical fields) and stream, allocated on first use and kept
+ * the cached base state (SP_OP_RESIDUAL only for the one-step operator). The
+ * members run in groups, one launch of each kernel per group: as many members as
+ * keep a group's intermediates within 128 MiB (one at least, 256 at most). A call
+ * of one group runs on the plan's stream; of several, up to nstreams (1..8) groups
+ * run concurrently (3 fill, with the plan's own stream, the 4 hardware queues a
+ * process gets by default), each with its own intermediates and stream. These
+ * are allocated on first use and kept
  * until sp_plan_destroy; the plan's stream waits for all members before the
  * call returns its work, so results are ordered like those of single calls and
  * equal to them bit for bit. SP_ERR_INVALID for count < 0, nstreams outside
@@ -250,9 +253,9 @@ sp_status sp_jvp_lin_batch(sp_plan* plan, int32_t op, int32_t count, int32_t nst
  * count = 0, which does nothing). Each column is formed
  * on the device (unit vector, unpack, Jacobian action, pack) without host
  * synchronisation. For the one-step operators (SP_OP_PHI, or SP_OP_RESIDUAL
- * with one BEFE step, no laminar advection) and count >= 8 the columns are
- * spread over 3 concurrent members as in sp_jvp_lin_batch, each with its own
- * unit vector and fields; the multi-step chain forms them one after another.
+ * with one BEFE step, no laminar advection) the columns run in groups as in
+ * sp_jvp_lin_batch (3 streams where there are several), each group with its own
+ * unit fields; the multi-step chain forms them one after another.
  * The plan's stream waits for all of them. Buffers are allocated on first use
  * and kept until sp_plan_destroy (SP_ERR_NOMEM if that fails). SP_ERR_INVALID for a bad
  * op, a range outside [0, packed_n), ld < packed_n or no base state. */

@@ -225,9 +225,10 @@ class Plan:
         return C.c_void_p(t.data_ptr())
 
     def befe_step_batch(self, u, out=None, streams: int = 3):
-        """Phi_dt of each of the count fields u[i] (a (count, *shape) tensor),
-        up to `streams` of them concurrently (3 with the plan's own stream
-        fill the 4 hardware queues a process gets by default)."""
+        """Phi_dt of each of the count fields u[i] (a (count, *shape) tensor), in
+        groups that share their launches, up to `streams` groups concurrently
+        (3 with the plan's own stream fill the 4 hardware queues a process
+        gets by default)."""
         torch = _torch()
         out = torch.empty_like(u) if out is None else out
         self._check(self.lib.sp_befe_step_batch(self.h, u.shape[0], streams,

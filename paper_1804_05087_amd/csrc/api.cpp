@@ -433,92 +433,127 @@ extern "C" sp_status sp_unpack(sp_plan* p, const double* packed, double* canonic
 }
 
 // ---- batched calls ----------------------------------------------------------------
-// Member i of a batch runs the unchanged pipeline on buffer set i mod S and its
-// stream, S = nstreams: while a member's launches are issued the plan's
-// intermediate pointers and stream point at its set (kernels take pointers and
-// the stream at launch), so up to S members execute concurrently. The sets'
+// The members of a batch run in groups: one launch of every kernel of the pipeline
+// covers a whole group (the members are a dimension of the grid), so that small
+// grids fill the chip and the launches, which bound them (four of 3 to 7 us for
+// one member at 16x17x16), are shared. One group runs on the plan's stream; with
+// more than one, group i runs on buffer set i mod S and its stream, S = nstreams:
+// while a group's launches are issued the plan's intermediate pointers and stream
+// point at its set (kernels take pointers and the stream at launch). The sets'
 // streams wait for the plan's stream before the batch, and the plan's stream
 // waits for them after it.
-static sp_status ensure_batch(sp_plan* p, int nstreams) {
+static void member_strides(const sp_plan* p, Members& m) {
+  const Dims& d = p->d;
+  m.yv = (size_t)6 * d.ny * d.nzm * d.nx;
+  // no x-physical fields where the z-line kernel takes the inverse x transforms (in
+  // FP64, then in FP32 too)
+  m.xp = zline_fuses_x_inverse(p, false, 5) ? 0 : (size_t)6 * d.ny * d.px * d.nzm;
+  m.np = (size_t)3 * d.ny * d.px * d.nzm;
+  m.nv = (size_t)3 * d.ny * d.nzm * d.nx;
+  m.in = m.out = canon_count(p);
+}
+
+// Members per group: as many as keep a group's intermediates within 128 MiB (half of
+// the Infinity Cache), one at least, 256 at most. Measured, us per member, one
+// stream: 24 fields of 32x33x32 in groups within 8, 32, 64, 128 and 256 MiB (with
+// x-physical fields, twice the bytes) 26.6, 9.1, 7.4, 6.4 and 4.8; 64 of 48x65x48
+// 41.9, 41.9, 31.1, 24.1, 21.1; 512 Jacobian columns of 16x17x16 2.3, 1.0, 0.95,
+// 0.89, 0.88 (19.6 one member at a time on three streams). With groups of one
+// (96x97x96) the streams overlap members: 231 us on one stream, 191 on two.
+static constexpr size_t kGroupBytes = (size_t)128 << 20;
+static constexpr size_t kGroupMost = 256;
+static int group_members(const sp_plan* p) {
+  Members m;
+  member_strides(p, m);
+  const size_t n = kGroupBytes / ((m.yv + m.xp + m.np + m.nv) * sizeof(double2));
+  return n < 1 ? 1 : (n > kGroupMost ? (int)kGroupMost : (int)n);
+}
+
+static sp_status ensure_batch(sp_plan* p, int nsets) {
   if (!p->bstart && hipEventCreateWithFlags(&p->bstart, hipEventDisableTiming) != hipSuccess) {
     p->bstart = nullptr;
     return set_error(p, SP_ERR_HIP, "cannot create the batch event");
   }
-  const Dims& d = p->d;
-  const size_t cz = sizeof(double2), canon = canon_count(p) * cz;
-  const size_t sizes[7] = {(size_t)6 * d.ny * d.nzm * d.nx * cz, (size_t)6 * d.ny * d.px * d.nzm * cz,
-                           (size_t)3 * d.ny * d.px * d.nzm * cz, (size_t)3 * d.ny * d.nzm * d.nx * cz,
-                           canon, canon, canon};
+  Members m;
+  member_strides(p, m);
+  const size_t sizes[4] = {m.yv, m.xp, m.np, m.nv};
+  const size_t G = group_members(p);
   size_t total = 0;
-  for (size_t b : sizes) total += (b + 255) / 256 * 256;
-  while ((int)p->bsets.size() < nstreams) {
+  for (size_t b : sizes) total += (b * G * sizeof(double2) + 255) / 256 * 256;
+  while ((int)p->bsets.size() < nsets) {
     BatchSet b;
     if (hipMalloc(&b.mem, total) != hipSuccess) {
       (void)hipGetLastError();
-      return set_error(p, SP_ERR_NOMEM, "cannot allocate the intermediates of a batch member");
+      return set_error(p, SP_ERR_NOMEM, "cannot allocate the intermediates of a batch");
     }
     if (hipStreamCreateWithFlags(&b.s, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&b.done, hipEventDisableTiming) != hipSuccess) {
       (void)hipGetLastError();
       if (b.s) (void)hipStreamDestroy(b.s);
       (void)hipFree(b.mem);
-      return set_error(p, SP_ERR_HIP, "cannot create the stream of a batch member");
+      return set_error(p, SP_ERR_HIP, "cannot create the stream of a batch");
     }
-    void** dst[7] = {&b.yv, &b.xp, &b.np, &b.nv, (void**)&b.g, (void**)&b.t1, (void**)&b.t2};
+    void** dst[4] = {&b.yv, &b.xp, &b.np, &b.nv};
     size_t off = 0;
-    for (int k = 0; k < 7; ++k) {
+    for (int k = 0; k < 4; ++k) {
       *dst[k] = (char*)b.mem + off;
-      off += (sizes[k] + 255) / 256 * 256;
+      off += (sizes[k] * G * sizeof(double2) + 255) / 256 * 256;
     }
     p->bsets.push_back(b);
   }
   return SP_OK;
 }
 
-// Points the plan at one buffer set for the launches issued in its scope.
+// Points the plan at one buffer set, a stream and a group of members for the launches
+// issued in its scope.
 struct BatchView {
   sp_plan* p;
   void *yv, *xp, *np, *nv;
-  double2 *g, *t1, *t2;
   hipStream_t s;
-  BatchView(sp_plan* p_, const BatchSet& b)
-      : p(p_), yv(p_->yv), xp(p_->xp), np(p_->np), nv(p_->nv), g(p_->g), t1(p_->t1), t2(p_->t2),
-        s(p_->stream) {
+  BatchView(sp_plan* p_, const BatchSet& b, hipStream_t stream, int members)
+      : p(p_), yv(p_->yv), xp(p_->xp), np(p_->np), nv(p_->nv), s(p_->stream) {
     p->yv = b.yv;
     p->xp = b.xp;
     p->np = b.np;
     p->nv = b.nv;
-    p->g = b.g;
-    p->t1 = b.t1;
-    p->t2 = b.t2;
-    p->stream = b.s;
+    p->stream = stream;
+    member_strides(p, p->mem);
+    p->mem.nb = members;
   }
   ~BatchView() {
     p->yv = yv;
     p->xp = xp;
     p->np = np;
     p->nv = nv;
-    p->g = g;
-    p->t1 = t1;
-    p->t2 = t2;
     p->stream = s;
+    p->mem = Members();
   }
 };
 
+// group(first, members, set) issues the launches of members first .. first + members - 1.
 template <typename F>
-static sp_status run_batch(sp_plan* p, int count, int nstreams, F member) {
+static sp_status run_batch(sp_plan* p, int count, int nstreams, F group) {
   if (count == 0) return SP_OK;
-  const int S = nstreams < count ? nstreams : count;
+  const int most = group_members(p);
+  const int groups = (count + most - 1) / most;
+  const int G = (count + groups - 1) / groups;  // evened out
+  const int S = nstreams < groups ? nstreams : groups;
   sp_status s = ensure_batch(p, S);
   if (s) return s;
+  if (groups == 1) {
+    BatchView v(p, p->bsets[0], p->stream, count);
+    return group(0, count, p->bsets[0]);
+  }
   SP_TRY_HIP(hipEventRecord(p->bstart, p->stream), "record batch start");
   for (int b = 0; b < S; ++b)
     SP_TRY_HIP(hipStreamWaitEvent(p->bsets[b].s, p->bstart, 0), "batch wait");
-  for (int i = 0; i < count && s == SP_OK; ++i) {
-    BatchView v(p, p->bsets[i % S]);
-    s = member(i);
+  for (int i = 0; i * G < count && s == SP_OK; ++i) {
+    const int members = count - i * G < G ? count - i * G : G;
+    BatchSet& set = p->bsets[i % S];
+    BatchView v(p, set, set.s, members);
+    s = group(i * G, members, set);
   }
-  for (int b = 0; b < S; ++b) {  // join even after an error: no member is left running
+  for (int b = 0; b < S; ++b) {  // join even after an error: no group is left running
     SP_TRY_HIP(hipEventRecord(p->bsets[b].done, p->bsets[b].s), "record batch end");
     SP_TRY_HIP(hipStreamWaitEvent(p->stream, p->bsets[b].done, 0), "batch join");
   }
@@ -536,6 +571,33 @@ extern "C" sp_status sp_jacobian_columns(sp_plan* p, int32_t op, int64_t first, 
     return set_error(p, SP_ERR_INVALID, "columns out of range or ld < packed length");
   if (!p->base_valid) return set_error(p, SP_ERR_INVALID, "no base state: call sp_linearize");
   if (count == 0) return SP_OK;
+  // one-step operators (whose base state the members only read) form the columns in
+  // groups; the multi-step chain re-caches the base per step, so it runs them one
+  // after another
+  const bool one_step = (op == SP_OP_PHI || (p->nsteps == 1 && p->scheme == 0)) && !p->advect;
+  if (one_step) {
+    if (p->base_step != 0) {
+      sp_status s = base_at(p, 0);
+      if (s) return s;
+    }
+    const size_t nc = canon_count(p);
+    return run_batch(p, (int)count, 3, [&](int c0, int members, BatchSet& set) -> sp_status {
+      if (!set.fin) {
+        const size_t cb = nc * sizeof(double2) * group_members(p);
+        if (hipMalloc((void**)&set.fin, 2 * cb) != hipSuccess) {
+          (void)hipGetLastError();
+          set.fin = nullptr;
+          return set_error(p, SP_ERR_NOMEM, "cannot allocate the Jacobian column buffers");
+        }
+        set.fout = set.fin + nc * group_members(p);
+      }
+      SP_TRY_HIP(launch_unit_fields(p, first + c0, members, set.fin), "unit vectors");
+      sp_status st = jvp_lin(p, op, set.fin, set.fout);
+      if (st) return st;
+      SP_TRY_HIP(launch_pack_rows(p, set.fout, members, J + (size_t)c0 * (size_t)ld, ld), "pack");
+      return SP_OK;
+    });
+  }
   if (!p->jc_e) {
     const size_t cb = canon_count(p) * sizeof(double2);
     if (hipMalloc((void**)&p->jc_e, (size_t)n * sizeof(double)) != hipSuccess ||
@@ -550,42 +612,6 @@ extern "C" sp_status sp_jacobian_columns(sp_plan* p, int32_t op, int64_t first, 
       return set_error(p, SP_ERR_NOMEM, "cannot allocate the Jacobian column buffers");
     }
     SP_TRY_HIP(launch_fill(p, p->jc_e, (size_t)n, 0.0), "zero unit vector");
-  }
-  // one-step operators (whose base state the members only read) spread the
-  // columns over 3 streams with their own buffers; the multi-step chain
-  // re-caches the base per step, so it runs them one after another
-  const bool one_step = (op == SP_OP_PHI || (p->nsteps == 1 && p->scheme == 0)) && !p->advect;
-  if (one_step && count >= 8) {
-    if (p->base_step != 0) {
-      sp_status s = base_at(p, 0);
-      if (s) return s;
-    }
-    const int S = 3;  // with the plan's stream: the 4 hardware queues of a process
-    sp_status s = ensure_batch(p, S);
-    if (s) return s;
-    for (int b = 0; b < S; ++b) {
-      BatchSet& bs = p->bsets[b];
-      if (bs.e) continue;
-      const size_t cb = canon_count(p) * sizeof(double2);
-      if (hipMalloc((void**)&bs.e, (size_t)n * sizeof(double)) != hipSuccess ||
-          hipMalloc((void**)&bs.fin, cb) != hipSuccess ||
-          hipMalloc((void**)&bs.fout, cb) != hipSuccess) {
-        (void)hipGetLastError();
-        return set_error(p, SP_ERR_NOMEM, "cannot allocate the Jacobian column buffers");
-      }
-      SP_TRY_HIP(launch_fill(p, bs.e, (size_t)n, 0.0), "zero unit vector");
-    }
-    return run_batch(p, (int)count, S, [&](int c) -> sp_status {
-      BatchSet& bs = p->bsets[c % S];
-      const size_t i = (size_t)(first + c);
-      SP_TRY_HIP(launch_set_entry(p, bs.e, i, 1.0), "unit vector");
-      SP_TRY_HIP(launch_unpack(p, bs.e, bs.fin), "unpack");
-      SP_TRY_HIP(launch_set_entry(p, bs.e, i, 0.0), "unit vector");
-      sp_status st = jvp_lin(p, op, bs.fin, bs.fout);
-      if (st) return st;
-      SP_TRY_HIP(launch_pack(p, bs.fout, J + (size_t)c * (size_t)ld), "pack");
-      return SP_OK;
-    });
   }
   for (int64_t c = 0; c < count; ++c) {
     const size_t i = (size_t)(first + c);
@@ -620,7 +646,7 @@ extern "C" sp_status sp_befe_step_batch(sp_plan* p, int32_t count, int32_t nstre
   if (s) return s;
   const size_t nc = canon_count(p);
   const bool fp32 = (p->precision == SP_MIXED);
-  return run_batch(p, count, nstreams, [&](int i) {
+  return run_batch(p, count, nstreams, [&](int i, int, BatchSet&) {
     return befe_into(p, (const double2*)u + i * nc, (double2*)out + i * nc, fp32);
   });
 }
@@ -639,7 +665,7 @@ extern "C" sp_status sp_jvp_lin_batch(sp_plan* p, int32_t op, int32_t count, int
     if (s) return s;
   }
   const size_t nc = canon_count(p);
-  return run_batch(p, count, nstreams, [&](int i) {
+  return run_batch(p, count, nstreams, [&](int i, int, BatchSet&) {
     return jvp_lin(p, op, (const double2*)du + i * nc, (double2*)out + i * nc);
   });
 }

@@ -39,7 +39,7 @@ template <typename R, int PT>
 __global__ void __launch_bounds__(256)
     k_fft_x_inv(const typename V2<R>::T* __restrict__ yv, typename V2<R>::T* __restrict__ xp,
                 const typename V2<R>::T* __restrict__ tw, FFTPlan1D pl, int nx, int ny, int nzm,
-                int kc, R alpha, R gamma, int plain) {
+                int kc, R alpha, R gamma, int plain, size_t mi, size_t mo) {
   using C = typename V2<R>::T;
   extern __shared__ unsigned char smem_raw[];
   const int px = pl.P;
@@ -47,7 +47,10 @@ __global__ void __launch_bounds__(256)
   C* A = reinterpret_cast<C*>(smem_raw);
   C* B = A + kc * LS;
   C* twl = B + kc * LS;
-  const int y = blockIdx.x;
+  const int member = blockIdx.x / ny;
+  const int y = blockIdx.x - member * ny;
+  yv += member * mi;
+  xp += member * mo;
   const int f = blockIdx.y;
   const int kz0 = blockIdx.z * kc;
   const int nl = min(kc, nzm - kz0);
@@ -113,11 +116,13 @@ template <typename R, int PT>
 __global__ void __launch_bounds__(256)
     k_z_product(const typename V2<R>::T* __restrict__ xp, typename V2<R>::T* __restrict__ np,
                 R* __restrict__ base, const typename V2<R>::T* __restrict__ tw, FFTPlan1D pl,
-                int ny, int px, int nzm, int xc, int mode, R scale) {
+                int ny, int px, int nzm, int xc, int mode, R scale, size_t mi, size_t mo) {
   using C = typename V2<R>::T;
   extern __shared__ unsigned char smem_raw[];
   const int pz = pl.P;
   const int y = blockIdx.x;
+  xp += blockIdx.z * mi;
+  np += blockIdx.z * mo;
   const int x0 = blockIdx.y * xc;
   const int nxl = min(xc, px - x0);
   const int LS = (PT == 0) ? pz : line_stride(PT);
@@ -217,7 +222,7 @@ template <typename R, int PT>
 __global__ void __launch_bounds__(256)
     k_fft_x_fwd(const typename V2<R>::T* __restrict__ np, typename V2<R>::T* __restrict__ nv,
                 const typename V2<R>::T* __restrict__ tw, FFTPlan1D pl, int nx, int ny, int nzm,
-                int kc) {
+                int kc, size_t mi, size_t mo) {
   using C = typename V2<R>::T;
   extern __shared__ unsigned char smem_raw[];
   const int px = pl.P;
@@ -225,7 +230,10 @@ __global__ void __launch_bounds__(256)
   C* A = reinterpret_cast<C*>(smem_raw);
   C* B = A + kc * LS;
   C* twl = B + kc * LS;
-  const int y = blockIdx.x;
+  const int member = blockIdx.x / ny;
+  const int y = blockIdx.x - member * ny;
+  np += member * mi;
+  nv += member * mo;
   const int c = blockIdx.y;
   const int kz0 = blockIdx.z * kc;
   const int nl = min(kc, nzm - kz0);
@@ -319,7 +327,7 @@ __device__ inline double half_wave_sum(double a, double b) {
 // ob x, written in the Hermitian form: the block of an m_z = 0 mode at m_x > 0
 // also writes the conjugate at -m_x (whose block has nothing to do), and the
 // (0,0) mode is real. x's entries n <= N are kept in LDS for it.
-template <int E, int AN, bool RES = false, int NT = 1>
+template <int E, int AN, bool RES = false, int NT = 1, bool MB = false>
 __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
     __attribute__((amdgpu_waves_per_eu(AN != 0 ? 3 : 1)))
     k_stokes_solve(const double2* __restrict__ g, double2* __restrict__ out,
@@ -327,8 +335,13 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
                    int stride, int nx, int ny, int nzh, double alpha, double gamma, double re,
                    double inv_dt, double wu, double wl, int inhomogeneous,
                    const void* __restrict__ nv_raw, const void* __restrict__ tinv_raw,
-                   const double2* __restrict__ x, double xa, double oa = 1.0, double ob = 0.0) {
+                   const double2* __restrict__ x, double xa, double oa = 1.0, double ob = 0.0,
+                   size_t mx = 0, size_t mnv = 0, size_t mout = 0) {
   static_assert(!RES || AN != 0, "the residual form reads x through the fused analysis");
+  if constexpr (MB) {  // members of a batch (grid y)
+    x += blockIdx.y * mx;
+    out += blockIdx.y * mout;
+  }
   extern __shared__ unsigned char smem_raw[];
   const int N = ny - 1;
   const int n1 = ny;
@@ -439,7 +452,7 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
   constexpr int QF = (E >= 3) ? 2 : 1;  // passes of 128 entries over 3 jp
   CA fa[QF], fb[QF];
   if constexpr (AN != 0) {
-    const CA* nv = reinterpret_cast<const CA*>(nv_raw);
+    const CA* nv = reinterpret_cast<const CA*>(nv_raw) + (MB ? blockIdx.y * mnv : 0);
     const int nzm = nzh - 1;
     const size_t cstride = (size_t)ny * nzm * nx;
     const size_t base = (size_t)j * nx + i;
@@ -907,7 +920,10 @@ __global__ void __launch_bounds__(256)
 
 // Packed real vector <-> canonical (see sp.h for the order).
 __global__ void k_pack(const double2* __restrict__ c, double* __restrict__ packed, int nx, int ny,
-                       int nzh) {
+                       int nzh, int64_t ld) {
+  // grid y: fields one after another, packed vectors ld apart
+  c += (size_t)blockIdx.y * 3 * nx * nzh * ny;
+  packed += (size_t)blockIdx.y * ld;
   const int nz = 2 * (nzh - 1);
   const int per_n = (nx - 1) * (nz - 1);  // reals per (component, n)
   const int total = 3 * ny * per_n;
@@ -932,6 +948,38 @@ __global__ void k_pack(const double2* __restrict__ c, double* __restrict__ packe
     }
     const double2 v = c[(((size_t)comp * nx + i) * nzh + j) * ny + n];
     packed[t] = part ? v.y : v.x;
+  }
+}
+
+// Member m of c (grid y) = unpack(e_{first + m}): zero but for the entry the packed
+// index names and, on the m_z = 0 plane at m_x > 0, its conjugate at -m_x.
+__global__ void k_unit_fields(int64_t first, double2* __restrict__ c, int nx, int ny, int nzh) {
+  const int nz = 2 * (nzh - 1);
+  const int per_n = (nx - 1) * (nz - 1);
+  const int total = 3 * nx * nzh * ny;
+  const int64_t v = first + blockIdx.y;
+  const int cn = (int)(v / per_n);
+  const int r = (int)(v - (int64_t)cn * per_n);
+  const int comp = cn / ny;
+  const int n = cn - comp * ny;
+  int i = 0, j = 0, part = 0;
+  if (r >= 1 && r < 1 + 2 * (nx / 2 - 1)) {
+    i = 1 + (r - 1) / 2;
+    part = (r - 1) & 1;
+  } else if (r > 0) {
+    const int q = r - 1 - 2 * (nx / 2 - 1);
+    part = q & 1;
+    j = 1 + (q / 2) / (nx - 1);
+    const int ii = (q / 2) % (nx - 1);
+    i = (ii < nx / 2) ? ii : ii + 1;
+  }
+  const int at = ((comp * nx + i) * nzh + j) * ny + n;
+  const int mirror = (j == 0 && i > 0) ? ((comp * nx + nx - i) * nzh) * ny + n : -1;
+  double2* o = c + (size_t)blockIdx.y * total;
+  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < total; t += gridDim.x * blockDim.x) {
+    const double re = (part == 0 && (t == at || t == mirror)) ? 1.0 : 0.0;
+    const double im = part == 0 ? 0.0 : (t == at ? 1.0 : (t == mirror ? -1.0 : 0.0));
+    o[t] = make_double2(re, im);
   }
 }
 
@@ -1001,17 +1049,17 @@ hipError_t launch_fft_x_inv_lds(sp_plan* p, const void* in, void* out, int nfiel
   const Dims& d = p->d;
   const size_t el = fp32 ? sizeof(float2) : sizeof(double2);
   const int kc = chunk_for(d.px, d.nzm, el);
-  dim3 grid(d.ny, nfields, (d.nzm + kc - 1) / kc);
+  dim3 grid(d.ny * p->mem.nb, nfields, (d.nzm + kc - 1) / kc);
   const size_t sh = (2 * (size_t)kc * lds_line(d.px) + d.px) * el;
   SP_PROF_BEGIN(p, KID_FFT_X_INV);
 #define L32(PV)                                                                                 \
   hipLaunchKernelGGL((k_fft_x_inv<float, PV>), grid, dim3(256), sh, p->stream, (const float2*)in, \
                      (float2*)out, p->f_twx, p->fx, d.nx, d.ny, d.nzm, kc, (float)d.alpha,      \
-                     (float)d.gamma, plain)
+                     (float)d.gamma, plain, p->mem.yv, p->mem.xp)
 #define L64(PV)                                                                          \
   hipLaunchKernelGGL((k_fft_x_inv<double, PV>), grid, dim3(256), sh, p->stream,          \
                      (const double2*)in, (double2*)out, p->d_twx, p->fx, d.nx, d.ny, d.nzm, kc, \
-                     d.alpha, d.gamma, plain)
+                     d.alpha, d.gamma, plain, p->mem.yv, p->mem.xp)
   if (fp32) {
     SP_FFT_DISPATCH(d.px, L32)
   } else {
@@ -1030,18 +1078,18 @@ hipError_t launch_z_product_lds(sp_plan* p, int mode, bool fp32) {
   int xc = (int)((48 * 1024 - d.pz * el) / (2 * 3 * lds_line(d.pz) * el));
   if (xc < 1) xc = 1;
   if (xc > d.px) xc = d.px;
-  dim3 grid(d.ny, (d.px + xc - 1) / xc);
+  dim3 grid(d.ny, (d.px + xc - 1) / xc, p->mem.nb);
   const size_t sh = (2 * (size_t)xc * 3 * lds_line(d.pz) + d.pz) * el;
   const double scale = 1.0 / ((double)d.px * d.pz);
   SP_PROF_BEGIN(p, KID_Z_PRODUCT);
 #define L32(PV)                                                                                  \
   hipLaunchKernelGGL((k_z_product<float, PV>), grid, dim3(256), sh, p->stream,                   \
                      (const float2*)p->xp, (float2*)p->np, p->base32, p->f_twz, p->fz, d.ny, d.px, \
-                     d.nzm, xc, mode, (float)scale)
+                     d.nzm, xc, mode, (float)scale, p->mem.xp, p->mem.np)
 #define L64(PV)                                                                                   \
   hipLaunchKernelGGL((k_z_product<double, PV>), grid, dim3(256), sh, p->stream,                   \
                      (const double2*)p->xp, (double2*)p->np, p->base, p->d_twz, p->fz, d.ny, d.px, \
-                     d.nzm, xc, mode, scale)
+                     d.nzm, xc, mode, scale, p->mem.xp, p->mem.np)
   if (fp32) {
     SP_FFT_DISPATCH(d.pz, L32)
   } else {
@@ -1057,15 +1105,17 @@ hipError_t launch_fft_x_fwd_lds(sp_plan* p, const void* in, void* out, int nfiel
   const Dims& d = p->d;
   const size_t el = fp32 ? sizeof(float2) : sizeof(double2);
   const int kc = chunk_for(d.px, d.nzm, el);
-  dim3 grid(d.ny, nfields, (d.nzm + kc - 1) / kc);
+  dim3 grid(d.ny * p->mem.nb, nfields, (d.nzm + kc - 1) / kc);
   const size_t sh = (2 * (size_t)kc * lds_line(d.px) + d.px) * el;
   SP_PROF_BEGIN(p, KID_FFT_X_FWD);
 #define L32(PV)                                                                                 \
   hipLaunchKernelGGL((k_fft_x_fwd<float, PV>), grid, dim3(256), sh, p->stream, (const float2*)in, \
-                     (float2*)out, p->f_twx, p->fx, d.nx, d.ny, d.nzm, kc)
+                     (float2*)out, p->f_twx, p->fx, d.nx, d.ny, d.nzm, kc, p->mem.np,         \
+                     p->mem.nv)
 #define L64(PV)                                                                       \
   hipLaunchKernelGGL((k_fft_x_fwd<double, PV>), grid, dim3(256), sh, p->stream,       \
-                     (const double2*)in, (double2*)out, p->d_twx, p->fx, d.nx, d.ny, d.nzm, kc)
+                     (const double2*)in, (double2*)out, p->d_twx, p->fx, d.nx, d.ny, d.nzm, kc, p->mem.np,       \
+                     p->mem.nv)
   if (fp32) {
     SP_FFT_DISPATCH(d.px, L32)
   } else {
@@ -1126,19 +1176,27 @@ hipError_t launch_analysis_solve(sp_plan* p, const double2* x, double xa, double
                                  int inhomogeneous, bool fp32) {
   const Dims& d = p->d;
   const size_t sh = solve_lds_bytes(p, fp32 ? 2 : 1);
+  const dim3 grid(d.nx * d.nzh, p->mem.nb);
+  const Members& mm = p->mem;
   SP_PROF_BEGIN(p, KID_SOLVE);
 #define SP_SOLVE_LAUNCH(EV, NTV)                                                                       \
   if (fp32)                                                                                       \
-    hipLaunchKernelGGL((k_stokes_solve<EV, 2>), dim3(d.nx * d.nzh), dim3(128), sh, p->stream,      \
+    hipLaunchKernelGGL((k_stokes_solve<EV, 2, false, 1, MB>), grid, dim3(128), sh, p->stream,      \
                        nullptr, out, p->d_mode, p->d_hwp, p->mode_stride, d.nx, d.ny, d.nzh,      \
                        d.alpha, d.gamma, d.re, d.inv_dt, d.wall_upper, d.wall_lower,             \
-                       inhomogeneous, p->nv, p->f_tinv_th, x, xa, 1.0, 0.0);                         \
+                       inhomogeneous, p->nv, p->f_tinv_th, x, xa, 1.0, 0.0, mm.in, mm.nv, mm.out); \
   else                                                                                            \
-    hipLaunchKernelGGL((k_stokes_solve<EV, 1, false, NTV>), dim3(d.nx * d.nzh), dim3(128), sh, p->stream,      \
+    hipLaunchKernelGGL((k_stokes_solve<EV, 1, false, NTV, MB>), grid, dim3(128), sh, p->stream,      \
                        nullptr, out, p->d_mode, p->d_hwp, p->mode_stride, d.nx, d.ny, d.nzh,      \
                        d.alpha, d.gamma, d.re, d.inv_dt, d.wall_upper, d.wall_lower,             \
-                       inhomogeneous, p->nv, p->d_tinv_th, x, xa, 1.0, 0.0)
-  SP_SOLVE_DISPATCH(SP_SOLVE_LAUNCH)
+                       inhomogeneous, p->nv, p->d_tinv_th, x, xa, 1.0, 0.0, mm.in, mm.nv, mm.out)
+  if (mm.nb > 1) {
+    constexpr bool MB = true;
+    SP_SOLVE_DISPATCH(SP_SOLVE_LAUNCH)
+  } else {
+    constexpr bool MB = false;
+    SP_SOLVE_DISPATCH(SP_SOLVE_LAUNCH)
+  }
 #undef SP_SOLVE_LAUNCH
   SP_PROF_END(p, KID_SOLVE);
   return hipGetLastError();
@@ -1150,19 +1208,27 @@ hipError_t launch_analysis_solve_res(sp_plan* p, const double2* x, double xa, do
                                      double2* out, bool fp32) {
   const Dims& d = p->d;
   const size_t sh = solve_lds_bytes(p, fp32 ? 2 : 1, true);
+  const dim3 grid(d.nx * d.nzh, p->mem.nb);
+  const Members& mm = p->mem;
   SP_PROF_BEGIN(p, KID_SOLVE);
 #define SP_SOLVE_LAUNCH(EV, NTV)                                                                       \
   if (fp32)                                                                                       \
-    hipLaunchKernelGGL((k_stokes_solve<EV, 2, true>), dim3(d.nx * d.nzh), dim3(128), sh,           \
+    hipLaunchKernelGGL((k_stokes_solve<EV, 2, true, 1, MB>), grid, dim3(128), sh,           \
                        p->stream, nullptr, out, p->d_mode, p->d_hwp, p->mode_stride, d.nx, d.ny,  \
                        d.nzh, d.alpha, d.gamma, d.re, d.inv_dt, d.wall_upper, d.wall_lower, 0,   \
-                       p->nv, p->f_tinv_th, x, xa, oa, ob);                                      \
+                       p->nv, p->f_tinv_th, x, xa, oa, ob, mm.in, mm.nv, mm.out);                \
   else                                                                                            \
-    hipLaunchKernelGGL((k_stokes_solve<EV, 1, true, NTV>), dim3(d.nx * d.nzh), dim3(128), sh,           \
+    hipLaunchKernelGGL((k_stokes_solve<EV, 1, true, NTV, MB>), grid, dim3(128), sh,           \
                        p->stream, nullptr, out, p->d_mode, p->d_hwp, p->mode_stride, d.nx, d.ny,  \
                        d.nzh, d.alpha, d.gamma, d.re, d.inv_dt, d.wall_upper, d.wall_lower, 0,   \
-                       p->nv, p->d_tinv_th, x, xa, oa, ob)
-  SP_SOLVE_DISPATCH(SP_SOLVE_LAUNCH)
+                       p->nv, p->d_tinv_th, x, xa, oa, ob, mm.in, mm.nv, mm.out)
+  if (mm.nb > 1) {
+    constexpr bool MB = true;
+    SP_SOLVE_DISPATCH(SP_SOLVE_LAUNCH)
+  } else {
+    constexpr bool MB = false;
+    SP_SOLVE_DISPATCH(SP_SOLVE_LAUNCH)
+  }
 #undef SP_SOLVE_LAUNCH
   SP_PROF_END(p, KID_SOLVE);
   return hipGetLastError();
@@ -1191,14 +1257,30 @@ hipError_t launch_norm_partial(sp_plan* p, const double2* a, double* partial, in
   return hipGetLastError();
 }
 
-hipError_t launch_pack(sp_plan* p, const double2* c, double* packed) {
+hipError_t launch_pack_rows(sp_plan* p, const double2* c, int members, double* packed,
+                            int64_t ld) {
   const Dims& d = p->d;
   const int total = 3 * d.ny * (d.nx - 1) * (d.nz - 1);
   int blocks = (total + 255) / 256;
   if (blocks > 4096) blocks = 4096;
   SP_PROF_BEGIN(p, KID_PACK);
-  hipLaunchKernelGGL(k_pack, dim3(blocks), dim3(256), 0, p->stream, c, packed, d.nx, d.ny, d.nzh);
+  hipLaunchKernelGGL(k_pack, dim3(blocks, members), dim3(256), 0, p->stream, c, packed, d.nx, d.ny,
+                     d.nzh, ld);
   SP_PROF_END(p, KID_PACK);
+  return hipGetLastError();
+}
+
+hipError_t launch_pack(sp_plan* p, const double2* c, double* packed) {
+  return launch_pack_rows(p, c, 1, packed, 0);
+}
+
+hipError_t launch_unit_fields(sp_plan* p, int64_t first, int members, double2* c) {
+  const Dims& d = p->d;
+  const int total = 3 * d.nx * d.nzh * d.ny;
+  SP_PROF_BEGIN(p, KID_UNPACK);
+  hipLaunchKernelGGL(k_unit_fields, dim3(std::min((total + 1023) / 1024, 4096), members), dim3(256),
+                     0, p->stream, first, c, d.nx, d.ny, d.nzh);
+  SP_PROF_END(p, KID_UNPACK);
   return hipGetLastError();
 }
 

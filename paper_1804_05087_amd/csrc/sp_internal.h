@@ -106,20 +106,24 @@ inline CMap compact_map(const Dims& d) {
   return m;
 }
 
-// Intermediates and stream of one member of a batched call (see api.cpp).
+// Members of a launch: nb independent evaluations in one grid, member m on the
+// buffers of member 0 plus m strides (complex elements; in and out are the
+// caller's canonical fields, yv .. nv the intermediates). The base state is shared.
+struct Members {
+  int nb = 1;
+  size_t in = 0, out = 0, yv = 0, xp = 0, np = 0, nv = 0;
+};
+
+// Intermediates and stream of one group of members of a batched call (see api.cpp).
 struct BatchSet {
   void* mem = nullptr;
   void* yv = nullptr;
   void* xp = nullptr;
   void* np = nullptr;
   void* nv = nullptr;
-  double2* g = nullptr;
-  double2* t1 = nullptr;
-  double2* t2 = nullptr;
   hipStream_t s = nullptr;
   hipEvent_t done = nullptr;
-  // dense Jacobian columns: packed unit vector, its field and the action
-  double* e = nullptr;
+  // dense Jacobian columns: the group's unit fields and their images
   double2* fin = nullptr;
   double2* fout = nullptr;
 };
@@ -198,8 +202,10 @@ struct sp_plan {
   double2* d_adv = nullptr;
   float2* f_adv = nullptr;  // FP32 copy of d_adv for the mixed-precision path
   double2* adv_x = nullptr;
-  // batched calls: one buffer set and stream per concurrent member
+  // batched calls: one buffer set and stream per concurrent group of members, and the
+  // members of the launch that is being issued
   std::vector<sp::BatchSet> bsets;
+  sp::Members mem;
   hipEvent_t bstart = nullptr;
   // dense Jacobian columns: a packed unit vector and its field in and out
   double* jc_e = nullptr;
@@ -270,6 +276,10 @@ hipError_t launch_axpby(sp_plan* p, const double2* x, double a, const double2* y
 hipError_t launch_norm_partial(sp_plan* p, const double2* a, double* partial, int* nblocks);
 hipError_t launch_pack(sp_plan* p, const double2* c, double* packed);
 hipError_t launch_unpack(sp_plan* p, const double* packed, double2* c);
+// member m of c = the canonical field of unit vector first + m of the packed basis
+hipError_t launch_unit_fields(sp_plan* p, int64_t first, int members, double2* c);
+// members canonical fields packed into rows of packed, ld apart
+hipError_t launch_pack_rows(sp_plan* p, const double2* c, int members, double* packed, int64_t ld);
 
 // GMRES BLAS (blas.hip)
 hipError_t launch_multidot(sp_plan* p, const double2* V, int nvec, const double2* w,

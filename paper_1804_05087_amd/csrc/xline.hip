@@ -21,31 +21,39 @@ namespace sp {
 // (ny, nfields, chunks)), reordered by xcd_order with the field fastest and
 // then the chunk: the blocks of one (y, chunk), which read the same spectral
 // lines for different output fields, share an L2.
+// MB: the grid's first dimension counts the planes of every member of a batch.
 struct XBlk {
-  int y, f, ch;
+  int member, y, f, ch;
 };
-__device__ inline XBlk xline_block() {
+template <bool MB>
+__device__ inline XBlk xline_block(int ny) {
   const int gy = gridDim.x, gf = gridDim.y, gc = gridDim.z;
   const int b = blockIdx.x + gy * (blockIdx.y + gf * blockIdx.z);
   const int l = xcd_order(b, gy * gf * gc);
-  return XBlk{l / (gf * gc), l % gf, (l / gf) % gc};
+  const int my = l / (gf * gc);
+  const int member = MB ? my / ny : 0;
+  return XBlk{member, my - member * ny, l % gf, (l / gf) % gc};
 }
 
 // plain == 0: output field f of (u, v, w, omega_x, omega_y, omega_z) from the
 // five y-valued fields (u, du/dy, v, w, dw/dy) with i k_x, i k_z; plain != 0:
 // output field f is input field f.
-template <typename R, int P1, int P2>
+template <typename R, int P1, int P2, bool MB>
 __global__ void __launch_bounds__(128)
     k_xinv_reg(const typename V2<R>::T* __restrict__ yv, typename V2<R>::T* __restrict__ xp,
                const typename V2<R>::T* __restrict__ tw, int nx, int ny, int nzm, int kc, R alpha,
-               R gamma, int plain) {
+               R gamma, int plain, size_t mi, size_t mo) {
   using C = typename V2<R>::T;
   constexpr int P = P1 * P2;
   constexpr int S1 = P1 + 1;
   extern __shared__ unsigned char smem_raw[];
   C* twl = reinterpret_cast<C*>(smem_raw);
   C* ex = twl + P;  // [kc][P2][S1]
-  const XBlk bk = xline_block();
+  const XBlk bk = xline_block<MB>(ny);
+  if constexpr (MB) {
+    yv += bk.member * mi;
+    xp += bk.member * mo;
+  }
   const int y = bk.y;
   const int f = bk.f;
   const int kz0 = bk.ch * kc;
@@ -114,17 +122,22 @@ __global__ void __launch_bounds__(128)
   }
 }
 
-template <typename R, int P1, int P2>
+template <typename R, int P1, int P2, bool MB>
 __global__ void __launch_bounds__(128)
     k_xfwd_reg(const typename V2<R>::T* __restrict__ np, typename V2<R>::T* __restrict__ nv,
-               const typename V2<R>::T* __restrict__ tw, int nx, int ny, int nzm, int kc) {
+               const typename V2<R>::T* __restrict__ tw, int nx, int ny, int nzm, int kc, size_t mi,
+               size_t mo) {
   using C = typename V2<R>::T;
   constexpr int P = P1 * P2;
   constexpr int S1 = P1 + 1;
   extern __shared__ unsigned char smem_raw[];
   C* twl = reinterpret_cast<C*>(smem_raw);
   C* ex = twl + P;  // [kc][P2][S1]
-  const XBlk bk = xline_block();
+  const XBlk bk = xline_block<MB>(ny);
+  if constexpr (MB) {
+    np += bk.member * mi;
+    nv += bk.member * mo;
+  }
   const int y = bk.y;
   const int c = bk.f;
   const int kz0 = bk.ch * kc;
@@ -184,10 +197,10 @@ hipError_t launch_fft_x_fwd_lds(sp_plan* p, const void* in, void* out, int nfiel
 // of LDS, split evenly; a chunk is widened to a whole number of 128-byte cache
 // lines (8 FP64 or 16 FP32 complex values) when that keeps the same even split,
 // so that chunks of the x-physical rows [x][kz] start on line boundaries
-static int xline_chunk(const Dims& d, int nfields, bool fp32, int P1, int P2) {
+static int xline_chunk(const Dims& d, int nb, int nfields, bool fp32, int P1, int P2) {
   const int lw = fp32 ? 16 : 8;
   const size_t el = fp32 ? sizeof(float2) : sizeof(double2);
-  const long per = (long)d.ny * nfields;
+  const long per = (long)d.ny * nfields * nb;
   const int nmax = d.nzm / 4 > 1 ? d.nzm / 4 : 1;
   auto lds = [&](int kc) { return ((size_t)d.px + (size_t)kc * P2 * (P1 + 1)) * el; };
   int nch = 1;
@@ -206,21 +219,27 @@ hipError_t launch_fft_x_inv_gen(sp_plan* p, const void* in, void* out, int nfiel
   const int P1 = reg_fft_split(d.px);
   if (P1 == 0) return launch_fft_x_inv_lds(p, in, out, nfields, plain, fp32);
   const int P2 = d.px / P1;
-  const int kc = xline_chunk(d, nfields, fp32, P1, P2);
-  const dim3 grid(d.ny, nfields, (d.nzm + kc - 1) / kc);
+  const int kc = xline_chunk(d, p->mem.nb, nfields, fp32, P1, P2);
+  const dim3 grid(d.ny * p->mem.nb, nfields, (d.nzm + kc - 1) / kc);
   const size_t el = fp32 ? sizeof(float2) : sizeof(double2);
   const size_t sh = ((size_t)d.px + (size_t)kc * P2 * (P1 + 1)) * el;
   SP_PROF_BEGIN(p, KID_FFT_X_INV);
 #define XI(A, B)                                                                                \
   if (fp32)                                                                                     \
-    hipLaunchKernelGGL((k_xinv_reg<float, A, B>), grid, dim3(128), sh, p->stream,               \
+    hipLaunchKernelGGL((k_xinv_reg<float, A, B, MB>), grid, dim3(128), sh, p->stream,               \
                        (const float2*)in, (float2*)out, p->f_twx, d.nx, d.ny, d.nzm, kc,        \
-                       (float)d.alpha, (float)d.gamma, plain);                                  \
+                       (float)d.alpha, (float)d.gamma, plain, p->mem.yv, p->mem.xp);            \
   else                                                                                          \
-    hipLaunchKernelGGL((k_xinv_reg<double, A, B>), grid, dim3(128), sh, p->stream,              \
+    hipLaunchKernelGGL((k_xinv_reg<double, A, B, MB>), grid, dim3(128), sh, p->stream,              \
                        (const double2*)in, (double2*)out, p->d_twx, d.nx, d.ny, d.nzm, kc,      \
-                       d.alpha, d.gamma, plain)
-  SP_REG_FFT_DISPATCH(d.px, XI)
+                       d.alpha, d.gamma, plain, p->mem.yv, p->mem.xp)
+  if (p->mem.nb > 1) {
+    constexpr bool MB = true;
+    SP_REG_FFT_DISPATCH(d.px, XI)
+  } else {
+    constexpr bool MB = false;
+    SP_REG_FFT_DISPATCH(d.px, XI)
+  }
 #undef XI
   SP_PROF_END(p, KID_FFT_X_INV);
   return hipGetLastError();
@@ -231,19 +250,27 @@ hipError_t launch_fft_x_fwd_gen(sp_plan* p, const void* in, void* out, int nfiel
   const int P1 = reg_fft_split(d.px);
   if (P1 == 0) return launch_fft_x_fwd_lds(p, in, out, nfields, fp32);
   const int P2 = d.px / P1;
-  const int kc = xline_chunk(d, nfields, fp32, P1, P2);
-  const dim3 grid(d.ny, nfields, (d.nzm + kc - 1) / kc);
+  const int kc = xline_chunk(d, p->mem.nb, nfields, fp32, P1, P2);
+  const dim3 grid(d.ny * p->mem.nb, nfields, (d.nzm + kc - 1) / kc);
   const size_t el = fp32 ? sizeof(float2) : sizeof(double2);
   const size_t sh = ((size_t)d.px + (size_t)kc * P2 * (P1 + 1)) * el;
   SP_PROF_BEGIN(p, KID_FFT_X_FWD);
 #define XF(A, B)                                                                                 \
   if (fp32)                                                                                      \
-    hipLaunchKernelGGL((k_xfwd_reg<float, A, B>), grid, dim3(128), sh, p->stream,                \
-                       (const float2*)in, (float2*)out, p->f_twx, d.nx, d.ny, d.nzm, kc);        \
+    hipLaunchKernelGGL((k_xfwd_reg<float, A, B, MB>), grid, dim3(128), sh, p->stream,                \
+                       (const float2*)in, (float2*)out, p->f_twx, d.nx, d.ny, d.nzm, kc,         \
+                       p->mem.np, p->mem.nv);                                                    \
   else                                                                                           \
-    hipLaunchKernelGGL((k_xfwd_reg<double, A, B>), grid, dim3(128), sh, p->stream,               \
-                       (const double2*)in, (double2*)out, p->d_twx, d.nx, d.ny, d.nzm, kc)
-  SP_REG_FFT_DISPATCH(d.px, XF)
+    hipLaunchKernelGGL((k_xfwd_reg<double, A, B, MB>), grid, dim3(128), sh, p->stream,               \
+                       (const double2*)in, (double2*)out, p->d_twx, d.nx, d.ny, d.nzm, kc,       \
+                       p->mem.np, p->mem.nv)
+  if (p->mem.nb > 1) {
+    constexpr bool MB = true;
+    SP_REG_FFT_DISPATCH(d.px, XF)
+  } else {
+    constexpr bool MB = false;
+    SP_REG_FFT_DISPATCH(d.px, XF)
+  }
 #undef XF
   SP_PROF_END(p, KID_FFT_X_FWD);
   return hipGetLastError();

@@ -107,20 +107,29 @@ __device__ inline Blk3 ycontract_block() {
 // to one MFMA column group and its imaginary part to a second, so the two
 // groups share every A fragment, a lane issues one load per two output values,
 // and each output row of the wave is one contiguous run of 16 complex values
-// (stored as pairs). Loads use clamped addresses and are masked after (a 0/1
+// (stored as pairs). Members of a batch: mu and mout apart (complex elements).
+// Loads use clamped addresses and are masked after (a 0/1
 // factor rather than a select keeps the compiler from sinking each load into
 // a branch of its own).
-template <typename R, int KS>
+// MB: a launch of several members (a template parameter: the member's division and
+// offsets took 0.3 us of a single member's 3 us launch at 16x17x16).
+template <typename R, int KS, bool MB>
 __global__ void __launch_bounds__(256)
     k_ysynth_mfma(const double2* __restrict__ u, SynthSpec<R> spec, R* __restrict__ out,
-                   int nx, int ny, int nzh, int nzm) {
+                   int nx, int ny, int nzh, int nzm, size_t mu, size_t mout) {
   using MF = Mfma<R>;
   using C = typename V2<R>::T;
   const int lane = threadIdx.x & 63;
   const int kq = lane >> 4;
   const int nq = nzm * nx;
   const Blk3 bk = ycontract_block();
-  const int g = bk.z;
+  int g = bk.z;
+  if constexpr (MB) {  // grid z = work-list entries x members
+    const int member = bk.z / spec.n;
+    g = bk.z - member * spec.n;
+    u += member * mu;
+    out += 2 * member * mout;
+  }
   const int t = bk.y;
   const int q0 = (bk.x * 4 + (threadIdx.x >> 6)) * 16;
   const int q = q0 + (lane & 15);
@@ -545,21 +554,33 @@ hipError_t launch_synth_tab(sp_plan* p, const double2* u, int which, void* out, 
   const Dims& d = p->d;
   // 64 modes per block, every 16-row tile, one work-list entry per z index
   const SynthSpec<double> sp64 = synth_spec<double>(p, which);
-  const dim3 grid((d.nzm * d.nx + 63) / 64, (d.ny + 15) / 16, sp64.n);
+  const dim3 grid((d.nzm * d.nx + 63) / 64, (d.ny + 15) / 16, sp64.n * p->mem.nb);
   SP_PROF_BEGIN(p, KID_SYNTH_Y);
   if (fp32) {
     const SynthSpec<float> sp = synth_spec<float>(p, which);
 #define L32(KS)                                                                                  \
-  hipLaunchKernelGGL((k_ysynth_mfma<float, KS>), grid, dim3(256), 0, p->stream, u, sp,          \
-                     (float*)out, d.nx, d.ny, d.nzh, d.nzm)
-    SP_KS_DISPATCH(d.ny, L32);
+  hipLaunchKernelGGL((k_ysynth_mfma<float, KS, MB>), grid, dim3(256), 0, p->stream, u, sp,          \
+                     (float*)out, d.nx, d.ny, d.nzh, d.nzm, p->mem.in, p->mem.yv)
+    if (p->mem.nb > 1) {
+      constexpr bool MB = true;
+      SP_KS_DISPATCH(d.ny, L32);
+    } else {
+      constexpr bool MB = false;
+      SP_KS_DISPATCH(d.ny, L32);
+    }
 #undef L32
   } else {
     const SynthSpec<double>& sp = sp64;
 #define L64(KS)                                                                                  \
-  hipLaunchKernelGGL((k_ysynth_mfma<double, KS>), grid, dim3(256), 0, p->stream, u, sp,         \
-                     (double*)out, d.nx, d.ny, d.nzh, d.nzm)
-    SP_KS_DISPATCH(d.ny, L64);
+  hipLaunchKernelGGL((k_ysynth_mfma<double, KS, MB>), grid, dim3(256), 0, p->stream, u, sp,         \
+                     (double*)out, d.nx, d.ny, d.nzh, d.nzm, p->mem.in, p->mem.yv)
+    if (p->mem.nb > 1) {
+      constexpr bool MB = true;
+      SP_KS_DISPATCH(d.ny, L64);
+    } else {
+      constexpr bool MB = false;
+      SP_KS_DISPATCH(d.ny, L64);
+    }
 #undef L64
   }
   SP_PROF_END(p, KID_SYNTH_Y);

@@ -100,16 +100,16 @@ struct ZLineMap {
 // (u, du/dy, v, w, dw/dy), from which the six curl-combined fields of the
 // x-lines are formed (the line map pairs fields (0, 1), (2, 3), (4, 5)); for
 // kXIn == 3 three fields taken as they are (pairs (0, 1), (2)). Requires
-// nx % 16 == 0 (so px % XL == 0), nzm == P / 3 and a 1-D grid of
-// ny * (px / XL) blocks; in and out do not alias.
+// nx % 16 == 0 (so px % XL == 0), nzm == P / 3 and a grid of
+// (ny * (px / XL), members) blocks; in and out do not alias.
 // Otherwise in = the x-physical fields [f][y][x][kz] (out may alias it) and
-// the grid is (ny, ceil(px / XL)).
+// the grid is (ny, ceil(px / XL), members). Members are mi and mo apart.
 template <typename R, int P1, int P2, int XL, class Op, bool XF = false>
 __global__ void __launch_bounds__(256)
     k_zline(const typename V2<R>::T* in, typename V2<R>::T* out,
             R* __restrict__ base, const typename V2<R>::T* __restrict__ tw, ZLineMap map, int ny,
             int px, int nzm, R scale, const typename V2<R>::T* __restrict__ twx = nullptr,
-            int nx = 0, R alpha = 0, R gamma = 0) {
+            int nx = 0, R alpha = 0, R gamma = 0, size_t mi = 0, size_t mo = 0) {
   using C = typename V2<R>::T;
   constexpr int P = P1 * P2;
   constexpr int NI = Op::NI;
@@ -132,6 +132,11 @@ __global__ void __launch_bounds__(256)
   __shared__ C ex2[E2F > E2X ? E2F : E2X];  // forward exchange (XF: first the x-physical lines)
   const int tid = threadIdx.x;
   int y, x0, xq, nxl;  // line xl of the block is x = x0 + xq * xl
+  {
+    const int member = XF ? blockIdx.y : blockIdx.z;
+    in += member * mi;
+    out += member * mo;
+  }
   if constexpr (XF) {
     const int nq = px / XL;
     const int l = xcd_order(blockIdx.x, gridDim.x);  // the blocks of one y-plane share an L2
@@ -452,7 +457,9 @@ static void zline_launch(sp_plan* p, const void* in, void* out, R* base, const v
                          const ZLineMap& map, double scale, const void* twx = nullptr) {
   const Dims& d = p->d;
   using C = typename V2<R>::T;
-  const dim3 grid = XF ? dim3(d.ny * (d.px / kZXL)) : dim3(d.ny, (d.px + kZXL - 1) / kZXL);
+  const int nb = p->mem.nb;
+  const dim3 grid =
+      XF ? dim3(d.ny * (d.px / kZXL), nb) : dim3(d.ny, (d.px + kZXL - 1) / kZXL, nb);
   const C* ci = (const C*)in;
   C* co = (C*)out;
   const C* ct = (const C*)tw;
@@ -460,7 +467,7 @@ static void zline_launch(sp_plan* p, const void* in, void* out, R* base, const v
 #define ZL(A, B)                                                                              \
   hipLaunchKernelGGL((k_zline<R, A, B, kZXL, Op, XF>), grid, dim3(256), 0, p->stream, ci, co,  \
                      base, ct, map, d.ny, d.px, d.nzm, (R)scale, cx, d.nx, (R)d.alpha,        \
-                     (R)d.gamma)
+                     (R)d.gamma, XF ? p->mem.yv : p->mem.xp, p->mem.np)
   SP_REG_FFT_DISPATCH(d.pz, ZL)
 #undef ZL
 }
