@@ -9,99 +9,264 @@
 // parities, so the per-mode system no longer splits into the parity chains of
 // the Stokes solve. The plan therefore builds, once per (Re, dt), each mode's
 // dense solution operator S~_k (the tau system's map from the 3 (N-1) used
-// right-hand-side coefficients to the 3 (N+1) velocity coefficients) on the
-// host, by LU with partial pivoting and iterative refinement with
-// extended-precision residuals, and the step applies it as a per-mode complex
-// matrix-vector product. The mean mode (k_x = 0, v = 0) is unchanged.
+// right-hand-side coefficients to the 3 (N+1) velocity coefficients) by LU with
+// partial pivoting and iterative refinement with extended-precision residuals,
+// and the step applies it as a per-mode matrix-vector product. The mean mode
+// (k_x = 0, v = 0) is unchanged: its operator is the Dirichlet Helmholtz solve.
+//
+// Two symmetries of the advected system quarter what is stored and read:
+//  - conjugation with z -> -z (w -> -w): S~(-k_x, k_z) = R conj(S~(k_x, k_z)) R,
+//    R = diag(1, 1, -1) over the components, so m_x and -m_x share an operator;
+//  - that, with the rotation (x, y) -> (-x, -y) (u, v -> -u, -v, a_n -> (-1)^n a_n),
+//    maps a mode to itself and conjugates it: with coefficients scaled by p_n = 1
+//    (n even), i (n odd) the operator is real (its entry is the complex one times
+//    p_col / p_row, whose imaginary part vanishes).
+// So a mode pair's operator is a real 3 (N-1) x 3 (N+1) matrix applied to four
+// real vectors, the parts of the two modes' scaled right-hand sides.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
 #include <complex>
 #include <thread>
+#include <type_traits>
 #include <vector>
 
 #include "device_common.h"
 #include "host_math.h"
+#include "solve_core.h"
 #include "sp_internal.h"
 
 namespace sp {
 
 namespace {
 
-// out_k = S~_k (g_k + i k_x Y x_k + (x_v, 0, 0)) on the used coefficients,
-// one block per mode; the mean mode and the Nyquist modes are skipped (their
-// output comes from the Stokes solve).
-__device__ inline double2 ld_op(const double2* S, size_t i) { return S[i]; }
-__device__ inline double2 ld_op(const float2* S, size_t i) {
-  const float2 f = S[i];
-  return make_double2(f.x, f.y);
-}
-
-// S~ in FP64, or its FP32 copy for the mixed-precision path (the sums stay FP64).
 template <typename TS>
+struct OpVec2;
+template <>
+struct OpVec2<double> {
+  typedef double T __attribute__((ext_vector_type(2)));
+};
+template <>
+struct OpVec2<float> {
+  typedef float T __attribute__((ext_vector_type(2)));
+};
+
+constexpr int kAdvRows = 128;  // row pairs a pass of the block covers
+constexpr int kAdvDepth = 8;   // columns in flight per thread
+
+// out_k = S~_k (g_k + xa x_k + i k_x Y x_k + (x_v, 0, 0)) on the used coefficients for
+// the modes (m_x, m_z) and (-m_x, m_z) of block m_x nzm + m_z (one mode at m_x = 0);
+// the blocks past the pairs write the Nyquist modes' zeros. out may alias x.
+// AN = 0: g (canonical) holds the right-hand side with xa x added already.
+// AN = 1: g = Tinv nv is formed here, in FP64, from the y-valued product fields
+// (folded halves and table as in the Stokes solve's fused analysis).
+// Smean: the (0,0) mode's operator, in FP64 for either TS.
+// wall: the (0,0) mode's response to the wall velocities, or NULL (homogeneous).
+// RES: out = oa (.) + ob x in the Hermitian form (the m_z = 0 plane's -m_x entries
+// are conjugates of the m_x ones, the (0,0) mode real); out must not alias x.
+//
+// Bound by the operators' bytes: 163 MB (FP64) at 48x65x48, read in about 40 us with
+// the analysis in front of it; as complex matrices, one per mode, they were 737 MB
+// and 130 us. A thread owns two rows (16-byte loads) and half of the columns, eight
+// loads ahead of their use; the four vectors' entries come from LDS (broadcast).
+template <typename TS, int AN, bool RES>
 __global__ void __launch_bounds__(256)
-    k_adv_apply(const double2* __restrict__ g, const double2* __restrict__ x,
-                const TS* __restrict__ S, double2* __restrict__ out, int nx, int ny,
-                int nzh, double alpha) {
+    k_adv_apply(const double2* __restrict__ g, const double2* x, double xa,
+                const TS* __restrict__ S, const double* __restrict__ Smean,
+                const double* __restrict__ wall, double2* out, int nx,
+                int ny, int nzh, double alpha, const double2* __restrict__ nv,
+                const double* __restrict__ th, double oa, double ob) {
   extern __shared__ unsigned char smem_raw[];
-  double2* gl = reinterpret_cast<double2*>(smem_raw);
-  const int mode = blockIdx.x;
-  const int i = mode / nzh;
-  const int j = mode - i * nzh;
-  if ((i == 0 && j == 0) || i == nx / 2 || j == nzh - 1) return;  // block-uniform
-  const int N = ny - 1;
-  const int C = 3 * (N - 1), R = 3 * ny;
+  const int nzm = nzh - 1, h = nx / 2, N = ny - 1;
+  const int nm = N - 1;  // used right-hand-side coefficients of a component
+  const int C = 3 * nm, R = 3 * ny, Rp = (R + 1) & ~1;
   const size_t cs = (size_t)nx * nzh * ny;
-  const size_t mo = (size_t)mode * ny;
-  const double kx = alpha * (double)(i < nx / 2 ? i : i - nx);
-  for (int t = threadIdx.x; t < C; t += blockDim.x) {
-    const int c = t / (N - 1);
-    const int n = t - c * (N - 1);
-    const double2* a = x + c * cs + mo;
-    double2 y;  // (y a)_n
-    if (n == 0) {
-      y = make_double2(0.5 * a[1].x, 0.5 * a[1].y);
-    } else {
-      const double w = (n == 1) ? 1.0 : 0.5;
-      y = make_double2(w * a[n - 1].x + 0.5 * a[n + 1].x, w * a[n - 1].y + 0.5 * a[n + 1].y);
+  const int tid = threadIdx.x;
+  if ((int)blockIdx.x >= h * nzm) {  // Nyquist: m_x = nx/2 (every m_z), then m_z = nz/2
+    const int q = blockIdx.x - h * nzm;
+    const int i = q < nzh ? h : q - nzh;
+    const int j = q < nzh ? q : nzh - 1;
+    const size_t mo = ((size_t)i * nzh + j) * ny;
+    for (int t = tid; t < R; t += 256) {
+      const int c = t / ny;
+      out[c * cs + mo + (t - c * ny)] = make_double2(0.0, 0.0);
     }
-    double2 v = g[c * cs + mo + n];
-    v.x -= kx * y.y;  // + i kx (y a)
-    v.y += kx * y.x;
-    if (c == 0) {
-      v.x += x[cs + mo + n].x;  // + v
-      v.y += x[cs + mo + n].y;
+    return;
+  }
+  const int i = blockIdx.x / nzm;
+  const int j = blockIdx.x - i * nzm;
+  const double kx = alpha * (double)i;
+  const bool mean = (i == 0 && j == 0);
+  const bool mirror = RES && j == 0 && i > 0;       // -m_x follows from m_x
+  const int nmode = (i == 0 || mirror) ? 1 : 2;
+  size_t mo[2];
+  mo[0] = ((size_t)i * nzh + j) * ny;
+  mo[1] = ((size_t)(i == 0 ? 0 : nx - i) * nzh + j) * ny;
+
+  double* vec = reinterpret_cast<double*>(smem_raw);  // [C][4]
+  // [6][jh] even and [6][jh] odd halves; afterwards [kAdvRows][8] partial sums
+  double2* fold = reinterpret_cast<double2*>(vec + 4 * C);
+  const int jh = N / 2 + 1;
+  if constexpr (AN == 1) {
+    const size_t fs = (size_t)ny * nzm * nx;
+    for (int t = tid; t < 3 * nmode * jh; t += 256) {
+      const int col = t / jh;  // 3 mode + component
+      const int jj = t - col * jh;
+      const int md = col / 3;
+      const double2* f = nv + (col - 3 * md) * fs + (size_t)j * nx + (md ? nx - i : i);
+      const double2 a = f[(size_t)jj * nzm * nx], b = f[(size_t)(N - jj) * nzm * nx];
+      const double same = (jj == N - jj) ? 0.0 : 1.0;  // middle point counted once
+      fold[col * jh + jj] = make_double2(a.x + same * b.x, a.y + same * b.y);
+      fold[(6 + col) * jh + jj] = make_double2((a.x - b.x) * same, (a.y - b.y) * same);
     }
-    gl[t] = v;
+    __syncthreads();
+  }
+  // the right-hand sides, scaled: entry (component c, coefficient n) of mode md
+  for (int t = tid; t < 2 * C; t += 256) {
+    const int md = t / C;
+    const int e = t - md * C;
+    const int c = e / nm;
+    const int n = e - c * nm;
+    double2 v = make_double2(0.0, 0.0);
+    if (md < nmode) {
+      const double2* a = x + c * cs + mo[md];
+      if constexpr (AN == 1) {
+        const double2* f = fold + ((n & 1 ? 6 : 0) + 3 * md + c) * jh;
+#pragma unroll 8
+        for (int jj = 0; jj < jh; ++jj) {
+          const double w = th[(size_t)jj * ny + n];
+          v.x += w * f[jj].x;
+          v.y += w * f[jj].y;
+        }
+        v.x += xa * a[n].x;
+        v.y += xa * a[n].y;
+      } else {
+        v = g[c * cs + mo[md] + n];
+      }
+      if (!mean) {
+        double2 y;  // (y a)_n
+        if (n == 0) {
+          y = make_double2(0.5 * a[1].x, 0.5 * a[1].y);
+        } else {
+          const double w = (n == 1) ? 1.0 : 0.5;
+          y = make_double2(w * a[n - 1].x + 0.5 * a[n + 1].x, w * a[n - 1].y + 0.5 * a[n + 1].y);
+        }
+        const double k = md ? -kx : kx;
+        v.x -= k * y.y;  // + i kx (y a)
+        v.y += k * y.x;
+        if (c == 0) {
+          v.x += x[cs + mo[md] + n].x;  // + v
+          v.y += x[cs + mo[md] + n].y;
+        }
+      }
+      // mode m_x: divided by p_n; mode -m_x: R conj(.) R, divided by conj(p_n)
+      if (n & 1) v = md ? make_double2(-v.y, v.x) : make_double2(v.y, -v.x);
+      if (md && c == 2) v = make_double2(-v.x, -v.y);
+    }
+    vec[4 * e + 2 * md] = v.x;
+    vec[4 * e + 2 * md + 1] = v.y;
   }
   __syncthreads();
-  const TS* Sm = S + (size_t)mode * C * R;
-  for (int r = threadIdx.x; r < R; r += blockDim.x) {
-    double ar = 0.0, ai = 0.0;
-#pragma unroll 8
-    for (int col = 0; col < C; ++col) {
-      const double2 s = ld_op(Sm, (size_t)col * R + r);
-      const double2 b = gl[col];
-      ar += s.x * b.x - s.y * b.y;
-      ai += s.x * b.y + s.y * b.x;
+  const TS* Sm = S + (size_t)blockIdx.x * C * Rp;
+  const int half = tid / kAdvRows;
+  const int rt = tid - half * kAdvRows;
+  const int c0 = half ? C / 2 : 0;
+  const int c1 = half ? C : C / 2;
+  double* part = reinterpret_cast<double*>(fold);
+  for (int r0 = 0; r0 < Rp / 2; r0 += kAdvRows) {  // uniform
+    const int rp = r0 + rt;
+    double acc[2][4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[0][q] = acc[1][q] = 0.0;
+    auto columns = [&](auto* M) {
+      using V2T = typename OpVec2<typename std::remove_cv<
+          typename std::remove_pointer<decltype(M)>::type>::type>::T;
+      const V2T* col = reinterpret_cast<const V2T*>(M) + rp;
+      const size_t ld = Rp / 2;
+      V2T s[kAdvDepth];
+#pragma unroll
+      for (int q = 0; q < kAdvDepth; ++q) s[q] = col[min(c0 + q, C - 1) * ld];
+      for (int cb = c0; cb < c1; cb += kAdvDepth) {
+#pragma unroll
+        for (int q = 0; q < kAdvDepth; ++q) {
+          const V2T w = s[q];
+          s[q] = col[min(cb + kAdvDepth + q, C - 1) * ld];  // past the end: re-reads
+          if (cb + q < c1) {                                // uniform
+            const double* b = vec + 4 * (cb + q);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              acc[0][k] += (double)w.x * b[k];
+              acc[1][k] += (double)w.y * b[k];
+            }
+          }
+        }
+      }
+    };
+    if (rp < Rp / 2) {
+      if (sizeof(TS) < sizeof(double) && mean)
+        columns(Smean);
+      else
+        columns(Sm);
     }
-    const int c = r / ny;
-    const int n = r - c * ny;
-    out[c * cs + mo + n] = make_double2(ar, ai);
+    __syncthreads();  // the folded columns (first pass) and the last pass' sums are read
+    if (half) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        part[k * kAdvRows + rt] = acc[0][k];
+        part[(4 + k) * kAdvRows + rt] = acc[1][k];
+      }
+    }
+    __syncthreads();
+    if (!half && rp < Rp / 2) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int r = 2 * rp + q;
+        if (r < R) {
+          double s[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) s[k] = acc[q][k] + part[(4 * q + k) * kAdvRows + rt];
+          const int c = r / ny;
+          const int n = r - c * ny;
+          for (int md = 0; md < nmode; ++md) {
+            const double re = md ? s[2] : s[0], im = md ? s[3] : s[1];
+            double2 o = make_double2(re, im);
+            if (n & 1) o = md ? make_double2(im, -re) : make_double2(-im, re);
+            if (md && c == 2) o = make_double2(-o.x, -o.y);
+            if (mean && c == 0 && wall != nullptr) o.x += wall[n];
+            if constexpr (RES) {
+              const double2 xv = x[c * cs + mo[md] + n];
+              o = make_double2(oa * o.x + ob * xv.x, oa * o.y + ob * xv.y);
+              if (mean) o.y = 0.0;
+              if (mirror) out[c * cs + mo[1] + n] = make_double2(o.x, -o.y);
+            }
+            out[c * cs + mo[md] + n] = o;
+          }
+        }
+      }
+    }
   }
 }
 
 }  // namespace
 
-size_t adv_bytes(const sp_plan* p) {
+// Operators of the mode pairs: m_x < nx/2, m_z < nz/2, column-major with an even
+// column length.
+static size_t adv_count(const sp_plan* p) {
   const Dims& d = p->d;
-  return (size_t)d.nx * d.nzh * 3 * (d.N - 1) * 3 * d.ny * sizeof(double2);
+  return (size_t)(d.nx / 2) * d.nzm * 3 * (d.N - 1) * ((3 * d.ny + 1) & ~1);
+}
+
+// Entry of the real operator from entry z of the complex one: z p_col / p_row, p = 1
+// (n even), i (n odd).
+__host__ __device__ static inline double adv_real_entry(double re, double im, int row_n, int col_n) {
+  if (((row_n ^ col_n) & 1) == 0) return re;
+  return (col_n & 1) ? -im : im;
 }
 
 namespace {
 
-// ---- The same operators built on the device, one workgroup per mode ----
+// ---- The operators built on the device, one workgroup per mode pair ----
 
 __device__ inline double d1_coef(int n, int m) {  // (D)_{nm}: d/dy on coefficients
   return (m > n && ((m + n) & 1)) ? (n == 0 ? 1.0 : 2.0) * m : 0.0;
@@ -255,11 +420,12 @@ __device__ double2 adv_residual_row(int N, double kx, double kz, double re, doub
 
 // Column c of the operator: solve A x = -e_c with the workgroup's factors,
 // refine twice with residuals accumulated in double-double, and write the
-// first R rows of x to column c of the mode's operator Sm (R x C, column-major).
+// first R rows of x, as real entries, to column c of the mode's operator Sm
+// (column length Rp).
 __device__ void adv_solve_refine(const double2* __restrict__ LU, const int* piv, int N, double kx,
                                  double kz, double re, double diag, int C, int R,
                                  double2* __restrict__ X, double2* __restrict__ Rw, int c,
-                                 double2* __restrict__ Sm) {
+                                 int Rp, double* __restrict__ Sm) {
   const int n4 = 4 * (N + 1);
   for (int r = 0; r < n4; ++r) X[(size_t)r * C + c] = make_double2(r == c ? -1.0 : 0.0, 0.0);
   adv_lu_solve_col(LU, piv, n4, C, X, c);
@@ -272,7 +438,11 @@ __device__ void adv_solve_refine(const double2* __restrict__ LU, const int* piv,
       X[(size_t)r * C + c] = make_double2(x.x + d.x, x.y + d.y);
     }
   }
-  for (int r = 0; r < R; ++r) Sm[(size_t)c * R + r] = X[(size_t)r * C + c];
+  const int cn = c % (N - 1);
+  for (int r = 0; r < R; ++r) {
+    const double2 z = X[(size_t)r * C + c];
+    Sm[(size_t)c * Rp + r] = adv_real_entry(z.x, z.y, r % (N + 1), cn);
+  }
 }
 
 constexpr int kAdvMaxN4 = 4 * 130;  // ny <= 129
@@ -288,14 +458,14 @@ constexpr int kAdvMaxN4 = 4 * 130;  // ny <= 129
 __global__ void __launch_bounds__(256)
     k_adv_build(const int* __restrict__ modes, int N, int nx, int nzh, double alpha, double gamma,
                 double re, double inv_dt, double2* __restrict__ ws, size_t ws_stride,
-                double2* __restrict__ S, int* __restrict__ status) {
+                double* __restrict__ S, int* __restrict__ status) {
   __shared__ int piv[kAdvMaxN4];
   __shared__ int rows[kAdvMaxN4];
   __shared__ double bval[256];
   __shared__ int bidx[256];
   __shared__ int nrows;
   const int tid = threadIdx.x;
-  const int n1 = N + 1, n4 = 4 * n1, C = 3 * (N - 1), R = 3 * n1;
+  const int n1 = N + 1, n4 = 4 * n1, C = 3 * (N - 1), R = 3 * n1, Rp = (R + 1) & ~1;
   const int mode = modes[blockIdx.x];
   const int i = mode / nzh, j = mode - i * nzh;
   const double kx = alpha * ((i < nx / 2) ? i : i - nx), kz = gamma * j;
@@ -377,49 +547,68 @@ __global__ void __launch_bounds__(256)
   }
   if (tid == 0) status[blockIdx.x] = 0;
   for (int c = tid; c < C; c += 256)
-    adv_solve_refine(LU, piv, N, kx, kz, re, diag, C, R, X, Rw, c, S + (size_t)mode * C * R);
+    adv_solve_refine(LU, piv, N, kx, kz, re, diag, C, R, X, Rw, c, Rp,
+                     S + (size_t)(i * (nzh - 1) + j) * C * Rp);
 }
 
 }  // namespace
 
-__global__ void k_narrow(const double2* __restrict__ a, float2* __restrict__ b, size_t n) {
+__global__ void k_narrow(const double* __restrict__ a, float* __restrict__ b, size_t n) {
   for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < n;
        t += (size_t)gridDim.x * blockDim.x)
-    b[t] = make_float2((float)a[t].x, (float)a[t].y);
+    b[t] = (float)a[t];
 }
 
-// The FP32 copy of the operators used by the mixed-precision path.
-static sp_status narrow_adv(sp_plan* p) {
-  const size_t n = adv_bytes(p) / sizeof(double2);
-  hipLaunchKernelGGL(k_narrow, dim3(4096), dim3(256), 0, p->stream, p->d_adv, p->f_adv, n);
-  sp_status s = hip_check(p, hipGetLastError(), "narrow operators");
+// The (0,0) mode's operator and wall response (host, the Helmholtz sweep of
+// solve_core.h per unit right-hand side), then the FP32 copy of all operators used
+// by the mixed-precision path.
+static sp_status finish_adv(sp_plan* p) {
+  const Dims& d = p->d;
+  const int N = d.N, n1 = d.ny, nm = N - 1, Rp = (3 * n1 + 1) & ~1;
+  std::vector<double> hw(3 * n1), blk(4 * n1 + 2), r(n1), q(n1), work(n1);
+  rhs_weights(N, hw.data());
+  sweep_factor(N, d.re * d.inv_dt, blk.data());
+  const SweepView sw(blk.data(), n1);
+  std::vector<double> S((size_t)3 * nm * Rp, 0.0), wall(n1, 0.0);
+  for (int n = 0; n < nm; ++n) {
+    std::fill(r.begin(), r.end(), 0.0);
+    std::fill(q.begin(), q.end(), 0.0);
+    r[n] = -d.re;
+    sweep_solve<double>(sw, hw.data(), N, n & 1, r.data(), 0.0, q.data(), work.data());
+    for (int c = 0; c < 3; c += 2)
+      for (int m = n & 1; m <= N; m += 2) S[(size_t)(c * nm + n) * Rp + c * n1 + m] = q[m];
+  }
+  std::fill(r.begin(), r.end(), 0.0);
+  for (int par = 0; par < 2; ++par) {
+    const double beta = 0.5 * (par ? d.wall_upper - d.wall_lower : d.wall_upper + d.wall_lower);
+    sweep_solve<double>(sw, hw.data(), N, par, r.data(), beta, wall.data(), work.data());
+  }
+  sp_status s = hip_check(p, hipMemcpy(p->d_adv, S.data(), S.size() * sizeof(double),
+                                       hipMemcpyHostToDevice),
+                          "upload the mean operator");
+  if (s) return s;
+  s = hip_check(p, hipMemcpy(p->d_advwall, wall.data(), n1 * sizeof(double), hipMemcpyHostToDevice),
+                "upload the wall response");
+  if (s) return s;
+  hipLaunchKernelGGL(k_narrow, dim3(4096), dim3(256), 0, p->stream, p->d_adv, p->f_adv,
+                     adv_count(p));
+  s = hip_check(p, hipGetLastError(), "narrow operators");
   if (s) return s;
   return hip_check(p, hipStreamSynchronize(p->stream), "sync");
 }
 
-// Allocates the operators (FP64 and the FP32 copy) and the scratch field of
-// the advected step if needed.
+// Allocates the operators (FP64 and the FP32 copy) and the wall response if needed.
 static sp_status ensure_adv_buffers(sp_plan* p) {
-  const Dims& d = p->d;
-  if (!p->d_adv) {
-    if (hipMalloc((void**)&p->d_adv, adv_bytes(p)) != hipSuccess) {
-      p->d_adv = nullptr;
-      return set_error(p, SP_ERR_NOMEM, "cannot allocate the advected solve operators");
-    }
-  }
-  if (!p->f_adv) {
-    if (hipMalloc((void**)&p->f_adv, adv_bytes(p) / 2) != hipSuccess) {
-      p->f_adv = nullptr;
-      return set_error(p, SP_ERR_NOMEM, "cannot allocate the advected solve operators");
-    }
-  }
-  if (!p->adv_x) {
-    if (hipMalloc((void**)&p->adv_x, (size_t)3 * d.nx * d.nzh * d.ny * sizeof(double2)) !=
-        hipSuccess) {
-      p->adv_x = nullptr;
-      return set_error(p, SP_ERR_NOMEM, "cannot allocate the advected scratch");
-    }
-  }
+  auto get = [&](auto** q, size_t bytes) {
+    if (*q || hipMalloc((void**)q, bytes) == hipSuccess) return true;
+    (void)hipGetLastError();
+    *q = nullptr;
+    return false;
+  };
+  if (!get(&p->d_adv, adv_count(p) * sizeof(double)) ||
+      !get(&p->f_adv, adv_count(p) * sizeof(float)) ||
+      !get(&p->d_advwall, p->d.ny * sizeof(double)))
+    return set_error(p, SP_ERR_NOMEM, "cannot allocate the advected solve operators");
   return SP_OK;
 }
 
@@ -432,9 +621,12 @@ static sp_status build_advection_device(sp_plan* p, const std::vector<int>& work
   if (n4 > kAdvMaxN4) return set_error(p, SP_ERR_INVALID, "ny too large for the device build");
   sp_status s = ensure_adv_buffers(p);
   if (s) return s;
-  s = hip_check(p, hipMemsetAsync(p->d_adv, 0, adv_bytes(p), p->stream), "clear operators");
+  s = hip_check(p, hipMemsetAsync(p->d_adv, 0, adv_count(p) * sizeof(double), p->stream), "clear operators");
   if (s) return s;
-  if (work.empty()) return hip_check(p, hipStreamSynchronize(p->stream), "sync");
+  if (work.empty()) {
+    s = hip_check(p, hipStreamSynchronize(p->stream), "sync");
+    return s ? s : finish_adv(p);
+  }
   const size_t per_mode = (size_t)n4 * n4 + (size_t)2 * n4 * C;  // double2 entries
   const size_t cap = ((size_t)4 << 30) / (per_mode * sizeof(double2));
   const int chunk = (int)std::max<size_t>(1, std::min<size_t>(cap, work.size()));
@@ -469,35 +661,39 @@ static sp_status build_advection_device(sp_plan* p, const std::vector<int>& work
   (void)hipStreamSynchronize(p->stream);  // no launch may still use the scratch
   (void)hipFree(scratch);
   if (s) return s;
-  return narrow_adv(p);
+  return finish_adv(p);
 }
 
 sp_status build_advection(sp_plan* p) {
   const Dims& d = p->d;
-  const int N = d.N, C = 3 * (N - 1), R = 3 * d.ny;
-  const int nmodes = d.nx * d.nzh;
-  std::vector<int> work;
-  for (int m = 0; m < nmodes; ++m) {
-    const int i = m / d.nzh, j = m - i * d.nzh;
-    if ((i == 0 && j == 0) || i == d.nx / 2 || j == d.nzh - 1) continue;
-    work.push_back(m);
-  }
+  const int N = d.N, C = 3 * (N - 1), R = 3 * d.ny, Rp = (R + 1) & ~1;
+  std::vector<int> work;  // one mode of each pair (+-m_x, m_z); the mean mode apart
+  for (int i = 0; i < d.nx / 2; ++i)
+    for (int j = 0; j < d.nzm; ++j)
+      if (i || j) work.push_back(i * d.nzh + j);
   if (!p->adv_host) return build_advection_device(p, work);
   using cplx = std::complex<double>;
-  std::vector<cplx> S((size_t)nmodes * C * R, cplx(0.0, 0.0));
+  std::vector<double> S(adv_count(p), 0.0);
   unsigned nt = std::thread::hardware_concurrency();
   nt = std::max(1u, std::min(nt == 0 ? 1u : nt, 16u));
   std::vector<int> ok(nt, 1);
   std::vector<std::thread> th;
   for (unsigned t = 0; t < nt; ++t)
     th.emplace_back([&, t]() {
+      std::vector<cplx> M((size_t)C * R);
       for (size_t w = t; w < work.size(); w += nt) {
         const int m = work[w];
         const int i = m / d.nzh, j = m - i * d.nzh;
-        const int mxv = (i < d.nx / 2) ? i : i - d.nx;
-        if (!adv_mode_operator(N, d.alpha * mxv, d.gamma * j, d.re, d.inv_dt,
-                               &S[(size_t)m * C * R]))
+        if (!adv_mode_operator(N, d.alpha * i, d.gamma * j, d.re, d.inv_dt, M.data())) {
           ok[t] = 0;
+          continue;
+        }
+        double* o = &S[(size_t)(i * d.nzm + j) * C * Rp];
+        for (int c = 0; c < C; ++c)
+          for (int r = 0; r < R; ++r) {
+            const cplx z = M[(size_t)c * R + r];
+            o[(size_t)c * Rp + r] = adv_real_entry(z.real(), z.imag(), r % d.ny, c % (N - 1));
+          }
       }
     });
   for (auto& x : th) x.join();
@@ -505,26 +701,52 @@ sp_status build_advection(sp_plan* p) {
     if (!v) return set_error(p, SP_ERR_INVALID, "singular advected tau system");
   sp_status s = ensure_adv_buffers(p);
   if (s) return s;
-  s = hip_check(p, hipMemcpy(p->d_adv, S.data(), adv_bytes(p), hipMemcpyHostToDevice),
+  s = hip_check(p, hipMemcpy(p->d_adv, S.data(), S.size() * sizeof(double), hipMemcpyHostToDevice),
                 "upload advected operators");
   if (s) return s;
-  return narrow_adv(p);
+  return finish_adv(p);
 }
 
-hipError_t launch_adv_apply(sp_plan* p, const double2* g, const double2* x, double2* out,
-                            bool fp32) {
+// g: NULL in FP64 (the analysis of p->nv is taken in the kernel).
+template <bool RES>
+static hipError_t adv_launch(sp_plan* p, const double2* g, const double2* x, double2* out,
+                             int inhomogeneous, double oa, double ob, bool fp32) {
   const Dims& d = p->d;
-  const size_t sh = (size_t)3 * (d.N - 1) * sizeof(double2);
+  const int C = 3 * (d.N - 1), jh = d.N / 2 + 1;
+  const size_t sh = (size_t)4 * C * sizeof(double) +
+                    std::max<size_t>((size_t)12 * jh * sizeof(double2),
+                                     (size_t)8 * kAdvRows * sizeof(double));
+  const dim3 grid((d.nx / 2) * d.nzm + d.nzh + d.nx);
+  const double* wall = inhomogeneous ? p->d_advwall : nullptr;
   SP_PROF_BEGIN(p, KID_ADV);
   if (fp32)
-    hipLaunchKernelGGL(k_adv_apply<float2>, dim3(d.nx * d.nzh), dim3(256), sh, p->stream, g, x,
-                       p->f_adv, out, d.nx, d.ny, d.nzh, d.alpha);
+    hipLaunchKernelGGL((k_adv_apply<float, 0, RES>), grid, dim3(256), sh, p->stream, g, x,
+                       d.inv_dt, p->f_adv, p->d_adv, wall, out, d.nx, d.ny, d.nzh, d.alpha,
+                       (const double2*)nullptr, (const double*)nullptr, oa, ob);
   else
-    hipLaunchKernelGGL(k_adv_apply<double2>, dim3(d.nx * d.nzh), dim3(256), sh, p->stream, g, x,
-                       p->d_adv, out, d.nx, d.ny, d.nzh, d.alpha);
+    hipLaunchKernelGGL((k_adv_apply<double, 1, RES>), grid, dim3(256), sh, p->stream, g, x,
+                       d.inv_dt, p->d_adv, p->d_adv, wall, out, d.nx, d.ny, d.nzh, d.alpha,
+                       (const double2*)p->nv, p->d_tinv_th, oa, ob);
   SP_PROF_END(p, KID_ADV);
   return hipGetLastError();
 }
 
-}  // namespace sp
+hipError_t launch_adv_solve(sp_plan* p, const double2* x, double2* out, int inhomogeneous,
+                            bool fp32) {
+  if (fp32) {
+    const hipError_t e = launch_analysis_rhs(p, x, p->d.inv_dt, p->g, true);
+    if (e != hipSuccess) return e;
+  }
+  return adv_launch<false>(p, p->g, x, out, inhomogeneous, 1.0, 0.0, fp32);
+}
 
+hipError_t launch_adv_solve_res(sp_plan* p, const double2* x, double oa, double ob, double2* out,
+                                bool fp32) {
+  if (fp32) {
+    const hipError_t e = launch_analysis_rhs(p, x, p->d.inv_dt, p->g, true);
+    if (e != hipSuccess) return e;
+  }
+  return adv_launch<true>(p, p->g, x, out, 0, oa, ob, fp32);
+}
+
+}  // namespace sp

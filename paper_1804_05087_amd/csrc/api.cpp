@@ -45,18 +45,10 @@ sp_status host_norm_of(sp_plan* p, const double2* a, double* out) {
 }
 
 sp_status befe_into(sp_plan* p, const double2* u, double2* out, bool fp32) {
-  if (p->advect && u == out) {  // the advected step reads u after the solve writes out
-    SP_TRY_HIP(hipMemcpyAsync(p->adv_x, u, canon_count(p) * sizeof(double2),
-                              hipMemcpyDeviceToDevice, p->stream),
-               "copy u");
-    u = p->adv_x;
-  }
   sp_status s = nonlinear_to_nv(p, u, 0, fp32);
   if (s) return s;
   if (p->advect) {
-    SP_TRY_HIP(launch_analysis_rhs(p, u, p->d.inv_dt, p->g, fp32), "analysis_rhs");
-    SP_TRY_HIP(launch_stokes_solve(p, p->g, out, 1), "stokes_solve (mean mode)");
-    SP_TRY_HIP(launch_adv_apply(p, p->g, u, out, fp32), "advected solve");
+    SP_TRY_HIP(launch_adv_solve(p, u, out, 1, fp32), "advected solve");
     return SP_OK;
   }
   SP_TRY_HIP(launch_analysis_solve(p, u, p->d.inv_dt, out, 1, fp32), "analysis+solve");
@@ -197,9 +189,7 @@ static sp_status jvp_phi_step(sp_plan* p, const double2* du, double2* out) {
   sp_status s = nonlinear_to_nv(p, du, 1, fp32);
   if (s) return s;
   if (p->advect) {
-    SP_TRY_HIP(launch_analysis_rhs(p, du, p->d.inv_dt, p->g, fp32), "analysis_rhs");
-    SP_TRY_HIP(launch_stokes_solve(p, p->g, out, 0), "stokes_solve (mean mode)");
-    SP_TRY_HIP(launch_adv_apply(p, p->g, du, out, fp32), "advected solve");
+    SP_TRY_HIP(launch_adv_solve(p, du, out, 0, fp32), "advected solve");
     return SP_OK;
   }
   SP_TRY_HIP(launch_analysis_solve(p, du, p->d.inv_dt, out, 0, fp32), "analysis+solve");
@@ -228,26 +218,26 @@ sp_status jvp_lin(sp_plan* p, int op, const double2* du, double2* out) {
     return SP_OK;
   }
   const int n = (op == SP_OP_PHI) ? 1 : p->nsteps;
-  if (n == 1 && op != SP_OP_PHI && !p->advect) {
+  if (n == 1 && op != SP_OP_PHI) {
     // (J_Phi du - du) / dt formed by the solve itself, in the Hermitian form
     sp_status s = base_at(p, 0);
     if (s) return s;
     const bool fp32 = (p->precision == SP_MIXED);
     s = nonlinear_to_nv(p, du, 1, fp32);
     if (s) return s;
-    SP_TRY_HIP(launch_analysis_solve_res(p, du, p->d.inv_dt, p->d.inv_dt, -p->d.inv_dt, out, fp32),
-               "analysis+solve (residual form)");
+    if (p->advect)
+      SP_TRY_HIP(launch_adv_solve_res(p, du, p->d.inv_dt, -p->d.inv_dt, out, fp32),
+                 "advected solve (residual form)");
+    else
+      SP_TRY_HIP(
+          launch_analysis_solve_res(p, du, p->d.inv_dt, p->d.inv_dt, -p->d.inv_dt, out, fp32),
+          "analysis+solve (residual form)");
     return SP_OK;
   }
   if (n == 1) {
     sp_status s = base_at(p, 0);
     if (s) return s;
-    double2* dst = (op == SP_OP_PHI) ? out : p->t2;
-    s = jvp_phi_step(p, du, dst);
-    if (s) return s;
-    if (op != SP_OP_PHI)
-      SP_TRY_HIP(launch_axpby_herm(p, p->t2, p->d.inv_dt, du, -p->d.inv_dt, out), "axpby");
-    return SP_OK;
+    return jvp_phi_step(p, du, out);
   }
   // chain rule along the trajectory: v_{k+1} = J_Phi(U_k) v_k
   const double2* v = du;

@@ -261,7 +261,7 @@ static void free_plan(sp_plan* p) {
   if (p->traj) (void)hipFree(p->traj);
   if (p->d_adv) (void)hipFree(p->d_adv);
   if (p->f_adv) (void)hipFree(p->f_adv);
-  if (p->adv_x) (void)hipFree(p->adv_x);
+  if (p->d_advwall) (void)hipFree(p->d_advwall);
   if (p->sb_u) (void)hipFree(p->sb_u);
   if (p->sb_x) (void)hipFree(p->sb_x);
   if (p->nv_prev) (void)hipFree(p->nv_prev);

@@ -194,14 +194,14 @@ struct sp_plan {
   double2* traj = nullptr;
   bool traj_valid = false;
   int base_step = 0;  // trajectory index of the cached base state
-  // laminar advection in the implicit operator: per-mode dense solution
-  // operators [mode][3(N-1)][3 ny] (device) and an input copy for aliasing
+  // laminar advection in the implicit operator: dense real solution operators of the
+  // mode pairs, [nx/2][nzm][3(N-1)][3 ny, even], and the (0,0) mode's wall response
   bool symmetric = false;  // Newton drivers confined to the shift-reflect subspace
   bool advect = false;
   bool adv_host = false;  // build the advected operators on the host (reference) or the device
-  double2* d_adv = nullptr;
-  float2* f_adv = nullptr;  // FP32 copy of d_adv for the mixed-precision path
-  double2* adv_x = nullptr;
+  double* d_adv = nullptr;
+  float* f_adv = nullptr;  // FP32 copy of d_adv for the mixed-precision path
+  double* d_advwall = nullptr;
   // batched calls: one buffer set and stream per concurrent group of members, and the
   // members of the launch that is being issued
   std::vector<sp::BatchSet> bsets;
@@ -338,9 +338,13 @@ sp_status residual_into(sp_plan* p, const double2* u, double2* r);
 sp_status linearize(sp_plan* p, const double2* u);
 sp_status base_at(sp_plan* p, int k);
 sp_status build_advection(sp_plan* p);
-// fp32: use the FP32 copy of the operators (the mixed-precision path)
-hipError_t launch_adv_apply(sp_plan* p, const double2* g, const double2* x, double2* out,
+// the advected solve from p->nv and x (out may alias x); fp32: analysis in FP32 and the
+// FP32 copy of the operators. _res: oa (.) + ob x in the Hermitian form, homogeneous
+// walls (out must not alias x)
+hipError_t launch_adv_solve(sp_plan* p, const double2* x, double2* out, int inhomogeneous,
                             bool fp32);
+hipError_t launch_adv_solve_res(sp_plan* p, const double2* x, double oa, double ob, double2* out,
+                                bool fp32);
 sp_status jvp_lin(sp_plan* p, int op, const double2* du, double2* out);
 sp_status vjp_lin(sp_plan* p, int op, const double2* w, double2* out);
 
