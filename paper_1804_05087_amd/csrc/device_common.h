@@ -340,8 +340,11 @@ __device__ inline void dft_reg(C (&v)[N], R sign, const C* tw) {
   }
 }
 
-// Lengths P = P1 * P2 with a register line kernel: returns P1 (0 if none).
-inline int reg_fft_split(int P) {
+// Lengths P = P1 * P2 with a register line kernel: returns P1 (0 if none). The FP32
+// path takes the lengths 27, 81, 162, 192, 216 and 288 through the LDS transform
+// (kernels.hip) instead: the order of its sums is part of what it returns, a relative
+// 1e-7, and stays.
+inline int reg_fft_split(int P, bool fp32) {
   switch (P) {
     case 12: return 4;
     case 18: return 6;
@@ -353,23 +356,44 @@ inline int reg_fft_split(int P) {
     case 96: return 12;
     case 108: return 12;
     case 144: return 16;
+    case 27: return fp32 ? 0 : 9;
+    case 81: return fp32 ? 0 : 9;
+    case 162: return fp32 ? 0 : 18;
+    case 192: return fp32 ? 0 : 16;
+    case 216: return fp32 ? 0 : 12;
+    case 288: return fp32 ? 0 : 16;
     default: return 0;
   }
 }
 
-// Expands LAUNCH(P1, P2) for the supported lengths (P must pass reg_fft_split).
+// Expands LAUNCH(P1, P2) for the supported lengths (P must pass reg_fft_split): those of
+// both precisions, and the ones of FP64 alone.
+#define SP_REG_FFT_CASES(LAUNCH) \
+  case 12: LAUNCH(4, 3); break;  \
+  case 18: LAUNCH(6, 3); break;  \
+  case 24: LAUNCH(8, 3); break;  \
+  case 36: LAUNCH(6, 6); break;  \
+  case 48: LAUNCH(8, 6); break;  \
+  case 54: LAUNCH(6, 9); break;  \
+  case 72: LAUNCH(8, 9); break;  \
+  case 96: LAUNCH(12, 8); break; \
+  case 108: LAUNCH(12, 9); break; \
+  case 144: LAUNCH(16, 9); break;
+#define SP_REG_FFT_CASES64(LAUNCH) \
+  case 27: LAUNCH(9, 3); break;    \
+  case 81: LAUNCH(9, 9); break;    \
+  case 162: LAUNCH(18, 9); break;  \
+  case 192: LAUNCH(16, 12); break; \
+  case 216: LAUNCH(12, 18); break; \
+  case 288: LAUNCH(16, 18); break;
 #define SP_REG_FFT_DISPATCH(P, LAUNCH) \
   switch (P) {                         \
-    case 12: LAUNCH(4, 3); break;      \
-    case 18: LAUNCH(6, 3); break;      \
-    case 24: LAUNCH(8, 3); break;      \
-    case 36: LAUNCH(6, 6); break;      \
-    case 48: LAUNCH(8, 6); break;      \
-    case 54: LAUNCH(6, 9); break;      \
-    case 72: LAUNCH(8, 9); break;      \
-    case 96: LAUNCH(12, 8); break;     \
-    case 108: LAUNCH(12, 9); break;    \
-    default: LAUNCH(16, 9); break;     \
+    SP_REG_FFT_CASES(LAUNCH)           \
+  }
+#define SP_REG_FFT_DISPATCH64(P, LAUNCH) \
+  switch (P) {                           \
+    SP_REG_FFT_CASES(LAUNCH)             \
+    SP_REG_FFT_CASES64(LAUNCH)           \
   }
 
 }  // namespace sp

@@ -12,6 +12,8 @@
 // contiguous across lanes.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "device_common.h"
 #include "sp_internal.h"
 
@@ -193,19 +195,24 @@ hipError_t launch_fft_x_inv_lds(sp_plan* p, const void* in, void* out, int nfiel
 hipError_t launch_fft_x_fwd_lds(sp_plan* p, const void* in, void* out, int nfields, bool fp32);
 
 // z-modes per block: the fewest chunks that give the grid at least 512 blocks
-// (and at least 4 modes per chunk) and keep the exchange buffer within 64 KiB
-// of LDS, split evenly; a chunk is widened to a whole number of 128-byte cache
+// (and at least 4 modes per chunk) and keep the exchange buffer within 32 KiB (16 in
+// FP32) of LDS, split evenly; a chunk is widened to a whole number of 128-byte cache
 // lines (8 FP64 or 16 FP32 complex values) when that keeps the same even split,
-// so that chunks of the x-physical rows [x][kz] start on line boundaries
+// so that chunks of the x-physical rows [x][kz] start on line boundaries. The LDS
+// bound leaves a CU five blocks of two waves; with 64 KiB it had two, and the long
+// lines waited: inverse, forward at 96x97x96 56.8, 18.4 us (64 KiB), 34.9, 11.8 (32),
+// 43.5, 12.1 (24), 61.6, 13.5 (16); 128x49x128 54.7, 17.2 / 33.6, 11.0 / 42.2, 12.3 / 49.5,
+// 12.0; FP32 inverse at 72x49x72 12.8 us (32 and 64 KiB), 8.9 (16).
 static int xline_chunk(const Dims& d, int nb, int nfields, bool fp32, int P1, int P2) {
   const int lw = fp32 ? 16 : 8;
   const size_t el = fp32 ? sizeof(float2) : sizeof(double2);
   const long per = (long)d.ny * nfields * nb;
   const int nmax = d.nzm / 4 > 1 ? d.nzm / 4 : 1;
   auto lds = [&](int kc) { return ((size_t)d.px + (size_t)kc * P2 * (P1 + 1)) * el; };
+  const size_t cap = fp32 ? 16384 : 32768;
   int nch = 1;
   while (nch < d.nzm &&
-         ((nch < nmax && per * nch < 512) || lds((d.nzm + nch - 1) / nch) > 65536))
+         ((nch < nmax && per * nch < 512) || lds((d.nzm + nch - 1) / nch) > cap))
     ++nch;
   int kc = (d.nzm + nch - 1) / nch;
   const int ka = (kc + lw - 1) / lw * lw;
@@ -216,7 +223,7 @@ static int xline_chunk(const Dims& d, int nb, int nfields, bool fp32, int P1, in
 hipError_t launch_fft_x_inv_gen(sp_plan* p, const void* in, void* out, int nfields, int plain,
                                 bool fp32) {
   const Dims& d = p->d;
-  const int P1 = reg_fft_split(d.px);
+  const int P1 = reg_fft_split(d.px, fp32);
   if (P1 == 0) return launch_fft_x_inv_lds(p, in, out, nfields, plain, fp32);
   const int P2 = d.px / P1;
   const int kc = xline_chunk(d, p->mem.nb, nfields, fp32, P1, P2);
@@ -224,30 +231,35 @@ hipError_t launch_fft_x_inv_gen(sp_plan* p, const void* in, void* out, int nfiel
   const size_t el = fp32 ? sizeof(float2) : sizeof(double2);
   const size_t sh = ((size_t)d.px + (size_t)kc * P2 * (P1 + 1)) * el;
   SP_PROF_BEGIN(p, KID_FFT_X_INV);
-#define XI(A, B)                                                                                \
-  if (fp32)                                                                                     \
-    hipLaunchKernelGGL((k_xinv_reg<float, A, B, MB>), grid, dim3(128), sh, p->stream,               \
-                       (const float2*)in, (float2*)out, p->f_twx, d.nx, d.ny, d.nzm, kc,        \
-                       (float)d.alpha, (float)d.gamma, plain, p->mem.yv, p->mem.xp);            \
-  else                                                                                          \
-    hipLaunchKernelGGL((k_xinv_reg<double, A, B, MB>), grid, dim3(128), sh, p->stream,              \
-                       (const double2*)in, (double2*)out, p->d_twx, d.nx, d.ny, d.nzm, kc,      \
-                       d.alpha, d.gamma, plain, p->mem.yv, p->mem.xp)
-  if (p->mem.nb > 1) {
-    constexpr bool MB = true;
-    SP_REG_FFT_DISPATCH(d.px, XI)
-  } else {
-    constexpr bool MB = false;
-    SP_REG_FFT_DISPATCH(d.px, XI)
-  }
-#undef XI
+#define XI32(A, B)                                                                              \
+  hipLaunchKernelGGL((k_xinv_reg<float, A, B, MB>), grid, dim3(128), sh, p->stream,             \
+                     (const float2*)in, (float2*)out, p->f_twx, d.nx, d.ny, d.nzm, kc,          \
+                     (float)d.alpha, (float)d.gamma, plain, p->mem.yv, p->mem.xp)
+#define XI64(A, B)                                                                              \
+  hipLaunchKernelGGL((k_xinv_reg<double, A, B, MB>), grid, dim3(128), sh, p->stream,            \
+                     (const double2*)in, (double2*)out, p->d_twx, d.nx, d.ny, d.nzm, kc,        \
+                     d.alpha, d.gamma, plain, p->mem.yv, p->mem.xp)
+  auto run = [&](auto mb) {
+    constexpr bool MB = decltype(mb)::value;
+    if (fp32) {
+      SP_REG_FFT_DISPATCH(d.px, XI32)
+    } else {
+      SP_REG_FFT_DISPATCH64(d.px, XI64)
+    }
+  };
+  if (p->mem.nb > 1)
+    run(std::true_type{});
+  else
+    run(std::false_type{});
+#undef XI32
+#undef XI64
   SP_PROF_END(p, KID_FFT_X_INV);
   return hipGetLastError();
 }
 
 hipError_t launch_fft_x_fwd_gen(sp_plan* p, const void* in, void* out, int nfields, bool fp32) {
   const Dims& d = p->d;
-  const int P1 = reg_fft_split(d.px);
+  const int P1 = reg_fft_split(d.px, fp32);
   if (P1 == 0) return launch_fft_x_fwd_lds(p, in, out, nfields, fp32);
   const int P2 = d.px / P1;
   const int kc = xline_chunk(d, p->mem.nb, nfields, fp32, P1, P2);
@@ -255,23 +267,28 @@ hipError_t launch_fft_x_fwd_gen(sp_plan* p, const void* in, void* out, int nfiel
   const size_t el = fp32 ? sizeof(float2) : sizeof(double2);
   const size_t sh = ((size_t)d.px + (size_t)kc * P2 * (P1 + 1)) * el;
   SP_PROF_BEGIN(p, KID_FFT_X_FWD);
-#define XF(A, B)                                                                                 \
-  if (fp32)                                                                                      \
-    hipLaunchKernelGGL((k_xfwd_reg<float, A, B, MB>), grid, dim3(128), sh, p->stream,                \
-                       (const float2*)in, (float2*)out, p->f_twx, d.nx, d.ny, d.nzm, kc,         \
-                       p->mem.np, p->mem.nv);                                                    \
-  else                                                                                           \
-    hipLaunchKernelGGL((k_xfwd_reg<double, A, B, MB>), grid, dim3(128), sh, p->stream,               \
-                       (const double2*)in, (double2*)out, p->d_twx, d.nx, d.ny, d.nzm, kc,       \
-                       p->mem.np, p->mem.nv)
-  if (p->mem.nb > 1) {
-    constexpr bool MB = true;
-    SP_REG_FFT_DISPATCH(d.px, XF)
-  } else {
-    constexpr bool MB = false;
-    SP_REG_FFT_DISPATCH(d.px, XF)
-  }
-#undef XF
+#define XF32(A, B)                                                                              \
+  hipLaunchKernelGGL((k_xfwd_reg<float, A, B, MB>), grid, dim3(128), sh, p->stream,             \
+                     (const float2*)in, (float2*)out, p->f_twx, d.nx, d.ny, d.nzm, kc,          \
+                     p->mem.np, p->mem.nv)
+#define XF64(A, B)                                                                              \
+  hipLaunchKernelGGL((k_xfwd_reg<double, A, B, MB>), grid, dim3(128), sh, p->stream,            \
+                     (const double2*)in, (double2*)out, p->d_twx, d.nx, d.ny, d.nzm, kc,        \
+                     p->mem.np, p->mem.nv)
+  auto run = [&](auto mb) {
+    constexpr bool MB = decltype(mb)::value;
+    if (fp32) {
+      SP_REG_FFT_DISPATCH(d.px, XF32)
+    } else {
+      SP_REG_FFT_DISPATCH64(d.px, XF64)
+    }
+  };
+  if (p->mem.nb > 1)
+    run(std::true_type{});
+  else
+    run(std::false_type{});
+#undef XF32
+#undef XF64
   SP_PROF_END(p, KID_FFT_X_FWD);
   return hipGetLastError();
 }

@@ -452,23 +452,35 @@ hipError_t launch_adj_z_lds(sp_plan* p, bool fp32);
 
 constexpr int kZXL = 8;
 
+// x-lines per block of length P: eight, but four past 72 points, where eight take 59 KB
+// of LDS or more and leave a CU one or two blocks. Measured (separate inverse x
+// transform): 60.4 us against 40.2 with four at P = 144 (96x97x96), 18.0 against 17.5 at
+// 108, 9.5 against 8.6 at 81, 8.3 against 8.6 at 54.
+constexpr int zline_lines(int P) { return P > 72 ? 4 : 8; }
+
 template <typename R, class Op, bool XF = false>
 static void zline_launch(sp_plan* p, const void* in, void* out, R* base, const void* tw,
                          const ZLineMap& map, double scale, const void* twx = nullptr) {
   const Dims& d = p->d;
   using C = typename V2<R>::T;
   const int nb = p->mem.nb;
-  const dim3 grid =
-      XF ? dim3(d.ny * (d.px / kZXL), nb) : dim3(d.ny, (d.px + kZXL - 1) / kZXL, nb);
   const C* ci = (const C*)in;
   C* co = (C*)out;
   const C* ct = (const C*)tw;
   const C* cx = (const C*)twx;
-#define ZL(A, B)                                                                              \
-  hipLaunchKernelGGL((k_zline<R, A, B, kZXL, Op, XF>), grid, dim3(256), 0, p->stream, ci, co,  \
-                     base, ct, map, d.ny, d.px, d.nzm, (R)scale, cx, d.nx, (R)d.alpha,        \
-                     (R)d.gamma, XF ? p->mem.yv : p->mem.xp, p->mem.np)
-  SP_REG_FFT_DISPATCH(d.pz, ZL)
+#define ZL(A, B)                                                                               \
+  {                                                                                            \
+    constexpr int XL = XF ? kZXL : zline_lines(A * B);                                         \
+    const dim3 grid = XF ? dim3(d.ny * (d.px / XL), nb) : dim3(d.ny, (d.px + XL - 1) / XL, nb); \
+    hipLaunchKernelGGL((k_zline<R, A, B, XL, Op, XF>), grid, dim3(256), 0, p->stream, ci, co,   \
+                       base, ct, map, d.ny, d.px, d.nzm, (R)scale, cx, d.nx, (R)d.alpha,       \
+                       (R)d.gamma, XF ? p->mem.yv : p->mem.xp, p->mem.np);                     \
+  }
+  if constexpr (sizeof(R) == sizeof(float) || XF) {
+    SP_REG_FFT_DISPATCH(d.pz, ZL)
+  } else {
+    SP_REG_FFT_DISPATCH64(d.pz, ZL)
+  }
 #undef ZL
 }
 
@@ -483,7 +495,7 @@ static void zline_launch(sp_plan* p, const void* in, void* out, R* base, const v
 // slower at 96x97x96 (3.8 and 1.9 MiB), so its bound is 1 MiB.
 bool zline_fuses_x_inverse(const sp_plan* p, bool fp32, int nfields) {
   const Dims& d = p->d;
-  if (reg_fft_split(d.pz) == 0 || d.nx % (2 * kZXL) != 0 || 3 * d.nzm != d.pz) return false;
+  if (reg_fft_split(d.pz, true) == 0 || d.nx % (2 * kZXL) != 0 || 3 * d.nzm != d.pz) return false;
   const size_t plane =
       (size_t)nfields * d.nzm * d.nx * (fp32 ? sizeof(float2) : sizeof(double2));
   const size_t bound = (nfields == 5 ? (size_t)4 : (size_t)1) << 20;
@@ -492,7 +504,7 @@ bool zline_fuses_x_inverse(const sp_plan* p, bool fp32, int nfields) {
 
 hipError_t launch_z_product(sp_plan* p, int mode, bool fp32) {
   const Dims& d = p->d;
-  if (reg_fft_split(d.pz) == 0) return launch_z_product_lds(p, mode, fp32);
+  if (reg_fft_split(d.pz, fp32) == 0) return launch_z_product_lds(p, mode, fp32);
   const double scale = 1.0 / ((double)d.px * d.pz);
   const ZLineMap map{{0, 2, 4}, {1, 3, 5}, {0, 2, -1}, {1, -1, -1}};
   SP_PROF_BEGIN(p, KID_Z_PRODUCT);
@@ -532,7 +544,7 @@ hipError_t launch_z_product(sp_plan* p, int mode, bool fp32) {
 
 hipError_t launch_adj_z(sp_plan* p, bool fp32) {
   const Dims& d = p->d;
-  if (reg_fft_split(d.pz) == 0) return launch_adj_z_lds(p, fp32);
+  if (reg_fft_split(d.pz, fp32) == 0) return launch_adj_z_lds(p, fp32);
   const double scale = 1.0 / ((double)d.px * d.pz);
   const ZLineMap map{{0, 2, -1}, {1, -1, -1}, {0, 2, 4}, {1, 3, 5}};
   SP_PROF_BEGIN(p, KID_ADJ_Z);
