@@ -10,7 +10,7 @@ namespace sp {
 
 // partial[(v * NR + r) * nb + chunk] = a chunk's share of <V_v, w_r>,
 // v = 0..nvec-1, r < NR (one or two right-hand vectors). Block (chunk, g) owns
-// 256 * ept consecutive entries of V's layout and the vectors 32 g .. 32 g + 31:
+// 256 * ept consecutive entries of V's layout and the vectors vecs g .. vecs (g + 1) - 1:
 // each thread keeps its weighted entries of the w_r in registers (weights
 // computed once), streams the vectors a group at a time, and the sums are
 // reduced with wave shuffles and LDS.
@@ -77,12 +77,11 @@ template <>
 struct DotShape<float2> {
   static constexpr int group = 4, ept = 8;
 };
-constexpr int kDotVecs = 32;
 
 template <int NR, typename T, class Layout>
 __global__ void __launch_bounds__(256)
     k_multidot(const T* __restrict__ V, int nvec, const double2* __restrict__ w0,
-               const double2* __restrict__ w1, double* __restrict__ partial, Layout L) {
+               const double2* __restrict__ w1, double* __restrict__ partial, int vecs, Layout L) {
   constexpr int kDotGroup = DotShape<T>::group;
   constexpr int kDotEPT = DotShape<T>::ept;
   __shared__ double red[4][kDotGroup * NR];
@@ -106,8 +105,8 @@ __global__ void __launch_bounds__(256)
       wi[r][i] = wt * x.y;
     }
   }
-  const int vbeg = blockIdx.y * kDotVecs;
-  const int vend = min(nvec, vbeg + kDotVecs);
+  const int vbeg = blockIdx.y * vecs;
+  const int vend = min(nvec, vbeg + vecs);
   for (int v0 = vbeg; v0 < vend; v0 += kDotGroup) {
     double acc[kDotGroup * NR];
 #pragma unroll
@@ -143,20 +142,18 @@ __global__ void __launch_bounds__(256)
   }
 }
 
-// out[v] = sum_b partial[v * nb + b] (+ add[v] if add != NULL); one block per v.
+// out[v] = sum_b partial[v * nb + b]; one wave per v.
 __global__ void __launch_bounds__(256)
-    k_reduce_rows(const double* __restrict__ partial, int nb, double* __restrict__ out) {
-  __shared__ double red[256];
-  const int v = blockIdx.x;
+    k_reduce_rows(const double* __restrict__ partial, int nv, int nb, double* __restrict__ out) {
+  const int v = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (v >= nv) return;  // uniform per wave
   double acc = 0.0;
-  for (int b = threadIdx.x; b < nb; b += blockDim.x) acc += partial[(size_t)v * nb + b];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[v] = red[0];
+#pragma unroll 4
+  for (int b = lane; b < nb; b += 64) acc += partial[(size_t)v * nb + b];
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) acc += __shfl_xor(acc, d);
+  if (lane == 0) out[v] = acc;
 }
 
 // w = beta * w + alpha * sum_v h[v] V_v (h in device memory) on the compact
@@ -215,73 +212,65 @@ __global__ void __launch_bounds__(256)
 // H is kept row-major on the device (H[l ld + i] = H(l, i)), so that a row of
 // H a is one contiguous run.
 
-// Ha[l] = (H a)_l for l < j: the completed columns i <= j - 2 (rows l <= i + 1)
-// plus column j - 1 = hprev + a. One wave per row.
+// (H a)_l, l < j, sums the completed columns i <= j - 2 (rows l <= i + 1) and column
+// j - 1 = hprev + a. One wave per row l <= j forms it and everything that row needs
+// (gamma and the scalars are formed by every block from the dots, 2 j values): row l of
+// column j - 1 of H, of the provisional column, and a_l and c_l for the update pass
+// (ac[l] = a_l, ac[cst + l] = c_l); row j adds 1 / gamma. rec is the host's record in
+// pinned memory, written directly: rec[0] = gamma, rec[1] = <u_j, u_j> - sum a_i^2 (its
+// finiteness is the host's check), rec[2] = j, rec[4 + l] = H(l, j - 1) for l <= j
+// (j > 0). One launch instead of two and a copy, each 4 to 5 us plus its gap.
 __global__ void __launch_bounds__(256)
-    k_arnoldi_ha(int j, int ld, const double* __restrict__ dots, const double* __restrict__ H,
-                 const double* __restrict__ hprev, double* __restrict__ Ha) {
-  const int l = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (l >= j) return;  // uniform per wave
-  double s = 0.0;
-  for (int i = (l > 0 ? l - 1 : 0) + lane; i <= j - 2; i += 64)
-    s += H[(size_t)l * ld + i] * dots[2 * i];
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d);
-  if (lane == 0) Ha[l] = s + (hprev[l] + dots[2 * l]) * dots[2 * (j - 1)];
-}
-
-// One block: gamma, column j - 1 of H (device H and the host record), the new
-// provisional column, a and c for the update pass (ac[i] = a_i, ac[cst + i] =
-// c_i) and 1 / gamma. rec[0] = gamma, rec[1] = <u_j, u_j> - sum a_i^2 (its
-// finiteness is the host's check), rec[2] = j, rec[4 + i] = H(i, j - 1) for
-// i <= j (j > 0).
-constexpr int kCoefThreads = 1024;
-__global__ void __launch_bounds__(kCoefThreads)
     k_arnoldi_coef(int j, int ld, int cst, const double* __restrict__ dots, double* __restrict__ H,
-                   double* __restrict__ hprev, const double* __restrict__ Ha,
-                   double* __restrict__ ac, double* __restrict__ inv_gamma,
-                   double* __restrict__ rec) {
-  __shared__ double red[2][kCoefThreads / 64];
+                   double* __restrict__ hprev, double* __restrict__ ac,
+                   double* __restrict__ inv_gamma, double* __restrict__ rec) {
+  __shared__ double red[2][4];
   const int t = threadIdx.x;
+  const int lane = t & 63;
   double saa = 0.0, sab = 0.0;
-  for (int i = t; i < j; i += kCoefThreads) {
+  for (int i = t; i < j; i += 256) {
     const double ai = dots[2 * i], bi = dots[2 * i + 1];
     saa += ai * ai;
     sab += ai * bi;
   }
+  const int l = blockIdx.x * 4 + (t >> 6);
+  double s = 0.0;
+  if (l < j)  // uniform per wave
+    for (int i = (l > 0 ? l - 1 : 0) + lane; i <= j - 2; i += 64)
+      s += H[(size_t)l * ld + i] * dots[2 * i];
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) {
     saa += __shfl_xor(saa, d);
     sab += __shfl_xor(sab, d);
+    s += __shfl_xor(s, d);
   }
-  if ((t & 63) == 0) {
+  if (lane == 0) {
     red[0][t >> 6] = saa;
     red[1][t >> 6] = sab;
   }
   __syncthreads();
+  if (lane != 0 || l > j) return;
   double aa = 0.0, ab = 0.0;
 #pragma unroll
-  for (int q = 0; q < kCoefThreads / 64; ++q) {
+  for (int q = 0; q < 4; ++q) {
     aa += red[0][q];
     ab += red[1][q];
   }
   const double g2 = dots[2 * j] - aa;
   const double gamma = g2 > 0.0 ? sqrt(g2) : 0.0;
   const double ig = 1.0 / gamma;  // infinite at a breakdown, where the host stops
-  const double haj = j > 0 ? gamma * dots[2 * (j - 1)] : 0.0;  // (H a)_j
-  for (int i = t; i < j; i += kCoefThreads) {
-    const double ai = dots[2 * i], bi = dots[2 * i + 1];
-    const double hc = hprev[i] + ai;
-    H[(size_t)i * ld + (j - 1)] = hc;
-    rec[4 + i] = hc;
-    const double hai = Ha[i];
-    const double hp = (bi - hai) * ig;
-    hprev[i] = hp;
-    ac[i] = ai;
-    ac[cst + i] = hai * ig + hp;
-  }
-  if (t == 0) {
+  if (l < j) {
+    const double al = dots[2 * l], bl = dots[2 * l + 1];
+    const double hc = hprev[l] + al;
+    const double hal = s + hc * dots[2 * (j - 1)];
+    const double hp = (bl - hal) * ig;
+    H[(size_t)l * ld + (j - 1)] = hc;
+    rec[4 + l] = hc;
+    hprev[l] = hp;
+    ac[l] = al;
+    ac[cst + l] = hal * ig + hp;
+  } else {
+    const double haj = j > 0 ? gamma * dots[2 * (j - 1)] : 0.0;  // (H a)_j
     if (j > 0) {
       H[(size_t)j * ld + (j - 1)] = gamma;
       rec[4 + j] = gamma;
@@ -427,16 +416,26 @@ static hipError_t multidot_impl(sp_plan* p, const T* V, int n, Layout L, int nve
   static_assert(ept >= DotShape<double2>::ept, "the partial buffer holds multidot_blocks chunks");
   const int nb = (n + 256 * ept - 1) / (256 * ept);
   SP_PROF_BEGIN(p, KID_MULTIDOT);
-  const dim3 grid(nb, (nvec + kDotVecs - 1) / kDotVecs);
+  // vectors per block: up to 32 (the right-hand sides' entries are loaded once for
+  // them), fewer while that leaves the chip short of blocks, evened out over the
+  // groups. One group of 211 chunks (30 vectors at 48x65x48) streamed at 3.6 TB/s; more
+  // than about 400 blocks gain nothing and load the right-hand sides more often.
+  constexpr int group = DotShape<T>::group;
+  int most = 32;
+  while (most > group && (long)nb * ((nvec + most - 1) / most) < 400) most /= 2;
+  const int ng = (nvec + most - 1) / most;
+  const int vecs = ((nvec + ng - 1) / ng + group - 1) / group * group;
+  const dim3 grid(nb, (nvec + vecs - 1) / vecs);
   if (nr == 1)
     hipLaunchKernelGGL((k_multidot<1, T, Layout>), grid, dim3(256), 0, p->stream, V, nvec, w0, w0,
-                       partial, L);
+                       partial, vecs, L);
   else
     hipLaunchKernelGGL((k_multidot<2, T, Layout>), grid, dim3(256), 0, p->stream, V, nvec, w0, w1,
-                       partial, L);
+                       partial, vecs, L);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_reduce_rows, dim3(nr * nvec), dim3(256), 0, p->stream, partial, nb, out);
+  hipLaunchKernelGGL(k_reduce_rows, dim3((nr * nvec + 3) / 4), dim3(256), 0, p->stream, partial,
+                     nr * nvec, nb, out);
   SP_PROF_END(p, KID_MULTIDOT);
   return hipGetLastError();
 }
@@ -505,17 +504,10 @@ hipError_t launch_dcgs2_update(sp_plan* p, float2* V, int j, const double* a, co
 }
 
 hipError_t launch_arnoldi_coef(sp_plan* p, int j, int ld, int cst, const double* dots, double* H,
-                              double* hprev, double* Ha, double* ac, double* inv_gamma,
-                              double* rec) {
+                              double* hprev, double* ac, double* inv_gamma, double* rec) {
   SP_PROF_BEGIN(p, KID_MULTIAXPY);
-  if (j > 0) {
-    hipLaunchKernelGGL(k_arnoldi_ha, dim3((j + 3) / 4), dim3(256), 0, p->stream, j, ld, dots, H,
-                       hprev, Ha);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(k_arnoldi_coef, dim3(1), dim3(kCoefThreads), 0, p->stream, j, ld, cst, dots,
-                     H, hprev, Ha, ac, inv_gamma, rec);
+  hipLaunchKernelGGL(k_arnoldi_coef, dim3((j + 4) / 4), dim3(256), 0, p->stream, j, ld, cst, dots,
+                     H, hprev, ac, inv_gamma, rec);
   SP_PROF_END(p, KID_MULTIAXPY);
   return hipGetLastError();
 }

@@ -67,9 +67,7 @@ size_t ws_bytes_for(const sp_plan* p, int K) {
   b += 3 * align256((size_t)2 * (K + 2) * sizeof(double));  // dots, a|c, y
   b += align256((size_t)(K + 1) * K * sizeof(double));      // Hessenberg matrix
   b += align256((size_t)(K + 2) * sizeof(double));          // provisional column
-  b += align256((size_t)(K + 2) * sizeof(double));          // H a
   b += align256(sizeof(double));                            // 1 / gamma
-  b += align256((size_t)2 * (K + 5) * sizeof(double));      // two host records
   return b;
 }
 
@@ -84,9 +82,7 @@ struct Workspace {
   double* y;
   double* H;      // (K+1) x K, row-major
   double* hprev;  // K+2
-  double* ha;     // K+2
   double* ig;     // 1
-  double* rec;    // 2 (K+5)
 };
 
 Workspace carve(sp_plan* p, int K) {
@@ -112,11 +108,7 @@ Workspace carve(sp_plan* p, int K) {
   c += align256((size_t)(K + 1) * K * sizeof(double));
   W.hprev = (double*)c;
   c += align256((size_t)(K + 2) * sizeof(double));
-  W.ha = (double*)c;
-  c += align256((size_t)(K + 2) * sizeof(double));
   W.ig = (double*)c;
-  c += align256(sizeof(double));
-  W.rec = (double*)c;
   return W;
 }
 
@@ -194,8 +186,8 @@ sp_status ensure_workspace(sp_plan* p, int K) {
 //
 // Each Arnoldi iteration runs on the device from end to end: the Jacobian
 // action, the fused projections, the coefficients (launch_arnoldi_coef) and the
-// update pass. The host only reads each iteration's Hessenberg column back
-// (a small record copied to pinned memory) and applies the Givens rotations
+// update pass. The host only reads each iteration's Hessenberg column
+// (a small record the device writes to pinned memory) and applies the Givens rotations
 // and the stop test one iteration behind the device, so the device never waits
 // for it. When the test stops the solve at iteration j, iteration j + 1 has
 // already been queued; its work writes only basis slots j + 1 and above and
@@ -207,7 +199,10 @@ struct Gmres {
   int K;
   Workspace W;
   size_t canon, nc, nk;
-  double* hrec = nullptr;  // pinned: two records of K+5 doubles
+  // two records of K+5 doubles in pinned memory, which the device writes; read here
+  // once the iteration's event has passed
+  double* hrec = nullptr;
+  double* hrec_dev = nullptr;
   hipEvent_t ev[2] = {nullptr, nullptr};
   std::vector<double> H, R, cs, sn, g;
   int kd = 0;
@@ -233,6 +228,7 @@ struct Gmres {
   }
   sp_status init() {
     SP_TRY_HIP(hipHostMalloc((void**)&hrec, 2 * (K + 5) * sizeof(double)), "hipHostMalloc");
+    SP_TRY_HIP(hipHostGetDevicePointer((void**)&hrec_dev, hrec, 0), "hipHostGetDevicePointer");
     for (hipEvent_t& e : ev)
       SP_TRY_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming), "hipEventCreate");
     return SP_OK;
@@ -243,7 +239,7 @@ struct Gmres {
   // Queues iteration j: u_j -> w = J u_j (none at j = K, which only completes
   // column K-1), the dots of q_0..q_{j-1} and u_j with u_j and w, the
   // coefficients, the update pass (q_j into slot j, u_{j+1} into slot j+1 and
-  // W.u), and the copy of the record to pinned slot j % 2.
+  // W.u); the record goes to pinned slot j % 2.
   sp_status enqueue(int j, const double2* U, const double2* r, double unorm, int* actions) {
     double2* uj = W.u;
     double* d_dots = W.h1;  // 2 (K + 2) doubles
@@ -272,8 +268,8 @@ struct Gmres {
     else
       SP_TRY_HIP(launch_krylov_multidot2(p, W.V, j + 1, uj, last ? uj : W.w, W.partial, d_dots),
                  "multidot");
-    double* rec = W.rec + (size_t)(j & 1) * (K + 5);
-    SP_TRY_HIP(launch_arnoldi_coef(p, j, K, K + 2, d_dots, W.H, W.hprev, W.ha, d_ac, W.ig, rec),
+    double* rec = hrec_dev + (size_t)(j & 1) * (K + 5);
+    SP_TRY_HIP(launch_arnoldi_coef(p, j, K, K + 2, d_dots, W.H, W.hprev, d_ac, W.ig, rec),
                "arnoldi coefficients");
     if (!last) {
       if (f32)
@@ -285,9 +281,6 @@ struct Gmres {
                                        W.V + (size_t)(j + 1) * nk, W.u),
                    "dcgs2 update");
     }
-    SP_TRY_HIP(hipMemcpyAsync(hrec + (size_t)(j & 1) * (K + 5), rec, (5 + j) * sizeof(double),
-                              hipMemcpyDeviceToHost, p->stream),
-               "copy record");
     SP_TRY_HIP(hipEventRecord(ev[j & 1], p->stream), "record event");
     return SP_OK;
   }

@@ -310,11 +310,10 @@ hipError_t launch_dcgs2_update(sp_plan* p, float2* V, int j, const double* a, co
 // The coefficients of Arnoldi iteration j on the device (blas.hip): from the
 // dots of launch_krylov_multidot2, the row-major Hessenberg matrix H (row
 // stride ld) and the provisional column hprev (both updated), writes a and c
-// (ac[i], ac[cst + i]), 1/gamma and the host record rec (gamma, the squared
-// norm, j, -, then column j-1 of H); Ha is scratch (j doubles).
+// (ac[i], ac[cst + i]), 1/gamma and the host record rec in pinned memory (gamma, the
+// squared norm, j, -, then column j-1 of H).
 hipError_t launch_arnoldi_coef(sp_plan* p, int j, int ld, int cst, const double* dots, double* H,
-                              double* hprev, double* Ha, double* ac, double* inv_gamma,
-                              double* rec);
+                              double* hprev, double* ac, double* inv_gamma, double* rec);
 // dst (compact) = src (canonical, Hermitian form); the FP32 form also writes the
 // rounded values back into src
 hipError_t launch_compact(sp_plan* p, double2* src, double2* dst);
