@@ -117,7 +117,7 @@ sp_status sp_plan_set_steps(sp_plan* plan, int32_t nsteps);
  * trajectory (du_{-1} = du_0 = du). SBDF2 needs FP64 actions and the Stokes
  * implicit operator (SP_ERR_INVALID from the residual, linearisation and
  * Jacobian calls otherwise); sp_befe_step and SP_OP_PHI actions stay one BEFE
- * step. The first switch to 1 allocates two canonical fields and one y-valued
+ * step. The first switch to 1 allocates a canonical field and one y-valued
  * nonlinear term (SP_ERR_NOMEM if that fails). Invalidates the base state.
  * Synchronises. */
 sp_status sp_plan_set_scheme(sp_plan* plan, int32_t scheme);

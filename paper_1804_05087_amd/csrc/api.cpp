@@ -75,18 +75,11 @@ static size_t nv_count(const sp_plan* p) {
 // walls). N_{k-1} is carried in y-values in nv_prev; first: N_{k-1} = N_k.
 static sp_status sbdf2_step(sp_plan* p, const double2* uk, const double2* ukm1, double2* out,
                             int mode, bool first) {
-  sp_status s = nonlinear_to_nv(p, uk, mode, false);
-  if (s) return s;
-  const size_t m = nv_count(p);
-  double2* nv = reinterpret_cast<double2*>(p->nv);
-  if (first)
-    SP_TRY_HIP(hipMemcpyAsync(p->nv_prev, nv, m * sizeof(double2), hipMemcpyDeviceToDevice,
-                              p->stream),
-               "copy N");
-  SP_TRY_HIP(launch_sbdf2_combine(p, nv, p->nv_prev, m), "combine N");
-  SP_TRY_HIP(launch_axpby(p, uk, 4.0 / 3.0, ukm1, -1.0 / 3.0, p->sb_x, canon_count(p)),
-             "combine u");
-  SP_TRY_HIP(launch_analysis_solve(p, p->sb_x, p->d.inv_dt, out, mode == 0 ? 1 : 0, false),
+  SP_TRY_HIP(launch_synth_y(p, uk, false), "synth_y");
+  if (!zline_fuses_x_inverse(p, false, 5)) SP_TRY_HIP(launch_fft_x_inv(p, false), "fft_x_inv");
+  SP_TRY_HIP(launch_z_product(p, mode, false), "z_product");
+  SP_TRY_HIP(launch_fft_x_fwd_sbdf2(p, p->nv_prev, first), "fft_x_fwd");
+  SP_TRY_HIP(launch_analysis_solve_sbdf2(p, uk, ukm1, p->d.inv_dt, out, mode == 0 ? 1 : 0),
              "analysis+solve");
   return SP_OK;
 }
@@ -347,13 +340,11 @@ extern "C" sp_status sp_plan_set_scheme(sp_plan* p, int32_t scheme) {
   if (scheme == 1 && !p->sb_u) {
     const size_t cb = canon_count(p) * sizeof(double2);
     if (hipMalloc((void**)&p->sb_u, cb) != hipSuccess ||
-        hipMalloc((void**)&p->sb_x, cb) != hipSuccess ||
         hipMalloc((void**)&p->nv_prev, nv_count(p) * sizeof(double2)) != hipSuccess) {
       (void)hipGetLastError();
       if (p->sb_u) (void)hipFree(p->sb_u);
-      if (p->sb_x) (void)hipFree(p->sb_x);
       if (p->nv_prev) (void)hipFree(p->nv_prev);
-      p->sb_u = p->sb_x = p->nv_prev = nullptr;
+      p->sb_u = p->nv_prev = nullptr;
       return set_error(p, SP_ERR_NOMEM, "cannot allocate the SBDF2 scratch");
     }
   }

@@ -323,11 +323,12 @@ __device__ inline double half_wave_sum(double a, double b) {
 // th[j][n] = Tinv[n][j], so the lanes' loads are contiguous.
 // Two-wave blocks are held to at most 168 VGPRs (3 waves per SIMD), so that
 // every mode's block is resident at once at 48x65x48 (2 x 1128 waves).
+// SB (with AN = 1): (4 x - x2) / 3 takes the place of x (an SBDF2 step).
 // RES (with AN != 0): the residual form of a Jacobian action, out = oa S(g) +
 // ob x, written in the Hermitian form: the block of an m_z = 0 mode at m_x > 0
 // also writes the conjugate at -m_x (whose block has nothing to do), and the
 // (0,0) mode is real. x's entries n <= N are kept in LDS for it.
-template <int E, int AN, bool RES = false, int NT = 1, bool MB = false>
+template <int E, int AN, bool RES = false, int NT = 1, bool MB = false, bool SB = false>
 __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
     __attribute__((amdgpu_waves_per_eu(AN != 0 ? 3 : 1)))
     k_stokes_solve(const double2* __restrict__ g, double2* __restrict__ out,
@@ -336,7 +337,8 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
                    double inv_dt, double wu, double wl, int inhomogeneous,
                    const void* __restrict__ nv_raw, const void* __restrict__ tinv_raw,
                    const double2* __restrict__ x, double xa, double oa = 1.0, double ob = 0.0,
-                   size_t mx = 0, size_t mnv = 0, size_t mout = 0) {
+                   size_t mx = 0, size_t mnv = 0, size_t mout = 0,
+                   const double2* __restrict__ x2 = nullptr) {
   static_assert(!RES || AN != 0, "the residual form reads x through the fused analysis");
   if constexpr (MB) {  // members of a batch (grid y)
     x += blockIdx.y * mx;
@@ -439,6 +441,13 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
       ga[t] = x[mo + nc];
       gb[t] = x[cs + mo + nc];
       gc[t] = x[2 * cs + mo + nc];
+      if constexpr (SB) {
+        const double c = 4.0 / 3.0, c2 = -1.0 / 3.0;
+        const double2 a = x2[mo + nc], b = x2[cs + mo + nc], e = x2[2 * cs + mo + nc];
+        ga[t] = make_double2(c * ga[t].x + c2 * a.x, c * ga[t].y + c2 * a.y);
+        gb[t] = make_double2(c * gb[t].x + c2 * b.x, c * gb[t].y + c2 * b.y);
+        gc[t] = make_double2(c * gc[t].x + c2 * e.x, c * gc[t].y + c2 * e.y);
+      }
     }
   }
   // fold loads of the y-valued columns (AN != 0) into registers, f_jj and f_{N-jj}
@@ -1197,6 +1206,25 @@ hipError_t launch_analysis_solve(sp_plan* p, const double2* x, double xa, double
     constexpr bool MB = false;
     SP_SOLVE_DISPATCH(SP_SOLVE_LAUNCH)
   }
+#undef SP_SOLVE_LAUNCH
+  SP_PROF_END(p, KID_SOLVE);
+  return hipGetLastError();
+}
+
+// out = S(Tinv nv + xa (4 x - x2) / 3), FP64: the combination of the last two states
+// took a launch of its own, 2.6 us of a 27 us step at 32x33x32.
+hipError_t launch_analysis_solve_sbdf2(sp_plan* p, const double2* x, const double2* x2, double xa,
+                                       double2* out, int inhomogeneous) {
+  const Dims& d = p->d;
+  const size_t sh = solve_lds_bytes(p, 1);
+  SP_PROF_BEGIN(p, KID_SOLVE);
+#define SP_SOLVE_LAUNCH(EV, NTV)                                                                 \
+  hipLaunchKernelGGL((k_stokes_solve<EV, 1, false, NTV, false, true>), dim3(d.nx * d.nzh),        \
+                     dim3(128), sh, p->stream, nullptr, out, p->d_mode, p->d_hwp, p->mode_stride, \
+                     d.nx, d.ny, d.nzh, d.alpha, d.gamma, d.re, d.inv_dt, d.wall_upper,           \
+                     d.wall_lower, inhomogeneous, p->nv, p->d_tinv_th, x, xa, 1.0, 0.0,           \
+                     (size_t)0, (size_t)0, (size_t)0, x2)
+  SP_SOLVE_DISPATCH(SP_SOLVE_LAUNCH)
 #undef SP_SOLVE_LAUNCH
   SP_PROF_END(p, KID_SOLVE);
   return hipGetLastError();

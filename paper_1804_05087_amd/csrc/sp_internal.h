@@ -189,7 +189,6 @@ struct sp_plan {
   // implicit step tau = dt (time step 3 dt / 2); scratch of the SBDF2 steps
   int scheme = 0;
   double2* sb_u = nullptr;
-  double2* sb_x = nullptr;
   double2* nv_prev = nullptr;
   double2* traj = nullptr;
   bool traj_valid = false;
@@ -246,6 +245,8 @@ hipError_t launch_z_product(sp_plan* p, int mode, bool fp32);
 // launch_adj_z, from p->nv), so that no separate inverse x launch precedes them
 bool zline_fuses_x_inverse(const sp_plan* p, bool fp32, int nfields);
 hipError_t launch_fft_x_fwd(sp_plan* p, bool fp32);
+// the same with the SBDF2 extrapolation of the nonlinear term (FP64)
+hipError_t launch_fft_x_fwd_sbdf2(sp_plan* p, double2* prev, bool first);
 // which = 0: forward synthesis table into p->yv; 1: Tinv^T on 3 components into out
 hipError_t launch_synth_tab(sp_plan* p, const double2* u, int which, void* out, bool fp32);
 hipError_t launch_fft_x_inv_gen(sp_plan* p, const void* in, void* out, int nfields, int plain,
@@ -263,6 +264,9 @@ hipError_t launch_stokes_solve(sp_plan* p, const double2* g, double2* out, int i
 // y-valued product fields p->nv -> Chebyshev analysis + xa * x -> solve, one kernel
 hipError_t launch_analysis_solve(sp_plan* p, const double2* x, double xa, double2* out,
                                  int inhomogeneous, bool fp32);
+// the same, FP64, with xa (4 x - x2) / 3 for xa x (an SBDF2 step)
+hipError_t launch_analysis_solve_sbdf2(sp_plan* p, const double2* x, const double2* x2, double xa,
+                                       double2* out, int inhomogeneous);
 // the same with homogeneous walls in the residual form out = oa S + ob x, written
 // in the Hermitian form (m_z = 0 plane exactly Hermitian, Nyquist entries zero)
 hipError_t launch_analysis_solve_res(sp_plan* p, const double2* x, double xa, double oa, double ob,
@@ -323,8 +327,8 @@ hipError_t launch_hermitian(sp_plan* p, double2* a);
 hipError_t launch_symmetrize(sp_plan* p, double2* a);
 // a[i] = v for i in [0, n) (fill) or for the single index i (set)
 hipError_t launch_fill(sp_plan* p, double* a, size_t n, double v);
-// nv <- 2 nv - prev, prev <- nv (the SBDF2 extrapolation of the nonlinear term)
-hipError_t launch_sbdf2_combine(sp_plan* p, double2* nv, double2* prev, size_t n);
+// nv <- 2 nv - prev (first: nv), prev <- nv (the SBDF2 extrapolation of the nonlinear term)
+hipError_t launch_sbdf2_combine(sp_plan* p, double2* nv, double2* prev, size_t n, bool first);
 hipError_t launch_set_entry(sp_plan* p, double* a, size_t i, double v);
 // element chunks of launch_multidot (1024 consecutive complex entries each); the
 // partial buffer passed to it holds nvec * multidot_blocks(p) doubles
