@@ -377,7 +377,10 @@ sp_status sp_profile_read(sp_plan* plan, int32_t n_max, char* names, int64_t* co
  * out as for sp_befe_step, out must not alias u. Uses the plan's precision.
  * Where the z-line kernel takes the inverse x transforms itself (it reads the
  * y-valued fields; chosen per grid and precision), SP_STAGE_XINV launches
- * nothing and writes 0 to *avg_us, and SP_STAGE_ZLINE covers both stages. */
+ * nothing and writes 0 to *avg_us, and SP_STAGE_ZLINE covers both stages. Where
+ * the evaluation takes the forward x transform inside the z-line and solve kernels
+ * (chosen per grid, FP64), the stages are timed in the form that has it as a kernel
+ * of its own. */
 typedef enum {
   SP_STAGE_SYNTH = 0, /* y-synthesis of u, du/dy, v, w, dw/dy (Sec. 3.2) */
   SP_STAGE_XINV = 1,  /* curl factors, 3/2 padding, inverse x FFT */

@@ -21,12 +21,14 @@ static size_t canon_count(const sp_plan* p) {
 
 namespace sp {
 
-// a2-a5: N(u) (or its linearisation, mode 1) into p->nv (y-valued spectral).
-static sp_status nonlinear_to_nv(sp_plan* p, const double2* u, int mode, bool fp32) {
+// a2-a5: N(u) (or its linearisation, mode 1) into p->nv (y-valued spectral), or for a
+// solve that takes the forward x transforms itself as far as that reads it (p->np).
+static sp_status nonlinear_to_nv(sp_plan* p, const double2* u, int mode, bool fp32, bool solve) {
+  const bool xfo = solve && solve_takes_x_forward(p, fp32);
   SP_TRY_HIP(launch_synth_y(p, u, fp32), "synth_y");
   if (!zline_fuses_x_inverse(p, fp32, 5)) SP_TRY_HIP(launch_fft_x_inv(p, fp32), "fft_x_inv");
-  SP_TRY_HIP(launch_z_product(p, mode, fp32), "z_product");
-  SP_TRY_HIP(launch_fft_x_fwd(p, fp32), "fft_x_fwd");
+  SP_TRY_HIP(launch_z_product(p, mode, fp32, xfo), "z_product");
+  if (!xfo) SP_TRY_HIP(launch_fft_x_fwd(p, fp32), "fft_x_fwd");
   return SP_OK;
 }
 
@@ -45,7 +47,7 @@ sp_status host_norm_of(sp_plan* p, const double2* a, double* out) {
 }
 
 sp_status befe_into(sp_plan* p, const double2* u, double2* out, bool fp32) {
-  sp_status s = nonlinear_to_nv(p, u, 0, fp32);
+  sp_status s = nonlinear_to_nv(p, u, 0, fp32, !p->advect);
   if (s) return s;
   if (p->advect) {
     SP_TRY_HIP(launch_adv_solve(p, u, out, 1, fp32), "advected solve");
@@ -64,8 +66,9 @@ static sp_status check_scheme(sp_plan* p) {
   return SP_OK;
 }
 
-static size_t nv_count(const sp_plan* p) {
-  return (size_t)3 * p->d.ny * p->d.nzm * p->d.nx;
+// entries of the SBDF2 steps' previous nonlinear term, in either of its forms
+static size_t prev_count(const sp_plan* p) {
+  return (size_t)3 * p->d.ny * p->d.nzm * p->d.px;
 }
 
 // One SBDF2 step (scheme 1) with implicit step tau = the plan's dt:
@@ -77,8 +80,12 @@ static sp_status sbdf2_step(sp_plan* p, const double2* uk, const double2* ukm1, 
                             int mode, bool first) {
   SP_TRY_HIP(launch_synth_y(p, uk, false), "synth_y");
   if (!zline_fuses_x_inverse(p, false, 5)) SP_TRY_HIP(launch_fft_x_inv(p, false), "fft_x_inv");
-  SP_TRY_HIP(launch_z_product(p, mode, false), "z_product");
-  SP_TRY_HIP(launch_fft_x_fwd_sbdf2(p, p->nv_prev, first), "fft_x_fwd");
+  if (solve_takes_x_forward(p, false)) {
+    SP_TRY_HIP(launch_z_product(p, mode, false, true, p->nv_prev, first), "z_product");
+  } else {
+    SP_TRY_HIP(launch_z_product(p, mode, false), "z_product");
+    SP_TRY_HIP(launch_fft_x_fwd_sbdf2(p, p->nv_prev, first), "fft_x_fwd");
+  }
   SP_TRY_HIP(launch_analysis_solve_sbdf2(p, uk, ukm1, p->d.inv_dt, out, mode == 0 ? 1 : 0),
              "analysis+solve");
   return SP_OK;
@@ -179,7 +186,7 @@ sp_status base_at(sp_plan* p, int k) {
 // one linearised BEFE step about the cached base: J_Phi du
 static sp_status jvp_phi_step(sp_plan* p, const double2* du, double2* out) {
   const bool fp32 = (p->precision == SP_MIXED);
-  sp_status s = nonlinear_to_nv(p, du, 1, fp32);
+  sp_status s = nonlinear_to_nv(p, du, 1, fp32, !p->advect);
   if (s) return s;
   if (p->advect) {
     SP_TRY_HIP(launch_adv_solve(p, du, out, 0, fp32), "advected solve");
@@ -216,7 +223,7 @@ sp_status jvp_lin(sp_plan* p, int op, const double2* du, double2* out) {
     sp_status s = base_at(p, 0);
     if (s) return s;
     const bool fp32 = (p->precision == SP_MIXED);
-    s = nonlinear_to_nv(p, du, 1, fp32);
+    s = nonlinear_to_nv(p, du, 1, fp32, !p->advect);
     if (s) return s;
     if (p->advect)
       SP_TRY_HIP(launch_adv_solve_res(p, du, p->d.inv_dt, -p->d.inv_dt, out, fp32),
@@ -263,7 +270,7 @@ extern "C" sp_status sp_nonlinear(sp_plan* p, const double* u, double* out) {
   CHECK_PTR(u);
   CHECK_PTR(out);
   if (u == out) return set_error(p, SP_ERR_INVALID, "sp_nonlinear: out aliases u");
-  sp_status s = nonlinear_to_nv(p, (const double2*)u, 0, false);
+  sp_status s = nonlinear_to_nv(p, (const double2*)u, 0, false, false);
   if (s) return s;
   SP_TRY_HIP(launch_analysis_rhs(p, nullptr, 0.0, (double2*)out, false), "analysis_rhs");
   return SP_OK;
@@ -340,7 +347,7 @@ extern "C" sp_status sp_plan_set_scheme(sp_plan* p, int32_t scheme) {
   if (scheme == 1 && !p->sb_u) {
     const size_t cb = canon_count(p) * sizeof(double2);
     if (hipMalloc((void**)&p->sb_u, cb) != hipSuccess ||
-        hipMalloc((void**)&p->nv_prev, nv_count(p) * sizeof(double2)) != hipSuccess) {
+        hipMalloc((void**)&p->nv_prev, prev_count(p) * sizeof(double2)) != hipSuccess) {
       (void)hipGetLastError();
       if (p->sb_u) (void)hipFree(p->sb_u);
       if (p->nv_prev) (void)hipFree(p->nv_prev);
@@ -694,12 +701,23 @@ extern "C" sp_status sp_time_stage(sp_plan* p, int32_t stage, const double* u, d
   const bool fp32 = (p->precision == SP_MIXED);
   const double2* uu = (const double2*)u;
   double2* oo = (double2*)out;
-  sp_status s = befe_into(p, uu, oo, fp32);
-  if (s) return s;
+  // every stage as a kernel of its own (the solve would otherwise take the forward x
+  // transforms with it where solve_takes_x_forward says so)
+  struct Apart {
+    sp_plan* p;
+    explicit Apart(sp_plan* q) : p(q) { p->stages_apart = true; }
+    ~Apart() { p->stages_apart = false; }
+  };
+  sp_status s = SP_OK;
   if (stage == SP_STAGE_XINV && zline_fuses_x_inverse(p, fp32, 5)) {  // no launch of its own
     *avg_us = 0.0;
-    return SP_OK;
+    return befe_into(p, uu, oo, fp32);
   }
+  float ms = 0.f;
+  {
+    const Apart apart(p);
+    s = befe_into(p, uu, oo, fp32);
+    if (s) return s;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   SP_TRY_HIP(hipEventCreate(&e0), "event");
   if (hipEventCreate(&e1) != hipSuccess) {
@@ -718,11 +736,16 @@ extern "C" sp_status sp_time_stage(sp_plan* p, int32_t stage, const double* u, d
   }
   if (e == hipSuccess) e = hipEventRecord(e1, p->stream);
   if (e == hipSuccess) e = hipEventSynchronize(e1);
-  float ms = 0.f;
   if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (e != hipSuccess) return hip_check(p, e, "sp_time_stage");
+  }
+  if (solve_takes_x_forward(p, fp32)) {  // out as sp_befe_step gives it
+    s = befe_into(p, uu, oo, fp32);
+    if (s) return s;
+    SP_TRY_HIP(hipStreamSynchronize(p->stream), "sync");
+  }
   *avg_us = 1000.0 * ms / reps;
   return SP_OK;
 }

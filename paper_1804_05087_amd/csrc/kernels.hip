@@ -286,6 +286,7 @@ __device__ inline void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "w
 // length, offset of the odd halves (in entries), passes of 64 coefficients whose
 // partial sums wave 1 hands over at once.
 constexpr int kFoldChunk = 3;
+constexpr int kXoAhead = 6;  // terms of the x transform in flight
 // sets of 32 coefficients that hold n <= ny - 3
 __host__ __device__ constexpr int fold_sets(int ny) { return (ny - 3) / 32 + 1; }
 __host__ __device__ inline int fold_pad(int ny, bool fp32) {
@@ -323,12 +324,16 @@ __device__ inline double half_wave_sum(double a, double b) {
 // th[j][n] = Tinv[n][j], so the lanes' loads are contiguous.
 // Two-wave blocks are held to at most 168 VGPRs (3 waves per SIMD), so that
 // every mode's block is resident at once at 48x65x48 (2 x 1128 waves).
+// XO (with AN = 1): the last step of the forward x transforms too. nv then holds
+// h [3][ny][nz/2][8][Q] (Q = px / 8) and this mode's value is sum_a W_px^(m_x a) h_r(a),
+// r = m_x mod 8 (k_zline's XFO; the table twx[q] = exp(-2 pi i q / px)).
 // SB (with AN = 1): (4 x - x2) / 3 takes the place of x (an SBDF2 step).
 // RES (with AN != 0): the residual form of a Jacobian action, out = oa S(g) +
 // ob x, written in the Hermitian form: the block of an m_z = 0 mode at m_x > 0
 // also writes the conjugate at -m_x (whose block has nothing to do), and the
 // (0,0) mode is real. x's entries n <= N are kept in LDS for it.
-template <int E, int AN, bool RES = false, int NT = 1, bool MB = false, bool SB = false>
+template <int E, int AN, bool RES = false, int NT = 1, bool MB = false, bool SB = false,
+          bool XO = false>
 __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
     __attribute__((amdgpu_waves_per_eu(AN != 0 ? 3 : 1)))
     k_stokes_solve(const double2* __restrict__ g, double2* __restrict__ out,
@@ -338,7 +343,8 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
                    const void* __restrict__ nv_raw, const void* __restrict__ tinv_raw,
                    const double2* __restrict__ x, double xa, double oa = 1.0, double ob = 0.0,
                    size_t mx = 0, size_t mnv = 0, size_t mout = 0,
-                   const double2* __restrict__ x2 = nullptr) {
+                   const double2* __restrict__ x2 = nullptr,
+                   const double2* __restrict__ twx = nullptr) {
   static_assert(!RES || AN != 0, "the residual form reads x through the fused analysis");
   if constexpr (MB) {  // members of a batch (grid y)
     x += blockIdx.y * mx;
@@ -471,6 +477,36 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
       if (128 * q < 3 * jp) {  // uniform
         const int c = min((t >= jp) + (t >= 2 * jp), 2);
         const int jj = min(t - c * jp, jh - 1);
+        if constexpr (XO) {
+          const int Q = 3 * nx / 16;
+          const int px = 8 * Q;
+          const CA* h0 = nv + ((size_t)(c * ny + jj) * nzm + j) * px + (mxv & 7) * Q;
+          const CA* h1 = nv + ((size_t)(c * ny + N - jj) * nzm + j) * px + (mxv & 7) * Q;
+          const int step = mxv < 0 ? mxv + px : mxv;  // twiddle index per a
+          int w = 0;
+          CA s0 = mk((RA)0, (RA)0), s1 = s0;
+          for (int a0 = 0; a0 < Q; a0 += kXoAhead) {
+            CA v0[kXoAhead], v1[kXoAhead];
+#pragma unroll
+            for (int a = 0; a < kXoAhead; ++a)
+              if (a0 + a < Q) {  // uniform
+                v0[a] = h0[a0 + a];
+                v1[a] = h1[a0 + a];
+              }
+#pragma unroll
+            for (int a = 0; a < kXoAhead; ++a)
+              if (a0 + a < Q) {
+                const CA tw = twx[w];
+                w += step;
+                w -= w >= px ? px : 0;
+                s0 = cadd(s0, cmul(v0[a], tw));
+                s1 = cadd(s1, cmul(v1[a], tw));
+              }
+          }
+          fa[q] = s0;
+          fb[q] = s1;
+          continue;
+        }
         fa[q] = nv[c * cstride + (size_t)jj * nzm * nx + base];
         fb[q] = nv[c * cstride + (size_t)(N - jj) * nzm * nx + base];
       }
@@ -1180,86 +1216,73 @@ hipError_t launch_stokes_solve(sp_plan* p, const double2* g, double2* out, int i
   return hipGetLastError();
 }
 
-// Chebyshev analysis of p->nv fused into the solve: out = S(Tinv nv + xa x).
-hipError_t launch_analysis_solve(sp_plan* p, const double2* x, double xa, double2* out,
-                                 int inhomogeneous, bool fp32) {
+// Launches k_stokes_solve<E, AN, RES, NT, MB, SB, XO>: AN = 1 in FP64, 2 in FP32.
+template <bool RES, bool SB>
+static hipError_t solve_launch(sp_plan* p, const double2* x, const double2* x2, double xa, double oa,
+                               double ob, double2* out, int inhomogeneous, bool fp32) {
   const Dims& d = p->d;
-  const size_t sh = solve_lds_bytes(p, fp32 ? 2 : 1);
-  const dim3 grid(d.nx * d.nzh, p->mem.nb);
+  const bool xo = solve_takes_x_forward(p, fp32);
   const Members& mm = p->mem;
+  const size_t sh = solve_lds_bytes(p, fp32 ? 2 : 1, RES);
+  const dim3 grid(d.nx * d.nzh, mm.nb);
+  const void* nv = xo ? p->np : p->nv;
+  const size_t mnv = xo ? mm.np : mm.nv;
+  const void* th = fp32 ? (const void*)p->f_tinv_th : (const void*)p->d_tinv_th;
   SP_PROF_BEGIN(p, KID_SOLVE);
-#define SP_SOLVE_LAUNCH(EV, NTV)                                                                       \
-  if (fp32)                                                                                       \
-    hipLaunchKernelGGL((k_stokes_solve<EV, 2, false, 1, MB>), grid, dim3(128), sh, p->stream,      \
-                       nullptr, out, p->d_mode, p->d_hwp, p->mode_stride, d.nx, d.ny, d.nzh,      \
-                       d.alpha, d.gamma, d.re, d.inv_dt, d.wall_upper, d.wall_lower,             \
-                       inhomogeneous, p->nv, p->f_tinv_th, x, xa, 1.0, 0.0, mm.in, mm.nv, mm.out); \
-  else                                                                                            \
-    hipLaunchKernelGGL((k_stokes_solve<EV, 1, false, NTV, MB>), grid, dim3(128), sh, p->stream,      \
-                       nullptr, out, p->d_mode, p->d_hwp, p->mode_stride, d.nx, d.ny, d.nzh,      \
-                       d.alpha, d.gamma, d.re, d.inv_dt, d.wall_upper, d.wall_lower,             \
-                       inhomogeneous, p->nv, p->d_tinv_th, x, xa, 1.0, 0.0, mm.in, mm.nv, mm.out)
-  if (mm.nb > 1) {
-    constexpr bool MB = true;
+  auto run = [&](auto an, auto mb, auto xov) {
+    constexpr int AN = decltype(an)::value;
+    constexpr bool MB = decltype(mb)::value, XO = decltype(xov)::value;
+#define SP_SOLVE_LAUNCH(EV, NTV)                                                                  \
+  hipLaunchKernelGGL((k_stokes_solve<EV, AN, RES, AN == 1 ? NTV : 1, MB, SB, XO>), grid,          \
+                     dim3(128), sh, p->stream, nullptr, out, p->d_mode, p->d_hwp, p->mode_stride, \
+                     d.nx, d.ny, d.nzh, d.alpha, d.gamma, d.re, d.inv_dt, d.wall_upper,           \
+                     d.wall_lower, inhomogeneous, nv, th, x, xa, oa, ob, mm.in, mnv, mm.out, x2,  \
+                     p->d_twx)
     SP_SOLVE_DISPATCH(SP_SOLVE_LAUNCH)
-  } else {
-    constexpr bool MB = false;
-    SP_SOLVE_DISPATCH(SP_SOLVE_LAUNCH)
-  }
 #undef SP_SOLVE_LAUNCH
+  };
+  auto run2 = [&](auto an, auto xov) {
+    if constexpr (SB) {  // single evaluations only
+      run(an, std::false_type{}, xov);
+    } else {
+      if (mm.nb > 1)
+        run(an, std::true_type{}, xov);
+      else
+        run(an, std::false_type{}, xov);
+    }
+  };
+  if constexpr (!SB) {
+    if (fp32) run2(std::integral_constant<int, 2>{}, std::false_type{});
+  }
+  if (!fp32) {
+    if (xo)
+      run2(std::integral_constant<int, 1>{}, std::true_type{});
+    else
+      run2(std::integral_constant<int, 1>{}, std::false_type{});
+  }
   SP_PROF_END(p, KID_SOLVE);
   return hipGetLastError();
+}
+
+// Chebyshev analysis of p->nv (or of p->np, see solve_takes_x_forward) fused into the
+// solve: out = S(Tinv nv + xa x).
+hipError_t launch_analysis_solve(sp_plan* p, const double2* x, double xa, double2* out,
+                                 int inhomogeneous, bool fp32) {
+  return solve_launch<false, false>(p, x, nullptr, xa, 1.0, 0.0, out, inhomogeneous, fp32);
 }
 
 // out = S(Tinv nv + xa (4 x - x2) / 3), FP64: the combination of the last two states
 // took a launch of its own, 2.6 us of a 27 us step at 32x33x32.
 hipError_t launch_analysis_solve_sbdf2(sp_plan* p, const double2* x, const double2* x2, double xa,
                                        double2* out, int inhomogeneous) {
-  const Dims& d = p->d;
-  const size_t sh = solve_lds_bytes(p, 1);
-  SP_PROF_BEGIN(p, KID_SOLVE);
-#define SP_SOLVE_LAUNCH(EV, NTV)                                                                 \
-  hipLaunchKernelGGL((k_stokes_solve<EV, 1, false, NTV, false, true>), dim3(d.nx * d.nzh),        \
-                     dim3(128), sh, p->stream, nullptr, out, p->d_mode, p->d_hwp, p->mode_stride, \
-                     d.nx, d.ny, d.nzh, d.alpha, d.gamma, d.re, d.inv_dt, d.wall_upper,           \
-                     d.wall_lower, inhomogeneous, p->nv, p->d_tinv_th, x, xa, 1.0, 0.0,           \
-                     (size_t)0, (size_t)0, (size_t)0, x2)
-  SP_SOLVE_DISPATCH(SP_SOLVE_LAUNCH)
-#undef SP_SOLVE_LAUNCH
-  SP_PROF_END(p, KID_SOLVE);
-  return hipGetLastError();
+  return solve_launch<false, true>(p, x, x2, xa, 1.0, 0.0, out, inhomogeneous, false);
 }
 
 // The residual form of the same: out = oa S(Tinv nv + xa x) + ob x in the
 // Hermitian form, homogeneous walls.
 hipError_t launch_analysis_solve_res(sp_plan* p, const double2* x, double xa, double oa, double ob,
                                      double2* out, bool fp32) {
-  const Dims& d = p->d;
-  const size_t sh = solve_lds_bytes(p, fp32 ? 2 : 1, true);
-  const dim3 grid(d.nx * d.nzh, p->mem.nb);
-  const Members& mm = p->mem;
-  SP_PROF_BEGIN(p, KID_SOLVE);
-#define SP_SOLVE_LAUNCH(EV, NTV)                                                                       \
-  if (fp32)                                                                                       \
-    hipLaunchKernelGGL((k_stokes_solve<EV, 2, true, 1, MB>), grid, dim3(128), sh,           \
-                       p->stream, nullptr, out, p->d_mode, p->d_hwp, p->mode_stride, d.nx, d.ny,  \
-                       d.nzh, d.alpha, d.gamma, d.re, d.inv_dt, d.wall_upper, d.wall_lower, 0,   \
-                       p->nv, p->f_tinv_th, x, xa, oa, ob, mm.in, mm.nv, mm.out);                \
-  else                                                                                            \
-    hipLaunchKernelGGL((k_stokes_solve<EV, 1, true, NTV, MB>), grid, dim3(128), sh,           \
-                       p->stream, nullptr, out, p->d_mode, p->d_hwp, p->mode_stride, d.nx, d.ny,  \
-                       d.nzh, d.alpha, d.gamma, d.re, d.inv_dt, d.wall_upper, d.wall_lower, 0,   \
-                       p->nv, p->d_tinv_th, x, xa, oa, ob, mm.in, mm.nv, mm.out)
-  if (mm.nb > 1) {
-    constexpr bool MB = true;
-    SP_SOLVE_DISPATCH(SP_SOLVE_LAUNCH)
-  } else {
-    constexpr bool MB = false;
-    SP_SOLVE_DISPATCH(SP_SOLVE_LAUNCH)
-  }
-#undef SP_SOLVE_LAUNCH
-  SP_PROF_END(p, KID_SOLVE);
-  return hipGetLastError();
+  return solve_launch<true, false>(p, x, nullptr, xa, oa, ob, out, 0, fp32);
 }
 
 hipError_t launch_axpby(sp_plan* p, const double2* x, double a, const double2* y, double b,

@@ -195,6 +195,7 @@ struct sp_plan {
   int base_step = 0;  // trajectory index of the cached base state
   // laminar advection in the implicit operator: dense real solution operators of the
   // mode pairs, [nx/2][nzm][3(N-1)][3 ny, even], and the (0,0) mode's wall response
+  bool stages_apart = false;  // stage timing: every stage as a kernel of its own
   bool symmetric = false;  // Newton drivers confined to the shift-reflect subspace
   bool advect = false;
   bool adv_host = false;  // build the advected operators on the host (reference) or the device
@@ -239,7 +240,13 @@ hipError_t launch_synth_y(sp_plan* p, const double2* u, bool fp32);
 hipError_t launch_fft_x_inv(sp_plan* p, bool fp32);
 // mode 0: u x omega ; 1: linearised du x Omega + U x dw (needs base) ;
 // 2: store U, Omega into base (no product) ; 3: adjoint (see kernels.hip)
-hipError_t launch_z_product(sp_plan* p, int mode, bool fp32);
+// xfo (FP64, solve_takes_x_forward): the first step of the forward x transforms too, into
+// p->np as the solve reads it; prev: with the SBDF2 extrapolation (first: none yet)
+hipError_t launch_z_product(sp_plan* p, int mode, bool fp32, bool xfo = false,
+                            double2* prev = nullptr, bool first = false);
+// true when the solve that follows the product takes the forward x transforms itself
+// (from p->np), so that no forward x launch comes between
+bool solve_takes_x_forward(const sp_plan* p, bool fp32);
 // true when the z-line kernels take the inverse x transforms themselves,
 // reading nfields y-valued fields (5: launch_z_product, from p->yv; 3:
 // launch_adj_z, from p->nv), so that no separate inverse x launch precedes them

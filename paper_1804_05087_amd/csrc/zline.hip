@@ -104,12 +104,20 @@ struct ZLineMap {
 // (ny * (px / XL), members) blocks; in and out do not alias.
 // Otherwise in = the x-physical fields [f][y][x][kz] (out may alias it) and
 // the grid is (ny, ceil(px / XL), members). Members are mi and mo apart.
-template <typename R, int P1, int P2, int XL, class Op, bool XF = false>
+//
+// With XFO (and XF) the block also starts the forward x transforms: of the outputs at its
+// lines x = a + Q j it forms h_r(a) = sum_j W_8^(r j) N(a + Q j) and stores [f][y][kz][r][a];
+// the kept mode m = r mod 8 is then sum_a W_px^(m a) h_r(a) (kernels.hip), Q terms.
+// SB: the SBDF2 steps' extrapolation as they are stored, out = 2 h - prev, prev = h
+// (first: out = prev = h).
+template <typename R, int P1, int P2, int XL, class Op, bool XF = false, bool XFO = false,
+          bool SB = false>
 __global__ void __launch_bounds__(256)
     k_zline(const typename V2<R>::T* in, typename V2<R>::T* out,
             R* __restrict__ base, const typename V2<R>::T* __restrict__ tw, ZLineMap map, int ny,
             int px, int nzm, R scale, const typename V2<R>::T* __restrict__ twx = nullptr,
-            int nx = 0, R alpha = 0, R gamma = 0, size_t mi = 0, size_t mo = 0) {
+            int nx = 0, R alpha = 0, R gamma = 0, size_t mi = 0, size_t mo = 0,
+            typename V2<R>::T* prev = nullptr, int first = 0) {
   using C = typename V2<R>::T;
   constexpr int P = P1 * P2;
   constexpr int NI = Op::NI;
@@ -421,6 +429,42 @@ __global__ void __launch_bounds__(256)
       }
     }
     __syncthreads();
+    if constexpr (XFO) {
+      // unpack, scale and transform over the block's eight lines: task (output field, m)
+      static_assert(XF && XL == 8 && NF == 2, "XFO: three fields on two packed lines");
+      for (int task = tid; task < 3 * nzk; task += 256) {
+        const int fo = task / nzk;
+        const int m = task - fo * nzk;
+        const int mr = m == 0 ? 0 : P - m;
+        const size_t off = (size_t)fo * fs + ((size_t)y * nzk + m) * px + x0;
+        C v[XL], b[XL];
+        if constexpr (SB) {  // in flight behind the transform
+#pragma unroll
+          for (int r = 0; r < XL; ++r) b[r] = prev[first ? 0 : off + r * xq];
+        }
+#pragma unroll
+        for (int xl = 0; xl < XL; ++xl) {
+          const C* o = ex1 + (xl * NF + (fo >> 1)) * P;
+          const C a = o[m];
+          const C am = conjc(o[mr]);
+          const C s1 = cscale(cadd(a, am), (R)0.5 * scale);
+          const C d = csub(a, am);
+          v[xl] = fo == 2 ? cscale(a, scale)
+                          : (fo == 0 ? s1 : mk(d.y * (R)0.5 * scale, -d.x * (R)0.5 * scale));
+        }
+        dft_reg<XL, P, C, R>(v, (R)-1, twl);
+#pragma unroll
+        for (int r = 0; r < XL; ++r) {
+          C h = v[r];
+          if constexpr (SB) {
+            prev[off + r * xq] = h;
+            if (!first) h = mk((R)2 * h.x - b[r].x, (R)2 * h.y - b[r].y);
+          }
+          out[off + r * xq] = h;
+        }
+      }
+      return;
+    }
     // unpack, scale and store the kept modes m < nzm: task (xl, line f, m)
     for (int task = tid; task < XL * NF * nzk; task += 256) {
       const int m = task % nzk;
@@ -458,9 +502,10 @@ constexpr int kZXL = 8;
 // 108, 9.5 against 8.6 at 81, 8.3 against 8.6 at 54.
 constexpr int zline_lines(int P) { return P > 72 ? 4 : 8; }
 
-template <typename R, class Op, bool XF = false>
+template <typename R, class Op, bool XF = false, bool XFO = false, bool SB = false>
 static void zline_launch(sp_plan* p, const void* in, void* out, R* base, const void* tw,
-                         const ZLineMap& map, double scale, const void* twx = nullptr) {
+                         const ZLineMap& map, double scale, const void* twx = nullptr,
+                         void* prev = nullptr, bool first = false) {
   const Dims& d = p->d;
   using C = typename V2<R>::T;
   const int nb = p->mem.nb;
@@ -472,9 +517,10 @@ static void zline_launch(sp_plan* p, const void* in, void* out, R* base, const v
   {                                                                                            \
     constexpr int XL = XF ? kZXL : zline_lines(A * B);                                         \
     const dim3 grid = XF ? dim3(d.ny * (d.px / XL), nb) : dim3(d.ny, (d.px + XL - 1) / XL, nb); \
-    hipLaunchKernelGGL((k_zline<R, A, B, XL, Op, XF>), grid, dim3(256), 0, p->stream, ci, co,   \
+    hipLaunchKernelGGL((k_zline<R, A, B, XL, Op, XF, XFO, SB>), grid, dim3(256), 0, p->stream, ci, co,   \
                        base, ct, map, d.ny, d.px, d.nzm, (R)scale, cx, d.nx, (R)d.alpha,       \
-                       (R)d.gamma, XF ? p->mem.yv : p->mem.xp, p->mem.np);                     \
+                       (R)d.gamma, XF ? p->mem.yv : p->mem.xp, p->mem.np, (C*)prev,            \
+                       first ? 1 : 0);                                                         \
   }
   if constexpr (sizeof(R) == sizeof(float) || XF) {
     SP_REG_FFT_DISPATCH(d.pz, ZL)
@@ -502,7 +548,20 @@ bool zline_fuses_x_inverse(const sp_plan* p, bool fp32, int nfields) {
   return (size_t)(d.px / kZXL) * plane <= bound;
 }
 
-hipError_t launch_z_product(sp_plan* p, int mode, bool fp32) {
+// The forward x transforms split between this kernel (XFO) and the solve save a launch,
+// 3 to 4 us of the device and 3.7 us of the host's enqueue, which bounds the smallest
+// grids; the solve then gathers Q = px / 8 values for each it read before. Measured, us
+// per Phi with the transform apart and split: 17.1, 14.7 (16x17x16, Q = 3), 20.5, 18.3
+// (16x65x16), 20.9, 19.4 (32x33x32, Q = 6), 26.1, 24.6 (32x65x32), 29.3, 28.3 (48x33x48,
+// Q = 9), 38.4, 40.0 (48x65x48), 36.5, 38.3 (64x33x64, Q = 12); members of a batch, which
+// the gather's cache lines bound: 0.74, 0.78 (16x17x16), 4.5, 4.6 (32x33x32), 20.5, 22.6
+// (48x65x48). FP32 keeps the transform of its own (the order of its sums).
+bool solve_takes_x_forward(const sp_plan* p, bool fp32) {
+  return !fp32 && !p->stages_apart && zline_fuses_x_inverse(p, false, 5) &&
+         p->d.px / kZXL <= 6;
+}
+
+hipError_t launch_z_product(sp_plan* p, int mode, bool fp32, bool xfo, double2* prev, bool first) {
   const Dims& d = p->d;
   if (reg_fft_split(d.pz, fp32) == 0) return launch_z_product_lds(p, mode, fp32);
   const double scale = 1.0 / ((double)d.px * d.pz);
@@ -534,7 +593,21 @@ hipError_t launch_z_product(sp_plan* p, int mode, bool fp32) {
                                                       scale, p->d_twx);
     }
   };
-  if (zline_fuses_x_inverse(p, fp32, 5))
+  if (xfo) {
+    auto ahead = [&](auto sb) {
+      constexpr bool SB = decltype(sb)::value;
+      if (mode == 0)
+        zline_launch<double, OpCross<double>, true, true, SB>(
+            p, p->yv, p->np, p->base, p->d_twz, map, scale, p->d_twx, prev, first);
+      else
+        zline_launch<double, OpCrossLin<double>, true, true, SB>(
+            p, p->yv, p->np, p->base, p->d_twz, map, scale, p->d_twx, prev, first);
+    };
+    if (prev)
+      ahead(std::true_type{});
+    else
+      ahead(std::false_type{});
+  } else if (zline_fuses_x_inverse(p, fp32, 5))
     run(std::true_type{});
   else
     run(std::false_type{});
