@@ -243,7 +243,7 @@ static std::vector<F> convert(const std::vector<D>& v) {
 static void free_plan(sp_plan* p) {
   void* ptrs[] = {p->d_T,   p->d_TD,  p->d_Tinv, p->d_G,    p->d_hw,   p->d_mode, p->d_twx,
                   p->d_twz, p->f_twx, p->f_twz,  p->f_T,    p->f_TD,   p->f_Tinv, p->d_scratch,
-                  p->d_yfrag, p->f_yfrag, p->d_tinv_th, p->f_tinv_th, p->d_hwp};
+                  p->d_yfrag, p->f_yfrag, p->d_tinv_th, p->f_tinv_th, p->d_hwp, p->d_yfold};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
   if (p->h_partial) (void)hipHostFree(p->h_partial);
@@ -389,6 +389,24 @@ extern "C" sp_status sp_plan_create(const sp_params* prm, void* hip_stream, sp_p
       return fail(s);
     auto ff = convert<float>(fr);
     if ((s = upload(p, (void**)&p->f_yfrag, ff.data(), ff.size() * sizeof(float), "fyfrag")))
+      return fail(s);
+  }
+  {
+    const int ny = d.ny, jh = (ny - 1) / 2 + 1, nt = ycontract_fold_tiles(ny);
+    const int ks = ycontract_fold_ks(ny);
+    std::vector<double> fr((size_t)YF_COUNT * 2 * nt * ks * 64, 0.0);
+    double* o = fr.data();
+    for (int m = 0; m < YF_COUNT; ++m)
+      for (int par = 0; par < 2; ++par)
+        for (int t = 0; t < nt; ++t)
+          for (int st = 0; st < ks; ++st)
+            for (int l = 0; l < 64; ++l, ++o) {
+              const int r = 16 * t + l % 16, c = 2 * (4 * st + l / 16) + par;
+              if (r < jh && c < ny)
+                *o = m == YF_T ? T[(size_t)r * ny + c]
+                               : (m == YF_TD ? TD[(size_t)r * ny + c] : Tinv[(size_t)c * ny + r]);
+            }
+    if ((s = upload(p, (void**)&p->d_yfold, fr.data(), fr.size() * sizeof(double), "yfold")))
       return fail(s);
   }
   {

@@ -52,6 +52,16 @@ inline int ycontract_ks(int ny) {
   return k <= 5 ? 5 : k <= 9 ? 9 : k <= 17 ? 17 : k <= 25 ? 25 : 33;
 }
 
+// The FP64 synthesis works on the even and odd coefficients apart (ycontract.hip): half
+// the rows, (ny / 2 + 1) / 16 tiles rounded up, and sums of ycontract_fold_ks(ny) steps
+// of 4 coefficients of one parity.
+enum YFoldId { YF_T = 0, YF_TD, YF_TINV_T, YF_COUNT };
+inline int ycontract_fold_ks(int ny) {
+  const int k = ((ny + 1) / 2 + 3) / 4;
+  return k <= 3 ? 3 : k <= 5 ? 5 : k <= 7 ? 7 : k <= 9 ? 9 : k <= 13 ? 13 : 17;
+}
+inline int ycontract_fold_tiles(int ny) { return ((ny - 1) / 2 + 1 + 15) / 16; }
+
 struct Dims {
   int nx, ny, nz, N, nzh, nzm, px, pz;
   double alpha, gamma, re, dt, inv_dt, wall_upper, wall_lower;
@@ -162,6 +172,9 @@ struct sp_plan {
   double* d_yfrag = nullptr;
   float* f_yfrag = nullptr;
   size_t yfrag_stride = 0;    // elements per matrix
+  // the FP64 synthesis' matrices by parity (sp::YFoldId): even coefficients, then odd,
+  // frag[t][s][l] = M(16 t + l % 16, 2 (4 s + l / 16) + parity), rows j <= (ny - 1) / 2
+  double* d_yfold = nullptr;
   sp::FFTPlan1D fx, fz;
 
   // scratch (device)

@@ -4,7 +4,7 @@
 // applied to the ny-long y-columns of all 2 * nx * (nz/2) real columns of a
 // field (paper Sec. 3.2: coefficients <-> values at the Gauss-Lobatto points):
 //
-//   k_ysynth_mfma  coefficients -> y-values:  out_f[y][col] = sum_n M_f[y][n] u_c[n][col]
+//   k_ysynth_mfma, k_ysynth_fold (FP32, FP64)  coefficients -> y-values:  out_f[y][col] = sum_n M_f[y][n] u_c[n][col]
 //                  (synthesis with T and T.D; adjoint of the analysis with Tinv^T)
 //   k_ycoef_mfma   y-values -> coefficients:  out_c[col][n] = sum_t sum_j M_t[n][j] Y_t[j][col]
 //                  (analysis with Tinv)
@@ -30,6 +30,8 @@
 // and the last, partial row tile goes through the MFMA like the others (its
 // padded rows are zero).
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "device_common.h"
 #include "sp_internal.h"
@@ -173,6 +175,93 @@ __global__ void __launch_bounds__(256)
         v.x = accr[i];
         v.y = acci[i];
         *reinterpret_cast<C*>(o + (size_t)y * nq * 2) = v;
+      }
+    }
+  }
+}
+
+// Work list of the FP64 synthesis: entry g applies the matrix at frag[g] (even
+// coefficients' table, then the odd ones') to component comp[g] and writes field[g];
+// rows j and N - j are s + t and sign (s - t) of the even sum s and the odd sum t (sign
+// 1 for T and Tinv^T, whose column n has parity n about y = 0, -1 for T.D).
+struct SynthFold {
+  int n;
+  int comp[5];
+  int field[5];
+  double sign[5];
+  const double* frag[5];
+};
+
+// The FP64 synthesis: as k_ysynth_mfma, a wave per 16 modes, 16-row tile and work-list
+// entry, on the even and odd coefficients apart, so that a tile of rows j <= N / 2 gives
+// the rows N - j as well. That takes 0.57 times the waves, MFMAs and loads at ny = 65 and
+// 97 (at 96x97x96 the whole matrix' MFMAs alone were 14 of its 32 us). FP32 keeps the
+// whole matrix (the order of its sums).
+template <int KS, bool MB>
+__global__ void __launch_bounds__(256)
+    k_ysynth_fold(const double2* __restrict__ u, SynthFold spec, double2* __restrict__ out, int nx,
+                  int ny, int nzh, int nzm, size_t mu, size_t mout) {
+  using MF = Mfma<double>;
+  const int lane = threadIdx.x & 63;
+  const int kq = lane >> 4;
+  const int nq = nzm * nx;
+  const Blk3 bk = ycontract_block();
+  int g = bk.z;
+  if constexpr (MB) {  // grid z = work-list entries x members
+    const int member = bk.z / spec.n;
+    g = bk.z - member * spec.n;
+    u += member * mu;
+    out += member * mout;
+  }
+  const int t = bk.y;
+  const int q0 = (bk.x * 4 + (threadIdx.x >> 6)) * 16;
+  const int q = q0 + (lane & 15);
+  const bool qv = q < nq;
+  double ae[KS], ao[KS], er[KS], ei[KS], odr[KS], odi[KS];
+  {
+    const double* fa = spec.frag[g] + (size_t)t * KS * 64 + lane;
+    const double* fo = fa + (size_t)gridDim.y * KS * 64;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      ae[s] = fa[s * 64];
+      ao[s] = fo[s * 64];
+    }
+    const int qc = qv ? q : nq - 1;
+    const int kz = qc / nx;
+    const int mx = qc - kz * nx;
+    const double2* src = u + (((size_t)spec.comp[g] * nx + mx) * nzh + kz) * ny;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const int n = 2 * (4 * s + kq);
+      const double2 v = src[n < ny ? n : ny - 1];
+      const double2 w = src[n + 1 < ny ? n + 1 : ny - 1];
+      const double m = (qv && n < ny) ? 1.0 : 0.0, mo = (qv && n + 1 < ny) ? 1.0 : 0.0;
+      er[s] = v.x * m;
+      ei[s] = v.y * m;
+      odr[s] = w.x * mo;
+      odi[s] = w.y * mo;
+    }
+  }
+  MF::acc_t sr = {0, 0, 0, 0}, si = {0, 0, 0, 0}, tr = {0, 0, 0, 0}, ti = {0, 0, 0, 0};
+#pragma unroll
+  for (int s = 0; s < KS; ++s) {
+    sr = MF::mma(ae[s], er[s], sr);
+    si = MF::mma(ae[s], ei[s], si);
+    tr = MF::mma(ao[s], odr[s], tr);
+    ti = MF::mma(ao[s], odi[s], ti);
+  }
+  if (qv) {
+    double2* o = out + (size_t)spec.field[g] * ny * nq + q;
+    const double sg = spec.sign[g];
+    const int jh = (ny - 1) / 2 + 1;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int y = 16 * t + MF::drow(kq, i);
+      if (y < jh) {
+        o[(size_t)y * nq] = make_double2(sr[i] + tr[i], si[i] + ti[i]);
+        if (ny - 1 - y != y)
+          o[(size_t)(ny - 1 - y) * nq] =
+              make_double2(sg * (sr[i] - tr[i]), sg * (si[i] - ti[i]));
       }
     }
   }
@@ -513,25 +602,37 @@ static YMat<R> ymat(const sp_plan* p, int id) {
   }
 }
 
+// The synthesis' work: forward (which = 0), fields u, du/dy, v, w, dw/dy; adjoint of the
+// analysis (1), Tinv^T on each component.
+struct SynthWork {
+  int n, comp[5], mat[5];
+};
+static constexpr SynthWork kSynthWork[2] = {{5, {0, 0, 1, 2, 2}, {YF_T, YF_TD, YF_T, YF_T, YF_TD}},
+                                            {3, {0, 1, 2}, {YF_TINV_T, YF_TINV_T, YF_TINV_T}}};
+
 template <typename R>
 static SynthSpec<R> synth_spec(const sp_plan* p, int which) {
+  const SynthWork& w = kSynthWork[which];
   SynthSpec<R> sp{};
-  if (which == 0) {  // forward: fields u, du/dy, v, w, dw/dy
-    const int comp[5] = {0, 0, 1, 2, 2};
-    const int mat[5] = {YM_T, YM_TD, YM_T, YM_T, YM_TD};
-    sp.n = 5;
-    for (int g = 0; g < 5; ++g) {
-      sp.comp[g] = comp[g];
-      sp.field[g] = g;
-      sp.mat[g] = ymat<R>(p, mat[g]);
-    }
-  } else {  // adjoint of the analysis: Tinv^T on each component
-    sp.n = 3;
-    for (int g = 0; g < 3; ++g) {
-      sp.comp[g] = g;
-      sp.field[g] = g;
-      sp.mat[g] = ymat<R>(p, YM_TINV_T);
-    }
+  sp.n = w.n;
+  for (int g = 0; g < w.n; ++g) {
+    sp.comp[g] = w.comp[g];
+    sp.field[g] = g;
+    sp.mat[g] = ymat<R>(p, w.mat[g] == YF_T ? YM_T : (w.mat[g] == YF_TD ? YM_TD : YM_TINV_T));
+  }
+  return sp;
+}
+
+static SynthFold synth_fold(const sp_plan* p, int which) {
+  const SynthWork& w = kSynthWork[which];
+  const size_t per = (size_t)2 * ycontract_fold_tiles(p->d.ny) * ycontract_fold_ks(p->d.ny) * 64;
+  SynthFold sp{};
+  sp.n = w.n;
+  for (int g = 0; g < w.n; ++g) {
+    sp.comp[g] = w.comp[g];
+    sp.field[g] = g;
+    sp.sign[g] = w.mat[g] == YF_TD ? -1.0 : 1.0;
+    sp.frag[g] = p->d_yfold + w.mat[g] * per;
   }
   return sp;
 }
@@ -550,39 +651,60 @@ static dim3 ycoef_grid(const Dims& d, int* nqb) {
   return g;
 }
 
+// FP64 synthesis on the parities apart (k_ysynth_fold) or on the whole matrix: the
+// fold has 0.5 to 0.67 times the waves, each a little longer (twice the stores), so it
+// pays where the whole form's waves queue up (two or more per SIMD) or its sums are
+// long. Measured, us per launch, whole and fold: 3.63, 3.89 (32x33x32, 480 waves), 7.03,
+// 7.45 (48x65x48, 1800), 11.1, 8.3 (64x65x64, 3200), 7.96, 7.62 (128x33x64), 6.66, 5.90
+// (128x17x128), 15.2, 9.6 (96x49x96), 31.7, 23.3 (96x97x96), 10.2, 7.4 (32x129x32, 1440).
+static bool synth_folds(const Dims& d, int n) {
+  const long waves = (long)((d.nzm * d.nx + 63) / 64) * ((d.ny + 15) / 16) * n * 4;
+  return waves >= 2048 || ycontract_ks(d.ny) >= 25;
+}
+
 hipError_t launch_synth_tab(sp_plan* p, const double2* u, int which, void* out, bool fp32) {
   const Dims& d = p->d;
   // 64 modes per block, every 16-row tile, one work-list entry per z index
-  const SynthSpec<double> sp64 = synth_spec<double>(p, which);
-  const dim3 grid((d.nzm * d.nx + 63) / 64, (d.ny + 15) / 16, sp64.n * p->mem.nb);
+  const int n = kSynthWork[which].n;
+  const bool fold = !fp32 && synth_folds(d, n);
+  const dim3 grid((d.nzm * d.nx + 63) / 64, fold ? ycontract_fold_tiles(d.ny) : (d.ny + 15) / 16,
+                  n * p->mem.nb);
   SP_PROF_BEGIN(p, KID_SYNTH_Y);
-  if (fp32) {
-    const SynthSpec<float> sp = synth_spec<float>(p, which);
-#define L32(KS)                                                                                  \
-  hipLaunchKernelGGL((k_ysynth_mfma<float, KS, MB>), grid, dim3(256), 0, p->stream, u, sp,          \
-                     (float*)out, d.nx, d.ny, d.nzh, d.nzm, p->mem.in, p->mem.yv)
-    if (p->mem.nb > 1) {
-      constexpr bool MB = true;
-      SP_KS_DISPATCH(d.ny, L32);
+  auto run = [&](auto mb) {
+    constexpr bool MB = decltype(mb)::value;
+    auto whole = [&](auto zero) {
+      using R = decltype(zero);
+      const SynthSpec<R> sp = synth_spec<R>(p, which);
+#define LW(KS)                                                                                  \
+  hipLaunchKernelGGL((k_ysynth_mfma<R, KS, MB>), grid, dim3(256), 0, p->stream, u, sp, (R*)out, \
+                     d.nx, d.ny, d.nzh, d.nzm, p->mem.in, p->mem.yv)
+      SP_KS_DISPATCH(d.ny, LW);
+#undef LW
+    };
+    if (fp32) {
+      whole(0.0f);
+    } else if (!fold) {
+      whole(0.0);
     } else {
-      constexpr bool MB = false;
-      SP_KS_DISPATCH(d.ny, L32);
+      const SynthFold sp = synth_fold(p, which);
+#define LF(KS)                                                                                  \
+  hipLaunchKernelGGL((k_ysynth_fold<KS, MB>), grid, dim3(256), 0, p->stream, u, sp,             \
+                     (double2*)out, d.nx, d.ny, d.nzh, d.nzm, p->mem.in, p->mem.yv)
+      switch (ycontract_fold_ks(d.ny)) {
+        case 3: LF(3); break;
+        case 5: LF(5); break;
+        case 7: LF(7); break;
+        case 9: LF(9); break;
+        case 13: LF(13); break;
+        default: LF(17); break;
+      }
+#undef LF
     }
-#undef L32
-  } else {
-    const SynthSpec<double>& sp = sp64;
-#define L64(KS)                                                                                  \
-  hipLaunchKernelGGL((k_ysynth_mfma<double, KS, MB>), grid, dim3(256), 0, p->stream, u, sp,         \
-                     (double*)out, d.nx, d.ny, d.nzh, d.nzm, p->mem.in, p->mem.yv)
-    if (p->mem.nb > 1) {
-      constexpr bool MB = true;
-      SP_KS_DISPATCH(d.ny, L64);
-    } else {
-      constexpr bool MB = false;
-      SP_KS_DISPATCH(d.ny, L64);
-    }
-#undef L64
-  }
+  };
+  if (p->mem.nb > 1)
+    run(std::true_type{});
+  else
+    run(std::false_type{});
   SP_PROF_END(p, KID_SYNTH_Y);
   return hipGetLastError();
 }
