@@ -19,7 +19,7 @@
 
 #include "device_common.h"
 #include "solve_core.h"
-#include "solve_row.h"
+#include "solve_reg.h"
 #include "sp_internal.h"
 
 namespace sp {
@@ -27,45 +27,31 @@ namespace sp {
 // ---------------------------------------------------------------------------
 // stokes_solve_adj: out = S_0^+ w per mode (conjugate transpose of the solve
 // with homogeneous walls): the forward steps of k_stokes_solve transposed and
-// taken in reverse order. One 64-lane wave per mode, four 16-lane rows:
-// rows 0, 1 run the (v, p) chain with v of parity r, rows 2, 3 the u_perp
-// chain of parity r - 2, whose transposed Helmholtz sweep shares a step with
-// the v sweep of rows 0, 1. (0,0) mode: rows 0, 1 u, rows 2, 3 w.
+// taken in reverse order, on the same chains in the same registers (solve_reg.h).
+// One 64-lane wave per mode, four 16-lane rows: rows 0, 1 run the (v, p) chain with
+// v of parity r, rows 2, 3 the u_perp chain of parity r - 2, whose transposed
+// Helmholtz sweep shares a step with the Poisson sweep of rows 0, 1. (0,0) mode:
+// rows 0, 1 u, rows 2, 3 w. Bound by that one chain of steps; with its
+// operands in fifteen LDS arrays (three to four round trips and one or two barriers a
+// step, 30 KB a mode at ny = 97) it took 6.7 / 10.3 / 15.4 / 107 us at 16x17x16,
+// 32x33x32, 48x65x48 and 96x97x96; in registers it takes 4.8 / 6.6 / 9.9 / 28 us.
 // ---------------------------------------------------------------------------
-#define SP_ROW_PAR(par, body)                       \
-  _Pragma("unroll") for (int e_ = 0; e_ < E; ++e_) { \
-    const int n = (par) + 2 * (l * E + e_);          \
-    if (n <= N) {                                    \
-      body                                           \
-    }                                                \
-  }
-
 template <int E>
 __global__ void __launch_bounds__(64)
     k_stokes_solve_adj(const double2* __restrict__ w, double2* __restrict__ out,
-                       const double* __restrict__ modedata, const double* __restrict__ hw_g,
+                       const double* __restrict__ modedata, const double* __restrict__ hwp_g,
                        int stride, int nx, int ny, int nzh, double alpha, double gamma, double re,
                        double inv_dt) {
   extern __shared__ unsigned char smem_raw[];
   const int N = ny - 1;
   const int n1 = ny;
   double* rec = reinterpret_cast<double*>(smem_raw);
-  double* hw = rec + stride;
-  cd* Upb = reinterpret_cast<cd*>(hw + 3 * n1);  // adjoint of u_par
-  cd* Ub = Upb + n1;                              // adjoint of u_perp
-  cd* Vb = Ub + n1;                               // adjoint of v
-  cd* A = Vb + n1;
-  cd* Tm = A + n1;
-  cd* W = Tm + n1;    // scratch of rows 0, 1
-  cd* W2 = W + n1;    // scratch of rows 2, 3
-  cd* Rb = W2 + n1;
-  cd* Rb2 = Rb + n1;
-  cd* Pb = Rb2 + n1;
-  cd* Db = Pb + n1;
-  cd* Fpb = Db + n1;
-  cd* Fpp = Fpb + n1;
-  cd* Fvb = Fpp + n1;
-  cd* Dm = Fvb + n1;  // output of the idle rows
+  double* hwp = rec + stride;
+  // by coefficient n: the adjoints of v, u_par and u_perp on their way in, then those of
+  // F_v, F_par and F_perp on their way out
+  cd* Av = reinterpret_cast<cd*>(rec + ((stride + 3 * hwp_row(n1) + 1) & ~1));
+  cd* Ap = Av + n1;
+  cd* Au = Ap + n1;
 
   const int mode = blockIdx.x;
   const int i = mode / nzh;
@@ -92,11 +78,12 @@ __global__ void __launch_bounds__(64)
   const double k = sqrt(k2);
   const double ik = mean ? 0.0 : 1.0 / k;
   const double lam = k2 + re * inv_dt;
-  double2 wa[3], wb[3], wc[3];
+  constexpr int NX = (E >= 5) ? 3 : (32 * E + 62) / 64;  // passes over ny <= 32 E - 1
+  double2 wa[NX], wb[NX], wc[NX];
   // packed-Euclidean -> Parseval weights: the (0,0) mode counts twice
   const double wscale = mean ? 2.0 : 1.0;
 #pragma unroll
-  for (int t = 0; t < 3; ++t) {  // clamped loads, masked after (no per-load branches)
+  for (int t = 0; t < NX; ++t) {  // clamped loads, masked after (no per-load branches)
     const int n = tid + 64 * t;
     const int nc = n < n1 ? n : N;
     const double keep = n < n1 ? wscale : 0.0;
@@ -107,18 +94,18 @@ __global__ void __launch_bounds__(64)
     wb[t] = make_double2(wb[t].x * keep, wb[t].y * keep);
     wc[t] = make_double2(wc[t].x * keep, wc[t].y * keep);
   }
-  // mode record and weights (contiguous in LDS: hw = rec + stride) in one round
+  // mode record and weights (contiguous in LDS: hwp = rec + stride) in one round
   // trip: all loads are issued before the first LDS store
   {
     constexpr int RPL = solve_record_loads(E);
     const double* src = modedata + (size_t)mode * stride;
-    const int tot = stride + 3 * n1;
+    const int tot = stride + 3 * hwp_row(n1);
     double rv[RPL];
 #pragma unroll
     for (int q = 0; q < RPL; ++q) {
       const int t = tid + 64 * q;
       const int tc = t < tot ? t : tot - 1;
-      rv[q] = (tc < stride) ? src[tc] : hw_g[tc - stride];
+      rv[q] = (tc < stride) ? src[tc] : hwp_g[tc - stride];
     }
 #pragma unroll
     for (int q = 0; q < RPL; ++q) {
@@ -127,84 +114,115 @@ __global__ void __launch_bounds__(64)
     }
   }
 #pragma unroll
-  for (int t = 0; t < 3; ++t) {
+  for (int t = 0; t < NX; ++t) {
     const int n = tid + 64 * t;
     if (n < n1) {
       const cd ub(wa[t].x, wa[t].y), vb(wb[t].x, wb[t].y), wbv(wc[t].x, wc[t].y);
       if (mean) {
-        Upb[n] = ub;
-        Ub[n] = wbv;
+        Av[n] = ub;
+        Au[n] = wbv;
+        Ap[n] = cd(0.0);
       } else {
-        Upb[n] = (ub * kx + wbv * kz) * ik;
-        Ub[n] = (ub * kz - wbv * kx) * ik;
+        Ap[n] = (ub * kx + wbv * kz) * ik;
+        Au[n] = (ub * kz - wbv * kx) * ik;
+        Av[n] = vb;
       }
-      Vb[n] = vb;
-      Pb[n] = cd(0.0);
-      Fvb[n] = cd(0.0);
-      Fpb[n] = cd(0.0);
-      Fpp[n] = cd(0.0);
     }
   }
   __syncthreads();
   const ModeLayout L{n1};
-  const SweepRec helm(rec + L.helm(), n1, lam);
-  const SweepRec pois(rec + L.pois(), n1, k2);
   const bool vrow = row < 2;
   const int pv = row & 1;  // v parity (rows 0, 1), u_perp / w parity (rows 2, 3)
-  const int po = 1 - pv;
+  // positions n = pv + 2 k of v's (u_perp's) chain and nP = pv - 1 + 2 k of P's (and
+  // u_par's); entries past the chains are zeros
+  cd v[E], P[E], f[E], c[E];
+  const cd* V0 = vrow ? Av : Au;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int n = pv + 2 * (l * E + e);
+    const int nP = n - 1;
+    v[e] = V0[n <= N ? n : N] * mask(n <= N);
+    c[e] = Ap[nP < 0 ? 0 : (nP <= N ? nP : N)] * mask(nP >= 0 && nP <= N);
+  }
+  __syncthreads();  // the result goes into the same arrays
   if (mean) {
-    wsweep_T<E>(helm, hw, N, pv, vrow ? Upb : Ub, vrow ? Rb : Rb2, vrow ? W : W2, l);
-    if (vrow)
-      SP_ROW_PAR(pv, Fpb[n] = -Rb[n];)
-    else
-      SP_ROW_PAR(pv, Fpp[n] = -Rb2[n];)
-  } else {
-    // u_par = i D v / k (transposed): A = conj(i) u_par_bar / k on parity po
-    if (vrow) SP_ROW_PAR(po, A[n] = mul_i(-Upb[n]) * ik;)
-    __syncthreads();
-    wderiv_T<E>(N, po, vrow ? A : Ub, vrow ? Tm : Dm, vrow ? W : W2, l);
-    __syncthreads();
-    if (vrow) SP_ROW_PAR(pv, Vb[n] = Vb[n] + Tm[n];)
-    __syncthreads();
-    // v = v_p + c_delta v_delta + c_b v_b, (c_delta, c_b) = -Minv (l_a, l_b)
-    const double* vdel = rec + L.vdel();
-    const double* vbs = rec + L.vb();
-    cd ca(0.0), cbb(0.0);
-    SP_ROW_PAR(pv, ca = ca + Vb[n] * vdel[n]; cbb = cbb + Vb[n] * vbs[n];)
-    ca = row_sum(ca);
-    cbb = row_sum(cbb);
-    const double* Mi = rec + L.minv() + 4 * pv;
-    const cd la = -(ca * Mi[0] + cbb * Mi[2]);
-    const cd lb = -(ca * Mi[1] + cbb * Mi[3]);
-    const int m = (N % 2 == pv) ? N : N - 1;
-    __syncthreads();
-    if (vrow) {
-      SP_ROW_PAR(pv, Vb[n] = Vb[n] + la * ((double)n * n) + ((n == m) ? lb * lam : cd(0.0));)
-      SP_ROW_PAR(po, if (n == N && m == N - 1) Pb[n] = Pb[n] + lb * (2.0 * N);)
+    rsweep_T<E>(RegSweep<E>(hwp, rec + L.helm(), N, pv, lam, l), v, f);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int n = pv + 2 * (l * E + e);
+      if (n <= N) (vrow ? Ap : Au)[n] = -f[e];
     }
-    __syncthreads();
-    // v_p = H(D P - F_v) on rows 0, 1; u_perp = H(-F_perp) on rows 2, 3
-    wsweep_T<E>(helm, hw, N, pv, vrow ? Vb : Ub, vrow ? Rb : Rb2, vrow ? W : W2, l);
-    if (vrow)
-      SP_ROW_PAR(pv, Fvb[n] = -Rb[n];)
-    else
-      SP_ROW_PAR(pv, Fpp[n] = -Rb2[n];)
-    __syncthreads();
-    wderiv_T<E>(N, pv, vrow ? Rb : Ub, vrow ? Tm : Dm, vrow ? W : W2, l);
-    __syncthreads();
-    if (vrow) SP_ROW_PAR(po, Pb[n] = Pb[n] + Tm[n];)
-    __syncthreads();
-    // P = Pois(div F), div F = i k F_par + D F_v
-    // the rows' operator chosen field by field (a per-lane choice between two
-    // records would be made through scratch memory)
-    const SweepRec pois_or_helm(rec + (vrow ? L.pois() : L.helm()), n1, vrow ? k2 : lam);
-    wsweep_T<E>(pois_or_helm, hw, N, vrow ? po : pv, vrow ? Pb : Ub, vrow ? Db : Dm,
-                vrow ? W : W2, l);
-    if (vrow) SP_ROW_PAR(po, Fpb[n] = mul_i(-Db[n]) * k;)
-    __syncthreads();
-    wderiv_T<E>(N, po, vrow ? Db : Ub, vrow ? Tm : Dm, vrow ? W : W2, l);
-    __syncthreads();
-    if (vrow) SP_ROW_PAR(pv, Fvb[n] = Fvb[n] + Tm[n];)
+  } else {
+    // weights 2 n of D on the two chains (zero outside), and c_0 = 2
+    double dv[E], dP[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int n = pv + 2 * (l * E + e);
+      dv[e] = (n <= N) ? 2.0 * n : 0.0;
+      dP[e] = (n >= 1 && n - 1 <= N) ? 2.0 * (n - 1) : 0.0;
+    }
+    const double halfP = (l == 0 && pv == 1) ? 0.5 : 1.0;  // position 0 of P's chain is n = 0
+    const double halfv = (l == 0 && pv == 0) ? 0.5 : 1.0;  // position 0 of v's chain is n = 0
+    // u_par = i A / k, A = D v
+#pragma unroll
+    for (int e = 0; e < E; ++e) c[e] = mul_i(-c[e]) * ik;
+    c[0] = c[0] * halfP;
+    prefix_sum<E>(c, c);
+    cd vb[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) vb[e] = v[e] + c[e] * dv[e];
+    // v = v_p + c_delta v_delta + c_b v_b, (c_delta, c_b) = -Minv (l_a, l_b)
+    cd ca(0.0), cb(0.0);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int n = pv + 2 * (l * E + e);
+      const int nc = n <= N ? n : N;
+      const double in = mask(n <= N);
+      ca = ca + vb[e] * (rec[L.vdel() + nc] * in);
+      cb = cb + vb[e] * (rec[L.vb() + nc] * in);
+    }
+    ca = row_sum(ca);
+    cb = row_sum(cb);
+    const double* Mi = rec + L.minv() + 4 * pv;
+    const cd la = -(ca * Mi[0] + cb * Mi[2]);
+    const cd lb = -(ca * Mi[1] + cb * Mi[3]);
+    const int m = (N % 2 == pv) ? N : N - 1;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int n = pv + 2 * (l * E + e);
+      vb[e] = vb[e] + la * ((n <= N) ? (double)n * n : 0.0) + lb * ((n == m) ? lam : 0.0);
+      P[e] = lb * ((n - 1 == N && m == N - 1) ? 2.0 * N : 0.0);
+    }
+    // v_p = H(D P - F_v)
+    rsweep_T<E>(RegSweep<E>(hwp, rec + L.helm(), N, pv, lam, l), vb, f);
+    // D P: position k of v's chain took the sum from k + 1 of P's
+    {
+      const cd below = cd_dpp<kDppRowShr | 1>(E == 1 ? f[0] * halfv : f[E - 1]);
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const cd lower = f[e > 0 ? e - 1 : 0];
+        c[e] = pick(e == 0, below, pick(e == 1, lower * halfv, lower));
+      }
+    }
+    prefix_sum<E>(c, c);
+    // P = Pois(div F) on rows 0, 1; u_perp = H(-F_perp) on rows 2, 3
+#pragma unroll
+    for (int e = 0; e < E; ++e) P[e] = pick(vrow, P[e] + c[e] * dP[e], v[e]);
+    rsweep_T<E>(RegSweep<E>(hwp, rec + (vrow ? L.pois() : L.helm()), N, vrow ? pv - 1 : pv,
+                            vrow ? k2 : lam, l),
+                P, v);
+    // div F = i k F_par + D F_v
+#pragma unroll
+    for (int e = 0; e < E; ++e) c[e] = v[e];
+    c[0] = c[0] * halfP;
+    prefix_sum<E>(c, c);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int n = pv + 2 * (l * E + e);
+      const cd Fv = c[e] * dv[e] - f[e];
+      if (n <= N) (vrow ? Av : Au)[n] = pick(vrow, Fv, -v[e]);
+      if (vrow && n >= 1 && n - 1 <= N) Ap[n - 1] = mul_i(-v[e]) * k;
+    }
   }
   __syncthreads();
   // n1 <= 32 E coefficients: a fixed, unrolled pass count
@@ -215,12 +233,12 @@ __global__ void __launch_bounds__(64)
     cd gu, gv, gw;
     if (n <= N - 2) {
       if (mean) {
-        gu = Fpb[n] * re;
-        gw = Fpp[n] * re;
+        gu = Ap[n] * re;
+        gw = Au[n] * re;
       } else {
-        gu = (Fpb[n] * kx + Fpp[n] * kz) * (re * ik);
-        gw = (Fpb[n] * kz - Fpp[n] * kx) * (re * ik);
-        gv = Fvb[n] * re;
+        gu = (Ap[n] * kx + Au[n] * kz) * (re * ik);
+        gw = (Ap[n] * kz - Au[n] * kx) * (re * ik);
+        gv = Av[n] * re;
       }
     }
     out[mo + n] = make_double2(gu.re, gu.im);
@@ -333,17 +351,16 @@ __global__ void __launch_bounds__(256)
 
 // ----------------------------------- launchers -----------------------------------
 
-
 hipError_t launch_stokes_solve_adj(sp_plan* p, const double2* w, double2* out) {
   const Dims& d = p->d;
-  const size_t sh = (size_t)p->mode_stride * sizeof(double) + 3 * (size_t)d.ny * sizeof(double) +
-                    15 * (size_t)d.ny * sizeof(cd);
+  const size_t rec = ((size_t)p->mode_stride + 3 * hwp_row(d.ny) + 1) / 2 * 2;
+  const size_t sh = rec * sizeof(double) + 3 * (size_t)d.ny * sizeof(cd);
   SP_PROF_BEGIN(p, KID_SOLVE_ADJ);
 #define SP_SOLVE_ADJ_LAUNCH(EV)                                                                \
   hipLaunchKernelGGL((k_stokes_solve_adj<EV>), dim3(d.nx * d.nzh), dim3(64), sh, p->stream, w, \
-                     out, p->d_mode, p->d_hw, p->mode_stride, d.nx, d.ny, d.nzh, d.alpha,       \
+                     out, p->d_mode, p->d_hwp, p->mode_stride, d.nx, d.ny, d.nzh, d.alpha,       \
                      d.gamma, d.re, d.inv_dt)
-  switch (solve_lanes_per_chain(d.ny)) {
+  switch (solve_reg_elems(d.ny)) {
     case 1: SP_SOLVE_ADJ_LAUNCH(1); break;
     case 2: SP_SOLVE_ADJ_LAUNCH(2); break;
     case 3: SP_SOLVE_ADJ_LAUNCH(3); break;

@@ -1172,9 +1172,6 @@ hipError_t launch_fft_x_fwd_lds(sp_plan* p, const void* in, void* out, int nfiel
   return hipGetLastError();
 }
 
-// elements per lane of a 16-lane row covering one parity chain (ny <= 129)
-int solve_lanes_per_chain(int ny) { return ((ny - 1) / 2 + 1 + 15) / 16; }
-
 // an: 0 (given right-hand side), 1 (fused analysis, FP64), 2 (FP32)
 static size_t solve_lds_bytes(const sp_plan* p, int an, bool res = false) {
   const int ny = p->d.ny;

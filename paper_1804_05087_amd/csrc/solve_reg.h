@@ -1,4 +1,4 @@
-// Register-resident building blocks of the forward per-mode Chebyshev-tau solve.
+// Register-resident building blocks of the per-mode Chebyshev-tau solve and its adjoint.
 //
 // A parity chain of coefficients lives in the vector registers of one 16-lane
 // row: lane l of the row holds the E consecutive chain positions k = l E + e,
@@ -23,7 +23,8 @@
 // a step) the solve took 6.3 / 8.5 / 13.8 / 95.8 us at 16x17x16, 32x33x32,
 // 48x65x48 and 96x97x96; with the steps in registers it takes 6.1 / 7.6 / 11.9 /
 // 55.2 us: a sweep fell from 2.8 k to 1.7 k cycles, and at ny = 97 the seven LDS
-// arrays no longer needed (11 KB a mode) let more modes share a CU.
+// arrays no longer needed (11 KB a mode) let more modes share a CU. The adjoint solve's
+// steps are these transposed, in reverse order.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -87,6 +88,24 @@ __device__ inline void suffix_sum(const cd (&c)[E], cd (&s)[E]) {
   }
 }
 
+// s_k = sum of c over the positions k' <= k of the row.
+template <int E>
+__device__ inline void prefix_sum(const cd (&c)[E], cd (&s)[E]) {
+  cd t = c[0];
+#pragma unroll
+  for (int e = 1; e < E; ++e) t = t + c[e];
+  t = t + cd_dpp<kDppRowShr | 1>(t);
+  t = t + cd_dpp<kDppRowShr | 2>(t);
+  t = t + cd_dpp<kDppRowShr | 4>(t);
+  t = t + cd_dpp<kDppRowShr | 8>(t);
+  cd x = cd_dpp<kDppRowShr | 1>(t);  // of all lower lanes (zero in lane 0)
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    x = c[e] + x;
+    s[e] = x;
+  }
+}
+
 // g with (D^2 - lam) g = r on the chain (rows 0..N-2) and sum g_n = beta:
 // sweep_solve's two recurrences (solve_core.h) on registers.
 template <int E>
@@ -113,6 +132,46 @@ __device__ inline void rsweep(const RegSweep<E>& f, const cd (&r)[E], cd beta, c
   const cd g0 = (beta - s) * f.inv_sum;
 #pragma unroll
   for (int e = 0; e < E; ++e) g[e] = a[e] + g0 * f.Q[e];  // Q = 1 at the first position
+}
+
+// rsweep transposed (beta = 0): r = its adjoint of the right-hand side from the adjoint g
+// of the solution, which is zero past the chain.
+template <int E>
+__device__ inline void rsweep_T(const RegSweep<E>& f, const cd (&g)[E], cd (&r)[E]) {
+  cd s = g[0] * f.Q[0];
+#pragma unroll
+  for (int e = 1; e < E; ++e) s = s + g[e] * f.Q[e];
+  s = row_sum(s) * (-f.inv_sum);
+  cd a[E], x[E];
+  double b[E];
+  // the forward pass transposed: x_k = (g_k + s) + q_{k+1} x_{k+1}
+  const double qn = dpp_mov<kDppRowShl | 1>(f.lam * f.w1[0] * f.id[0], 0.0);
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    a[e] = g[e] + s;
+    const int u = e < E - 1 ? e + 1 : 0;
+    b[e] = (e == E - 1) ? qn : f.lam * f.w1[u] * f.id[u];
+  }
+  rec_down<E>(a, b, cd(0.0), x);
+  // the back substitution transposed: a_k = x_k + (-cc / den)_{k-1} a_{k-1}
+  const double cp = dpp_mov<kDppRowShr | 1>(f.lam * f.w3[E - 1] * f.id[E - 1], 0.0);
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int u = e > 0 ? e - 1 : 0;
+    b[e] = (e == 0) ? cp : f.lam * f.w3[u] * f.id[u];
+  }
+  rec_up<E>(x, b, cd(0.0), a);
+  // the right-hand side's combination transposed
+#pragma unroll
+  for (int e = 0; e < E; ++e) a[e] = a[e] * f.id[e];
+  const cd up = cd_dpp<kDppRowShl | 1>(a[0] * f.w1[0]);
+  const cd dn = cd_dpp<kDppRowShr | 1>(a[E - 1] * f.w3[E - 1]);
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int u = e < E - 1 ? e + 1 : 0, v = e > 0 ? e - 1 : 0;
+    r[e] = a[e] * f.w2[e] + pick(e == E - 1, up, a[u] * f.w1[u]) +
+           pick(e == 0, dn, a[v] * f.w3[v]);
+  }
 }
 
 }  // namespace sp

@@ -32,9 +32,9 @@ struct ModeLayout {
 };
 
 // Doubles each of the 64 lanes of the per-mode solve kernels loads to stage one
-// mode record and the three weight rows (stride + 3 ny = 9 ny + 12 values),
-// for E elements per lane and parity chain: enough up to ny = 32 E, the
-// largest (even) ny with E elements per lane.
+// mode record and the three padded weight rows (stride + 3 (ny + 2) = 9 ny + 18
+// values), for E elements per lane and parity chain: enough up to ny = 32 E - 1,
+// the largest ny with E elements per lane.
 __host__ __device__ constexpr int solve_record_loads(int E) { return (288 * E + 12 + 63) / 64; }
 
 struct FFTPlan1D {
@@ -153,8 +153,7 @@ struct sp_plan {
   double* d_TD = nullptr;     // [ny][ny] T . D (values of d/dy)
   double* d_Tinv = nullptr;   // [ny][ny] analysis
   double* d_G = nullptr;      // [ny][ny] Gram matrix int T_n T_m
-  double* d_hw = nullptr;     // [3][ny] Helmholtz right-hand-side weights
-  double* d_hwp = nullptr;    // the same zero padded, [3][ny + 2] (solve_reg.h)
+  double* d_hwp = nullptr;    // Helmholtz right-hand-side weights, zero padded, [3][ny + 2]
   double* d_mode = nullptr;   // per-mode solve records
   int mode_stride = 0;
   double2* d_twx = nullptr;   // [px] exp(-2 pi i k / px)
@@ -245,8 +244,6 @@ size_t noalloc_bytes_needed(const Dims& d);
 sp_status set_error(sp_plan* p, sp_status s, const std::string& msg);
 sp_status hip_check(sp_plan* p, hipError_t e, const char* what);
 sp_status build_mode_data(sp_plan* p);
-// elements per lane of a 16-lane row covering one parity chain (kernels.hip)
-int solve_lanes_per_chain(int ny);
 
 // kernel launchers (kernels.hip); all enqueue on p->stream
 hipError_t launch_synth_y(sp_plan* p, const double2* u, bool fp32);
