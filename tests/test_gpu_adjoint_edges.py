@@ -33,3 +33,22 @@ def test_vjp_at_the_edges(ny):
     P.linearize(to_dev(u))
     for op, name in ((SP_OP_PHI, "phi"), (SP_OP_RESIDUAL, "residual")):
         assert rel(to_np(P.vjp_lin(to_dev(w), op)), B.vjp(u, w, name)) < tol
+
+
+def test_gradient_of_an_argument_changed_after_the_forward_pass():
+    """The backward pass works on the state of the forward pass, bit for bit."""
+    import torch
+    from paper_1804_05087_amd import PhiFunction, Plan
+    dims, re, dt = (8, 9, 8), 400.0, 10.0
+    P = Plan(*dims, *BOX, re, dt)
+    x0 = P.pack(to_dev(synth.perturbation_field(*dims, *BOX, seed=1)))
+    gy = P.pack(to_dev(synth.random_spectral(*dims, seed=2)))
+    grads = []
+    for change in (False, True):
+        x = x0.clone().requires_grad_(True)
+        y = PhiFunction.apply(x, P)
+        if change:
+            with torch.no_grad():
+                x.mul_(2.0)
+        grads.append(torch.autograd.grad(y, x, gy)[0])
+    assert torch.equal(*grads)
