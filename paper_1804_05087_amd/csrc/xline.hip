@@ -37,6 +37,19 @@ __device__ inline XBlk xline_block(int ny) {
   return XBlk{member, my - member * ny, l % gf, (l / gf) % gc};
 }
 
+// Modes per block of the FP64 inverse transform (128 threads): a thread takes one column
+// of step 1 and at most xinv_passes columns of step 2, since the columns stay in registers
+// while their real parts, then their imaginary ones, go through LDS. Bound by how many
+// waves hide the chains of the transforms: with half the LDS a CU holds eight blocks
+// instead of five, and the six fields take 27.1 us instead of 34.7 at 96x97x96, 25.9
+// instead of 33.5 at 128x49x128, 11.0 as before at 72x49x72. FP32 lines are half as long
+// in LDS already and keep the exchange in one piece.
+__host__ __device__ constexpr int xinv_passes(int P1, int P2) { return 2 * P1 > 3 * P2 ? 2 : 1; }
+constexpr int xinv_max_modes(int P1, int P2) {
+  const int a = 128 / P2, b = 128 * xinv_passes(P1, P2) / P1;
+  return a < b ? a : b;
+}
+
 // plain == 0: output field f of (u, v, w, omega_x, omega_y, omega_z) from the
 // five y-valued fields (u, du/dy, v, w, dw/dy) with i k_x, i k_z; plain != 0:
 // output field f is input field f.
@@ -50,7 +63,6 @@ __global__ void __launch_bounds__(128)
   constexpr int S1 = P1 + 1;
   extern __shared__ unsigned char smem_raw[];
   C* twl = reinterpret_cast<C*>(smem_raw);
-  C* ex = twl + P;  // [kc][P2][S1]
   const XBlk bk = xline_block<MB>(ny);
   if constexpr (MB) {
     yv += bk.member * mi;
@@ -64,62 +76,109 @@ __global__ void __launch_bounds__(128)
   __syncthreads();
   const size_t fs = (size_t)ny * nzm * nx;
   const int h = nx / 2;
-  // step 1: task (l, n2), values at padded positions pos = P2 n1 + n2
-  for (int task = threadIdx.x; task < kc * P2; task += blockDim.x) {
-    const int l = task / P2;
-    const int n2 = task - l * P2;
-    if (l < nl) {
-      const int kz = kz0 + l;
-      const C* src = yv + ((size_t)y * nzm + kz) * nx;
-      const R kzv = gamma * (R)kz;
-      C v[P1];
-#pragma unroll
-      for (int n1 = 0; n1 < P1; ++n1) {
-        const int pos = P2 * n1 + n2;
-        const bool lo = pos < h;
-        const bool hi = pos > P - h;
-        const int i = lo ? pos : (hi ? pos - P + nx : 0);
-        const R keep = (lo || hi) ? (R)1 : (R)0;
-        const R kxv = alpha * (R)(lo ? i : i - nx);
-        C val;
-        if (plain) {
-          val = src[f * fs + i];
-        } else if (f == 0) {
-          val = src[i];
-        } else if (f == 1) {
-          val = src[2 * fs + i];
-        } else if (f == 2) {
-          val = src[3 * fs + i];
-        } else if (f == 3) {  // dw/dy - i kz v
-          val = csub(src[4 * fs + i], sidot(cscale(src[2 * fs + i], kzv), (R)1));
-        } else if (f == 4) {  // i kz u - i kx w
-          val = sidot(csub(cscale(src[i], kzv), cscale(src[3 * fs + i], kxv)), (R)1);
-        } else {  // i kx v - du/dy
-          val = csub(sidot(cscale(src[2 * fs + i], kxv), (R)1), src[fs + i]);
-        }
-        v[n1] = cscale(val, keep);
-      }
-      dft_reg<P1, P, C, R>(v, (R)1, twl);
-      C* e = ex + (l * P2 + n2) * S1;
-#pragma unroll
-      for (int k1 = 0; k1 < P1; ++k1)
-        e[k1] = (k1 == 0 || n2 == 0) ? v[k1] : cmul(v[k1], wpow<P, P, C, R>(n2 * k1, (R)1, twl));
-    }
-  }
-  __syncthreads();
-  // step 2: task (k1, l), physical points x = k1 + P1 k2
+  // step 1: task (l, n2), values at padded positions pos = P2 n1 + n2; then the exchange
+  // and step 2: task (k1, l), physical points x = k1 + P1 k2
   C* dst = xp + ((size_t)f * ny + y) * P * nzm + kz0;
-  for (int task = threadIdx.x; task < P1 * kc; task += blockDim.x) {
-    const int k1 = task / kc;
-    const int l = task - k1 * kc;
-    if (l < nl) {
-      C t[P2];
-      const C* e = ex + l * P2 * S1 + k1;
+  auto step1 = [&](int l, int n2, C(&v)[P1]) {
+    const int kz = kz0 + l;
+    const C* src = yv + ((size_t)y * nzm + kz) * nx;
+    const R kzv = gamma * (R)kz;
 #pragma unroll
-      for (int n2 = 0; n2 < P2; ++n2) t[n2] = e[n2 * S1];
-      dft_reg<P2, P, C, R>(t, (R)1, twl);
+    for (int n1 = 0; n1 < P1; ++n1) {
+      const int pos = P2 * n1 + n2;
+      const bool lo = pos < h;
+      const bool hi = pos > P - h;
+      const int i = lo ? pos : (hi ? pos - P + nx : 0);
+      const R keep = (lo || hi) ? (R)1 : (R)0;
+      const R kxv = alpha * (R)(lo ? i : i - nx);
+      C val;
+      if (plain) {
+        val = src[f * fs + i];
+      } else if (f == 0) {
+        val = src[i];
+      } else if (f == 1) {
+        val = src[2 * fs + i];
+      } else if (f == 2) {
+        val = src[3 * fs + i];
+      } else if (f == 3) {  // dw/dy - i kz v
+        val = csub(src[4 * fs + i], sidot(cscale(src[2 * fs + i], kzv), (R)1));
+      } else if (f == 4) {  // i kz u - i kx w
+        val = sidot(csub(cscale(src[i], kzv), cscale(src[3 * fs + i], kxv)), (R)1);
+      } else {  // i kx v - du/dy
+        val = csub(sidot(cscale(src[2 * fs + i], kxv), (R)1), src[fs + i]);
+      }
+      v[n1] = cscale(val, keep);
+    }
+    dft_reg<P1, P, C, R>(v, (R)1, twl);
 #pragma unroll
-      for (int k2 = 0; k2 < P2; ++k2) dst[(size_t)(k1 + P1 * k2) * nzm + l] = t[k2];
+    for (int k1 = 1; k1 < P1; ++k1)
+      if (n2 != 0) v[k1] = cmul(v[k1], wpow<P, P, C, R>(n2 * k1, (R)1, twl));
+  };
+  auto step2 = [&](int k1, int l, C(&t)[P2]) {
+    dft_reg<P2, P, C, R>(t, (R)1, twl);
+#pragma unroll
+    for (int k2 = 0; k2 < P2; ++k2) dst[(size_t)(k1 + P1 * k2) * nzm + l] = t[k2];
+  };
+  if constexpr (sizeof(R) == 8) {
+    R* ex = reinterpret_cast<R*>(twl + P);  // [kc][P2][S1]
+    constexpr int NP = xinv_passes(P1, P2);
+    const int l1 = threadIdx.x / P2;
+    const int n2 = threadIdx.x - l1 * P2;
+    const bool act = l1 < kc && l1 < nl;  // kc P2 <= 128: one task a thread
+    C v[P1], t[NP][P2];
+    if (act) step1(l1, n2, v);
+#pragma unroll
+    for (int part = 0; part < 2; ++part) {
+      if (part) __syncthreads();
+      if (act) {
+        R* e = ex + (l1 * P2 + n2) * S1;
+#pragma unroll
+        for (int k1 = 0; k1 < P1; ++k1) e[k1] = part ? v[k1].y : v[k1].x;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < NP; ++q) {
+        const int task = threadIdx.x + 128 * q;
+        const int k1 = task / kc;
+        const int l = task - k1 * kc;
+        if (k1 < P1 && l < nl) {
+          const R* e = ex + l * P2 * S1 + k1;
+#pragma unroll
+          for (int m = 0; m < P2; ++m) (part ? t[q][m].y : t[q][m].x) = e[m * S1];
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const int task = threadIdx.x + 128 * q;
+      const int k1 = task / kc;
+      const int l = task - k1 * kc;
+      if (k1 < P1 && l < nl) step2(k1, l, t[q]);
+    }
+  } else {
+    C* ex = twl + P;  // [kc][P2][S1]
+    for (int task = threadIdx.x; task < kc * P2; task += blockDim.x) {
+      const int l = task / P2;
+      const int n2 = task - l * P2;
+      if (l < nl) {
+        C v[P1];
+        step1(l, n2, v);
+        C* e = ex + (l * P2 + n2) * S1;
+#pragma unroll
+        for (int k1 = 0; k1 < P1; ++k1) e[k1] = v[k1];
+      }
+    }
+    __syncthreads();
+    for (int task = threadIdx.x; task < P1 * kc; task += blockDim.x) {
+      const int k1 = task / kc;
+      const int l = task - k1 * kc;
+      if (l < nl) {
+        C t[P2];
+        const C* e = ex + l * P2 * S1 + k1;
+#pragma unroll
+        for (int n2 = 0; n2 < P2; ++n2) t[n2] = e[n2 * S1];
+        step2(k1, l, t);
+      }
     }
   }
 }
@@ -221,27 +280,29 @@ hipError_t launch_fft_x_fwd_lds(sp_plan* p, const void* in, void* out, int nfiel
 
 // z-modes per block: the fewest chunks that give the grid at least 512 blocks
 // (and at least 4 modes per chunk) and keep the exchange buffer within 32 KiB (16 in
-// FP32) of LDS, split evenly; a chunk is widened to a whole number of 128-byte cache
-// lines (8 FP64 or 16 FP32 complex values) when that keeps the same even split,
-// so that chunks of the x-physical rows [x][kz] start on line boundaries. The LDS
-// bound leaves a CU five blocks of two waves; with 64 KiB it had two, and the long
-// lines waited: inverse, forward at 96x97x96 56.8, 18.4 us (64 KiB), 34.9, 11.8 (32),
-// 43.5, 12.1 (24), 61.6, 13.5 (16); 128x49x128 54.7, 17.2 / 33.6, 11.0 / 42.2, 12.3 / 49.5,
-// 12.0; FP32 inverse at 72x49x72 12.8 us (32 and 64 KiB), 8.9 (16).
-static int xline_chunk(const Dims& d, int nb, int nfields, bool fp32, int P1, int P2) {
+// FP32) of LDS or, exchanged in halves, within xinv_max_modes, split evenly; a chunk is
+// widened to a whole number of 128-byte cache lines (8 FP64 or 16 FP32 complex values)
+// when that keeps the same even split, so that chunks of the x-physical rows [x][kz]
+// start on line boundaries. The LDS bound leaves a CU five blocks of two waves; with
+// 64 KiB it had two, and the long lines waited: forward at 96x97x96 18.4 us (64 KiB),
+// 11.8 (32), 12.1 (24), 13.5 (16); 128x49x128 17.2 / 11.0 / 12.3 / 12.0; FP32 inverse at
+// 72x49x72 12.8 us (32 and 64 KiB), 8.9 (16).
+static int xline_chunk(const Dims& d, int nb, int nfields, bool fp32, int P1, int P2,
+                       bool halves = false) {
   const int lw = fp32 ? 16 : 8;
   const size_t el = fp32 ? sizeof(float2) : sizeof(double2);
   const long per = (long)d.ny * nfields * nb;
   const int nmax = d.nzm / 4 > 1 ? d.nzm / 4 : 1;
-  auto lds = [&](int kc) { return ((size_t)d.px + (size_t)kc * P2 * (P1 + 1)) * el; };
-  const size_t cap = fp32 ? 16384 : 32768;
+  const int most = halves ? xinv_max_modes(P1, P2) : d.nzm;
+  auto over = [&](int kc) {
+    return kc > most ||
+           (!halves && ((size_t)d.px + (size_t)kc * P2 * (P1 + 1)) * el > (fp32 ? 16384 : 32768));
+  };
   int nch = 1;
-  while (nch < d.nzm &&
-         ((nch < nmax && per * nch < 512) || lds((d.nzm + nch - 1) / nch) > cap))
-    ++nch;
+  while (nch < d.nzm && ((nch < nmax && per * nch < 512) || over((d.nzm + nch - 1) / nch))) ++nch;
   int kc = (d.nzm + nch - 1) / nch;
   const int ka = (kc + lw - 1) / lw * lw;
-  if (d.nzm % ka == 0 && d.nzm / ka == nch) kc = ka;
+  if (d.nzm % ka == 0 && d.nzm / ka == nch && ka <= most) kc = ka;
   return kc;
 }
 
@@ -251,10 +312,10 @@ hipError_t launch_fft_x_inv_gen(sp_plan* p, const void* in, void* out, int nfiel
   const int P1 = reg_fft_split(d.px, fp32);
   if (P1 == 0) return launch_fft_x_inv_lds(p, in, out, nfields, plain, fp32);
   const int P2 = d.px / P1;
-  const int kc = xline_chunk(d, p->mem.nb, nfields, fp32, P1, P2);
+  const int kc = xline_chunk(d, p->mem.nb, nfields, fp32, P1, P2, !fp32);
   const dim3 grid(d.ny * p->mem.nb, nfields, (d.nzm + kc - 1) / kc);
-  const size_t el = fp32 ? sizeof(float2) : sizeof(double2);
-  const size_t sh = ((size_t)d.px + (size_t)kc * P2 * (P1 + 1)) * el;
+  const size_t ex = (size_t)kc * P2 * (P1 + 1);
+  const size_t sh = fp32 ? (d.px + ex) * sizeof(float2) : d.px * sizeof(double2) + ex * sizeof(double);
   SP_PROF_BEGIN(p, KID_FFT_X_INV);
 #define XI32(A, B)                                                                              \
   hipLaunchKernelGGL((k_xinv_reg<float, A, B, MB>), grid, dim3(128), sh, p->stream,             \
