@@ -96,6 +96,18 @@ struct ZLineMap {
   int fout_a[3], fout_b[3];
 };
 
+// x-lines per block of length P: eight, but four past 72 points, where eight take 59 KB
+// of LDS or more and leave a CU one or two blocks. Measured (separate inverse x
+// transform): 60.4 us against 40.2 with four at P = 144 (96x97x96), 18.0 against 17.5 at
+// 108, 9.5 against 8.6 at 81, 8.3 against 8.6 at 54.
+constexpr int zline_lines(int P) { return P > 72 ? 4 : 8; }
+
+// Threads of a block: 128 for four lines of 73 to 144 points, whose stages have 64 to 192
+// tasks, so that two of four waves would only hold registers (three waves a SIMD at 144
+// points): 38.2, 34.9, 33.7 us with 256, 192, 128 threads at 96x97x96, 15.6, 14.8, 13.6
+// at 72x49x72. Longer lines have up to 256 tasks a stage.
+constexpr int zline_threads(int P, bool xf) { return !xf && P > 72 && P <= 144 ? 128 : 256; }
+
 // XF: in = y-valued fields [f][y][kz][mx]: for Op::kXIn == 5 the five fields
 // (u, du/dy, v, w, dw/dy), from which the six curl-combined fields of the
 // x-lines are formed (the line map pairs fields (0, 1), (2, 3), (4, 5)); for
@@ -112,7 +124,7 @@ struct ZLineMap {
 // (first: out = prev = h).
 template <typename R, int P1, int P2, int XL, class Op, bool XF = false, bool XFO = false,
           bool SB = false>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(zline_threads(P1* P2, XF))
     k_zline(const typename V2<R>::T* in, typename V2<R>::T* out,
             R* __restrict__ base, const typename V2<R>::T* __restrict__ tw, ZLineMap map, int ny,
             int px, int nzm, R scale, const typename V2<R>::T* __restrict__ twx = nullptr,
@@ -123,21 +135,32 @@ __global__ void __launch_bounds__(256)
   constexpr int NI = Op::NI;
   constexpr int NF = Op::NF;
   constexpr int S1 = P1 + 1;  // padded row of the exchange buffers
-  // operators with a base state and no more output than input lines take the
-  // pointwise stage one physical point per task, writing the products in place
-  // over their input slots (the others keep one task per (line, k1), which
-  // for base-state operators reads the base once per point)
-  constexpr bool kSplit = Op::kBase && NF > 0 && NF <= NI;
-  constexpr int LS = NI;  // line slots per x-line in the exchange block
+  // the forward transforms in place of the inverse ones: a task each, held in registers
+  // over a barrier, so that no second exchange buffer is needed and a CU holds more
+  // blocks (40.9 -> 30.9 us at 128x49x128). With XF the x-physical lines take its place
+  // all the same, but for the adjoint, where three lines follow two.
+  constexpr int NTH = zline_threads(P1 * P2, XF);
+  constexpr bool IP = NF > 0 && (!XF || NF > NI) && XL * NF * P2 <= NTH &&
+                      (Op::kBase || XL * P1 * NF <= NTH);
+  constexpr int LS = IP && NF > NI ? NF : NI;  // line slots per x-line in the exchange block
+  // operators with a base state take the pointwise stage one physical point per
+  // task where the products fit the line slots, writing them in place over their
+  // input slots (the others keep one task per (line, k1), which for base-state
+  // operators reads the base once per point). The adjoint held three lines in registers
+  // in that form, one or two waves a SIMD: 18.2 -> 13.8 us at 48x65x48 and, with the
+  // transforms in place, 68 -> 55 at 96x97x96, 92 -> 49 at 128x49x128.
+  constexpr bool kSplit = Op::kBase && NF > 0 && NF <= LS;
+  constexpr int LF = IP ? LS : NF;  // of the forward exchange
   constexpr int E1 = (XL * LS * P2 * S1 > XL * NF * P) ? XL * LS * P2 * S1 : XL * NF * P;
   constexpr int NXF = Op::kXIn == 5 ? 6 : Op::kXIn;  // x-physical fields formed by XF
-  constexpr int E2F = NF > 0 ? XL * NF * P2 * S1 : 1;
+  constexpr int E2F = NF > 0 && !IP ? XL * NF * P2 * S1 : 1;
   constexpr int E2X = XF ? XL * NXF * (P / 3) : 1;
   static_assert(!XF || (XL == 8 && 2 * NI >= NXF && E1 >= NXF * (P / 3) * (XL + 1)),
                 "XF: eight lines of packed pairs; partial sums fit the exchange block");
   __shared__ C twl[P];
   __shared__ C ex1[E1];  // inverse exchange, then forward output (XF: first the partial sums)
   __shared__ C ex2[E2F > E2X ? E2F : E2X];  // forward exchange (XF: first the x-physical lines)
+  C* const fx = IP ? ex1 : ex2;
   const int tid = threadIdx.x;
   int y, x0, xq, nxl;  // line xl of the block is x = x0 + xq * xl
   {
@@ -164,7 +187,7 @@ __global__ void __launch_bounds__(256)
   const size_t fs = (size_t)ny * px * nzk;
   // offset of line xl in a field of the x-physical layout (in units of nzm)
   auto line_of = [&](int xl) { return (size_t)y * px + x0 + (size_t)xq * xl; };
-  for (int t = tid; t < P; t += 256) twl[t] = tw[t];
+  for (int t = tid; t < P; t += NTH) twl[t] = tw[t];
   if constexpr (XF) {
     // Partial sums g_r of the NXF x-line fields: task (kz, r), over the kept
     // padded positions m = r mod XL. With nx a multiple of 16 these are, for
@@ -180,7 +203,7 @@ __global__ void __launch_bounds__(256)
     const int h = nx / 2;
     const int h8 = nx / (2 * XL);
     const int dq = (XL * x0) % px;  // step of the twiddle index m a mod px per t
-    for (int task = tid; task < nzk * XL; task += 256) {
+    for (int task = tid; task < nzk * XL; task += NTH) {
       const int r = task % XL;
       const int kz = task / XL;
       const C* src = in + ((size_t)y * nzk + kz) * nx;
@@ -231,7 +254,7 @@ __global__ void __launch_bounds__(256)
     __syncthreads();
     // XL-point inverse DFT over r: task (field, kz) -> the block's XL lines
     C* xs = ex2;  // [XL][NXF][nzm]
-    for (int task = tid; task < NXF * nzk; task += 256) {
+    for (int task = tid; task < NXF * nzk; task += NTH) {
       const int kz = task % nzk;
       const int f = task / nzk;
       C v[XL];
@@ -245,7 +268,7 @@ __global__ void __launch_bounds__(256)
   __syncthreads();
 
   // step 1 of the inverse transforms: task (xl, line i, n2)
-  for (int task = tid; task < XL * NI * P2; task += 256) {
+  for (int task = tid; task < XL * NI * P2; task += NTH) {
     const int n2 = task % P2;
     const int li = task / P2;  // xl * NI + i
     const int i = li % NI;
@@ -266,11 +289,16 @@ __global__ void __launch_bounds__(256)
       C v[P1];
 #pragma unroll
       for (int n1 = 0; n1 < P1; ++n1) {
+        // Hermitian extension: m < nzm direct, m > P - nzm mirrored, else zero; masks
+        // multiply loaded values so the loads stay unconditional, but for the n1 whose
+        // every m is one of the zeros
+        if (P2 * n1 >= P / 3 && P2 * n1 + P2 - 1 <= P - P / 3) {
+          v[n1] = mk((R)0, (R)0);
+          continue;
+        }
         const int m = P2 * n1 + n2;
-        // Hermitian extension: m < nzm direct, m > P - nzm mirrored, else zero;
-        // masks multiply loaded values so the loads stay unconditional
-        const bool lo_half = m < nzk;
-        const bool hi_half = m > P - nzk;
+        const bool lo_half = P2 * n1 + P2 <= P / 3 || m < nzk;
+        const bool hi_half = P2 * n1 > P - P / 3 || m > P - nzk;
         const int mm = lo_half ? m : (hi_half ? P - m : 0);
         const C a = fa[mm];
         const C b = fbp[mm];
@@ -292,7 +320,7 @@ __global__ void __launch_bounds__(256)
   // step 2 of the inverse transforms, in place: task (xl, line i, k1); column
   // k1 of the exchange block then holds the physical points z = k1 + P1 k2
   const size_t bs = (size_t)ny * px * P;
-  for (int task = tid; task < XL * NI * P1; task += 256) {
+  for (int task = tid; task < XL * NI * P1; task += NTH) {
     const int k1 = task % P1;
     const int li = task / P1;  // xl * NI + i
     const int xl = li / NI;
@@ -324,7 +352,7 @@ __global__ void __launch_bounds__(256)
     // physical point z = k1 + P1 k2 each, so that every wave reads base values
     // (consecutive tasks read consecutive z); the products go in place over the
     // point's input slots (slot f < NF of the x-line's LS slots)
-    for (int task = tid; task < XL * P1 * P2; task += 256) {
+    for (int task = tid; task < XL * P1 * P2; task += NTH) {
       const int k1 = task % P1;
       const int k2 = (task / P1) % P2;
       const int xl = task / (P1 * P2);
@@ -340,7 +368,7 @@ __global__ void __launch_bounds__(256)
     }
     __syncthreads();
     // step 1 of the forward transforms: task (xl, k1, forward line f), f slowest
-    for (int task = tid; task < XL * P1 * NF; task += 256) {
+    for (int task = tid; task < XL * P1 * NF; task += NTH) {
       const int f = task / (XL * P1);
       const int k1 = task % P1;
       const int xl = (task / P1) % XL;
@@ -349,7 +377,7 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
         for (int k2 = 0; k2 < P2; ++k2) fw[k2] = ex1[((xl * LS + f) * P2 + k2) * S1 + k1];
         dft_reg<P2, P, C, R>(fw, (R)-1, twl);
-        C* e = ex2 + ((xl * NF + f) * P2) * S1 + k1;
+        C* e = fx + ((xl * LF + f) * P2) * S1 + k1;
 #pragma unroll
         for (int m2 = 0; m2 < P2; ++m2)
           e[m2 * S1] = (m2 == 0 || k1 == 0) ? fw[m2]
@@ -364,48 +392,61 @@ __global__ void __launch_bounds__(256)
     // XL * P1 a multiple of 64 it is uniform over a wave), else (xl, k1) with
     // every f in one task, so the base state is read once per point
     constexpr int NFT = Op::kBase ? 1 : NF;  // forward lines per task split
-    for (int task = tid; task < XL * P1 * NFT; task += 256) {
-      const int fsel = task / (XL * P1);
-      const int k1 = task % P1;
-      const int xl = (task / P1) % XL;
-      if (xl < nxl) {
-        const size_t bo0 = line_of(xl) * P + k1;
-        // forward lines F0 .. F0 + NFL - 1 (compile-time, so pout stays in registers)
-        auto run = [&](auto f0) {
-          constexpr int F0 = decltype(f0)::value;
-          constexpr int NFL = Op::kBase ? NF : 1;
+    constexpr int NFL = NF / NFT;            // forward lines of a task
+    // lines F0 .. F0 + NFL - 1 (compile-time, so pout stays in registers)
+    auto products = [&](auto f0, int xl, int k1, C(&fw)[NFL][P2]) {
+      constexpr int F0 = decltype(f0)::value;
+      const size_t bo0 = line_of(xl) * P + k1;
+      const Op op{};
+#pragma unroll
+      for (int k2 = 0; k2 < P2; ++k2) {
+        C pin[NI], pout[NF];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) pin[i] = ex1[((xl * LS + i) * P2 + k2) * S1 + k1];
+        op(pin, pout, base, bs, bo0 + (size_t)P1 * k2);
+#pragma unroll
+        for (int q = 0; q < NFL; ++q) fw[q][k2] = pout[F0 + q];
+      }
+#pragma unroll
+      for (int q = 0; q < NFL; ++q) {
+        dft_reg<P2, P, C, R>(fw[q], (R)-1, twl);
+#pragma unroll
+        for (int m2 = 1; m2 < P2; ++m2)
+          if (k1 != 0) fw[q][m2] = cmul(fw[q][m2], wpow<P, P, C, R>(k1 * m2, (R)-1, twl));
+      }
+    };
+    auto load = [&](int fsel, int xl, int k1, C(&fw)[NFL][P2]) {
+      if (NFT == 1 || fsel == 0) products(std::integral_constant<int, 0>{}, xl, k1, fw);
+      if constexpr (NFT > 1) {
+        if (fsel == 1) products(std::integral_constant<int, 1>{}, xl, k1, fw);
+      }
+      if constexpr (NFT > 2) {
+        if (fsel == 2) products(std::integral_constant<int, 2>{}, xl, k1, fw);
+      }
+    };
+    auto store = [&](int fsel, int xl, int k1, const C(&fw)[NFL][P2]) {
+#pragma unroll
+      for (int q = 0; q < NFL; ++q) {
+        C* e = fx + ((xl * LF + (NFL > 1 ? q : fsel)) * P2) * S1 + k1;
+#pragma unroll
+        for (int m2 = 0; m2 < P2; ++m2) e[m2 * S1] = fw[q][m2];
+      }
+    };
+    constexpr int NT = XL * P1 * NFT;
+    if constexpr (IP) {
+      const int k1 = tid % P1, xl = (tid / P1) % XL, fsel = tid / (XL * P1);
+      const bool act = tid < NT && xl < nxl;
+      C fw[NFL][P2];
+      if (act) load(fsel, xl, k1, fw);
+      if constexpr (NFT > 1) __syncthreads();  // (a task of every line owns its column)
+      if (act) store(fsel, xl, k1, fw);
+    } else {
+      for (int task = tid; task < NT; task += NTH) {
+        const int k1 = task % P1, xl = (task / P1) % XL, fsel = task / (XL * P1);
+        if (xl < nxl) {
           C fw[NFL][P2];
-          const Op op{};
-#pragma unroll
-          for (int k2 = 0; k2 < P2; ++k2) {
-            C pin[NI], pout[NF];
-#pragma unroll
-            for (int i = 0; i < NI; ++i) pin[i] = ex1[((xl * NI + i) * P2 + k2) * S1 + k1];
-            op(pin, pout, base, bs, bo0 + (size_t)P1 * k2);
-#pragma unroll
-            for (int q = 0; q < NFL; ++q) fw[q][k2] = pout[F0 + q];
-          }
-#pragma unroll
-          for (int q = 0; q < NFL; ++q) {
-            dft_reg<P2, P, C, R>(fw[q], (R)-1, twl);
-            C* e = ex2 + ((xl * NF + F0 + q) * P2) * S1 + k1;
-#pragma unroll
-            for (int m2 = 0; m2 < P2; ++m2)
-              e[m2 * S1] = (m2 == 0 || k1 == 0)
-                               ? fw[q][m2]
-                               : cmul(fw[q][m2], wpow<P, P, C, R>(k1 * m2, (R)-1, twl));
-          }
-        };
-        if constexpr (Op::kBase) {
-          run(std::integral_constant<int, 0>{});
-        } else {
-          if (fsel == 0) run(std::integral_constant<int, 0>{});
-          if constexpr (NF > 1) {
-            if (fsel == 1) run(std::integral_constant<int, 1>{});
-          }
-          if constexpr (NF > 2) {
-            if (fsel == 2) run(std::integral_constant<int, 2>{});
-          }
+          load(fsel, xl, k1, fw);
+          store(fsel, xl, k1, fw);
         }
       }
     }
@@ -413,26 +454,40 @@ __global__ void __launch_bounds__(256)
   if constexpr (NF > 0) {
     __syncthreads();
     // step 2 of the forward transforms: task (xl, line f, m2), outputs m = P2 m1 + m2
-    for (int task = tid; task < XL * NF * P2; task += 256) {
-      const int m2 = task % P2;
-      const int lf = task / P2;
+    auto load = [&](int lf, int m2, C(&v)[P1]) {
       const int xl = lf / NF;
-      if (xl < nxl) {
-        const C* e = ex2 + (lf * P2 + m2) * S1;
-        C v[P1];
+      const C* e = fx + ((xl * LF + lf - xl * NF) * P2 + m2) * S1;
 #pragma unroll
-        for (int n1 = 0; n1 < P1; ++n1) v[n1] = e[n1];
-        dft_reg<P1, P, C, R>(v, (R)-1, twl);
-        C* o = ex1 + lf * P;
+      for (int n1 = 0; n1 < P1; ++n1) v[n1] = e[n1];
+      dft_reg<P1, P, C, R>(v, (R)-1, twl);
+    };
+    auto store = [&](int lf, int m2, const C(&v)[P1]) {
+      C* o = ex1 + lf * P;
 #pragma unroll
-        for (int m1 = 0; m1 < P1; ++m1) o[P2 * m1 + m2] = v[m1];
+      for (int m1 = 0; m1 < P1; ++m1) o[P2 * m1 + m2] = v[m1];
+    };
+    if constexpr (IP) {
+      const int m2 = tid % P2, lf = tid / P2;
+      const bool act = lf < XL * NF && lf / NF < nxl;
+      C v[P1];
+      if (act) load(lf, m2, v);
+      __syncthreads();
+      if (act) store(lf, m2, v);
+    } else {
+      for (int task = tid; task < XL * NF * P2; task += NTH) {
+        const int m2 = task % P2, lf = task / P2;
+        if (lf / NF < nxl) {
+          C v[P1];
+          load(lf, m2, v);
+          store(lf, m2, v);
+        }
       }
     }
     __syncthreads();
     if constexpr (XFO) {
       // unpack, scale and transform over the block's eight lines: task (output field, m)
       static_assert(XF && XL == 8 && NF == 2, "XFO: three fields on two packed lines");
-      for (int task = tid; task < 3 * nzk; task += 256) {
+      for (int task = tid; task < 3 * nzk; task += NTH) {
         const int fo = task / nzk;
         const int m = task - fo * nzk;
         const int mr = m == 0 ? 0 : P - m;
@@ -466,7 +521,7 @@ __global__ void __launch_bounds__(256)
       return;
     }
     // unpack, scale and store the kept modes m < nzm: task (xl, line f, m)
-    for (int task = tid; task < XL * NF * nzk; task += 256) {
+    for (int task = tid; task < XL * NF * nzk; task += NTH) {
       const int m = task % nzk;
       const int lf = task / nzk;
       const int f = lf % NF;
@@ -496,12 +551,6 @@ hipError_t launch_adj_z_lds(sp_plan* p, bool fp32);
 
 constexpr int kZXL = 8;
 
-// x-lines per block of length P: eight, but four past 72 points, where eight take 59 KB
-// of LDS or more and leave a CU one or two blocks. Measured (separate inverse x
-// transform): 60.4 us against 40.2 with four at P = 144 (96x97x96), 18.0 against 17.5 at
-// 108, 9.5 against 8.6 at 81, 8.3 against 8.6 at 54.
-constexpr int zline_lines(int P) { return P > 72 ? 4 : 8; }
-
 template <typename R, class Op, bool XF = false, bool XFO = false, bool SB = false>
 static void zline_launch(sp_plan* p, const void* in, void* out, R* base, const void* tw,
                          const ZLineMap& map, double scale, const void* twx = nullptr,
@@ -517,10 +566,10 @@ static void zline_launch(sp_plan* p, const void* in, void* out, R* base, const v
   {                                                                                            \
     constexpr int XL = XF ? kZXL : zline_lines(A * B);                                         \
     const dim3 grid = XF ? dim3(d.ny * (d.px / XL), nb) : dim3(d.ny, (d.px + XL - 1) / XL, nb); \
-    hipLaunchKernelGGL((k_zline<R, A, B, XL, Op, XF, XFO, SB>), grid, dim3(256), 0, p->stream, ci, co,   \
-                       base, ct, map, d.ny, d.px, d.nzm, (R)scale, cx, d.nx, (R)d.alpha,       \
-                       (R)d.gamma, XF ? p->mem.yv : p->mem.xp, p->mem.np, (C*)prev,            \
-                       first ? 1 : 0);                                                         \
+    hipLaunchKernelGGL((k_zline<R, A, B, XL, Op, XF, XFO, SB>), grid,                          \
+                       dim3(zline_threads(A * B, XF)), 0, p->stream, ci, co, base, ct, map,    \
+                       d.ny, d.px, d.nzm, (R)scale, cx, d.nx, (R)d.alpha, (R)d.gamma,          \
+                       XF ? p->mem.yv : p->mem.xp, p->mem.np, (C*)prev, first ? 1 : 0);        \
   }
   if constexpr (sizeof(R) == sizeof(float) || XF) {
     SP_REG_FFT_DISPATCH(d.pz, ZL)
@@ -536,9 +585,9 @@ static void zline_launch(sp_plan* p, const void* in, void* out, R* base, const v
 // 4 MiB L2 (48x65x48 in FP64 and FP32: 0.8 and 0.4 MiB per plane; 96x97x96
 // in FP32: 3.2 MiB) and slower beyond (96x97x96 in FP64: 6.3 MiB per plane,
 // 146 us against 57 + 61 us for the two kernels). The adjoint kernel (three
-// fields) holds two waves per SIMD instead of three and hides less of that
-// latency: fused it was 6-10 % faster at 48x65x48 (0.5 and 0.2 MiB) and 1-2 %
-// slower at 96x97x96 (3.8 and 1.9 MiB), so its bound is 1 MiB.
+// fields) was 6-10 % faster fused at 48x65x48 (0.5 and 0.2 MiB), 24.2 us against 6.2 +
+// 17.6 at 64x65x64 in FP64 (1.1 MiB) and 79.8 against 12.6 + 55.4 at 96x97x96 (3.8 MiB;
+// in FP32, 1.9 MiB, 1-2 % slower), so its bound is 1 MiB.
 bool zline_fuses_x_inverse(const sp_plan* p, bool fp32, int nfields) {
   const Dims& d = p->d;
   if (reg_fft_split(d.pz, true) == 0 || d.nx % (2 * kZXL) != 0 || 3 * d.nzm != d.pz) return false;
