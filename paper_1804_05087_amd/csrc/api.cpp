@@ -718,28 +718,28 @@ extern "C" sp_status sp_time_stage(sp_plan* p, int32_t stage, const double* u, d
     const Apart apart(p);
     s = befe_into(p, uu, oo, fp32);
     if (s) return s;
-  hipEvent_t e0 = nullptr, e1 = nullptr;
-  SP_TRY_HIP(hipEventCreate(&e0), "event");
-  if (hipEventCreate(&e1) != hipSuccess) {
-    (void)hipEventDestroy(e0);
-    return set_error(p, SP_ERR_HIP, "event");
-  }
-  hipError_t e = hipEventRecord(e0, p->stream);
-  for (int r = 0; r < reps && e == hipSuccess; ++r) {
-    switch (stage) {
-      case SP_STAGE_SYNTH: e = launch_synth_y(p, uu, fp32); break;
-      case SP_STAGE_XINV: e = launch_fft_x_inv(p, fp32); break;
-      case SP_STAGE_ZLINE: e = launch_z_product(p, 0, fp32); break;
-      case SP_STAGE_XFWD: e = launch_fft_x_fwd(p, fp32); break;
-      default: e = launch_analysis_solve(p, uu, p->d.inv_dt, oo, 1, fp32); break;
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    SP_TRY_HIP(hipEventCreate(&e0), "event");
+    if (hipEventCreate(&e1) != hipSuccess) {
+      (void)hipEventDestroy(e0);
+      return set_error(p, SP_ERR_HIP, "event");
     }
-  }
-  if (e == hipSuccess) e = hipEventRecord(e1, p->stream);
-  if (e == hipSuccess) e = hipEventSynchronize(e1);
-  if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
-  if (e != hipSuccess) return hip_check(p, e, "sp_time_stage");
+    hipError_t e = hipEventRecord(e0, p->stream);
+    for (int r = 0; r < reps && e == hipSuccess; ++r) {
+      switch (stage) {
+        case SP_STAGE_SYNTH: e = launch_synth_y(p, uu, fp32); break;
+        case SP_STAGE_XINV: e = launch_fft_x_inv(p, fp32); break;
+        case SP_STAGE_ZLINE: e = launch_z_product(p, 0, fp32); break;
+        case SP_STAGE_XFWD: e = launch_fft_x_fwd(p, fp32); break;
+        default: e = launch_analysis_solve(p, uu, p->d.inv_dt, oo, 1, fp32); break;
+      }
+    }
+    if (e == hipSuccess) e = hipEventRecord(e1, p->stream);
+    if (e == hipSuccess) e = hipEventSynchronize(e1);
+    if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+    (void)hipEventDestroy(e0);
+    (void)hipEventDestroy(e1);
+    if (e != hipSuccess) return hip_check(p, e, "sp_time_stage");
   }
   if (solve_takes_x_forward(p, fp32)) {  // out as sp_befe_step gives it
     s = befe_into(p, uu, oo, fp32);

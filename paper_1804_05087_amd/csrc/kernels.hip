@@ -353,8 +353,9 @@ __global__ void __launch_bounds__(AN != 0 ? 128 : 64)
   extern __shared__ unsigned char smem_raw[];
   const int N = ny - 1;
   const int n1 = ny;
-  // the mode record and the weights; by coefficient n: the right-hand side on its way into the rows' registers
-  // (F_v, F_par, -F_perp), then the solution on its way out (v, A = D v, u_perp)
+  // the mode record and the weights; by coefficient n: the right-hand side on its way into
+  // the rows' registers (F_v, F_par, -F_perp), then the solution on its way out (v,
+  // A = D v, u_perp)
   double* rec = reinterpret_cast<double*>(smem_raw);
   double* hwp = rec + stride;
   cd* Fv = reinterpret_cast<cd*>(rec + ((stride + 3 * hwp_row(n1) + 1) & ~1));

@@ -162,19 +162,53 @@ __global__ void __launch_bounds__(128)
       if (k1 < P1 && l < nl) step2(k1, l, t[q]);
     }
   } else {
+    // FP32 keeps the one exchange and every rounding: which products the compiler contracts
+    // into fused multiply-adds follows the code's shape
     C* ex = twl + P;  // [kc][P2][S1]
+    // step 1: task (l, n2), values at padded positions pos = P2 n1 + n2
     for (int task = threadIdx.x; task < kc * P2; task += blockDim.x) {
       const int l = task / P2;
       const int n2 = task - l * P2;
       if (l < nl) {
+        const int kz = kz0 + l;
+        const C* src = yv + ((size_t)y * nzm + kz) * nx;
+        const R kzv = gamma * (R)kz;
         C v[P1];
-        step1(l, n2, v);
+#pragma unroll
+        for (int n1 = 0; n1 < P1; ++n1) {
+          const int pos = P2 * n1 + n2;
+          const bool lo = pos < h;
+          const bool hi = pos > P - h;
+          const int i = lo ? pos : (hi ? pos - P + nx : 0);
+          const R keep = (lo || hi) ? (R)1 : (R)0;
+          const R kxv = alpha * (R)(lo ? i : i - nx);
+          C val;
+          if (plain) {
+            val = src[f * fs + i];
+          } else if (f == 0) {
+            val = src[i];
+          } else if (f == 1) {
+            val = src[2 * fs + i];
+          } else if (f == 2) {
+            val = src[3 * fs + i];
+          } else if (f == 3) {  // dw/dy - i kz v
+            val = csub(src[4 * fs + i], sidot(cscale(src[2 * fs + i], kzv), (R)1));
+          } else if (f == 4) {  // i kz u - i kx w
+            val = sidot(csub(cscale(src[i], kzv), cscale(src[3 * fs + i], kxv)), (R)1);
+          } else {  // i kx v - du/dy
+            val = csub(sidot(cscale(src[2 * fs + i], kxv), (R)1), src[fs + i]);
+          }
+          v[n1] = cscale(val, keep);
+        }
+        dft_reg<P1, P, C, R>(v, (R)1, twl);
         C* e = ex + (l * P2 + n2) * S1;
 #pragma unroll
-        for (int k1 = 0; k1 < P1; ++k1) e[k1] = v[k1];
+        for (int k1 = 0; k1 < P1; ++k1)
+          e[k1] = (k1 == 0 || n2 == 0) ? v[k1] : cmul(v[k1], wpow<P, P, C, R>(n2 * k1, (R)1, twl));
       }
     }
     __syncthreads();
+    // step 2: task (k1, l), physical points x = k1 + P1 k2
     for (int task = threadIdx.x; task < P1 * kc; task += blockDim.x) {
       const int k1 = task / kc;
       const int l = task - k1 * kc;
@@ -183,7 +217,9 @@ __global__ void __launch_bounds__(128)
         const C* e = ex + l * P2 * S1 + k1;
 #pragma unroll
         for (int n2 = 0; n2 < P2; ++n2) t[n2] = e[n2 * S1];
-        step2(k1, l, t);
+        dft_reg<P2, P, C, R>(t, (R)1, twl);
+#pragma unroll
+        for (int k2 = 0; k2 < P2; ++k2) dst[(size_t)(k1 + P1 * k2) * nzm + l] = t[k2];
       }
     }
   }

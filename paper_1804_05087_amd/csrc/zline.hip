@@ -138,9 +138,12 @@ __global__ void __launch_bounds__(zline_threads(P1* P2, XF))
   // the forward transforms in place of the inverse ones: a task each, held in registers
   // over a barrier, so that no second exchange buffer is needed and a CU holds more
   // blocks (40.9 -> 30.9 us at 128x49x128). With XF the x-physical lines take its place
-  // all the same, but for the adjoint, where three lines follow two.
+  // all the same, but for the adjoint, where three lines follow two. FP32 keeps its two
+  // buffers and the code of its forward steps: which products the compiler contracts into
+  // fused multiply-adds follows their shape, and the results are pinned to those roundings
+  // (a relative 1e-7).
   constexpr int NTH = zline_threads(P1 * P2, XF);
-  constexpr bool IP = NF > 0 && (!XF || NF > NI) && XL * NF * P2 <= NTH &&
+  constexpr bool IP = sizeof(R) == 8 && NF > 0 && (!XF || NF > NI) && XL * NF * P2 <= NTH &&
                       (Op::kBase || XL * P1 * NF <= NTH);
   constexpr int LS = IP && NF > NI ? NF : NI;  // line slots per x-line in the exchange block
   // operators with a base state take the pointwise stage one physical point per
@@ -291,14 +294,14 @@ __global__ void __launch_bounds__(zline_threads(P1* P2, XF))
       for (int n1 = 0; n1 < P1; ++n1) {
         // Hermitian extension: m < nzm direct, m > P - nzm mirrored, else zero; masks
         // multiply loaded values so the loads stay unconditional, but for the n1 whose
-        // every m is one of the zeros
-        if (P2 * n1 >= P / 3 && P2 * n1 + P2 - 1 <= P - P / 3) {
+        // every m is one of the zeros (in FP64)
+        if (sizeof(R) == 8 && P2 * n1 >= P / 3 && P2 * n1 + P2 - 1 <= P - P / 3) {
           v[n1] = mk((R)0, (R)0);
           continue;
         }
         const int m = P2 * n1 + n2;
-        const bool lo_half = P2 * n1 + P2 <= P / 3 || m < nzk;
-        const bool hi_half = P2 * n1 > P - P / 3 || m > P - nzk;
+        const bool lo_half = (sizeof(R) == 8 && P2 * n1 + P2 <= P / 3) || m < nzk;
+        const bool hi_half = (sizeof(R) == 8 && P2 * n1 > P - P / 3) || m > P - nzk;
         const int mm = lo_half ? m : (hi_half ? P - m : 0);
         const C a = fa[mm];
         const C b = fbp[mm];
@@ -385,7 +388,57 @@ __global__ void __launch_bounds__(zline_threads(P1* P2, XF))
       }
     }
   }
-  if constexpr (NF > 0 && !kSplit) {
+  if constexpr (NF > 0 && !kSplit && sizeof(R) == 4) {
+    __syncthreads();
+    // the pointwise stage and step 1 of the forward transforms: as below, FP32's own code
+    constexpr int NFT = Op::kBase ? 1 : NF;  // forward lines per task split
+    for (int task = tid; task < XL * P1 * NFT; task += NTH) {
+      const int fsel = task / (XL * P1);
+      const int k1 = task % P1;
+      const int xl = (task / P1) % XL;
+      if (xl < nxl) {
+        const size_t bo0 = line_of(xl) * P + k1;
+        // forward lines F0 .. F0 + NFL - 1 (compile-time, so pout stays in registers)
+        auto run = [&](auto f0) {
+          constexpr int F0 = decltype(f0)::value;
+          constexpr int NFL = Op::kBase ? NF : 1;
+          C fw[NFL][P2];
+          const Op op{};
+#pragma unroll
+          for (int k2 = 0; k2 < P2; ++k2) {
+            C pin[NI], pout[NF];
+#pragma unroll
+            for (int i = 0; i < NI; ++i) pin[i] = ex1[((xl * NI + i) * P2 + k2) * S1 + k1];
+            op(pin, pout, base, bs, bo0 + (size_t)P1 * k2);
+#pragma unroll
+            for (int q = 0; q < NFL; ++q) fw[q][k2] = pout[F0 + q];
+          }
+#pragma unroll
+          for (int q = 0; q < NFL; ++q) {
+            dft_reg<P2, P, C, R>(fw[q], (R)-1, twl);
+            C* e = ex2 + ((xl * NF + F0 + q) * P2) * S1 + k1;
+#pragma unroll
+            for (int m2 = 0; m2 < P2; ++m2)
+              e[m2 * S1] = (m2 == 0 || k1 == 0)
+                               ? fw[q][m2]
+                               : cmul(fw[q][m2], wpow<P, P, C, R>(k1 * m2, (R)-1, twl));
+          }
+        };
+        if constexpr (Op::kBase) {
+          run(std::integral_constant<int, 0>{});
+        } else {
+          if (fsel == 0) run(std::integral_constant<int, 0>{});
+          if constexpr (NF > 1) {
+            if (fsel == 1) run(std::integral_constant<int, 1>{});
+          }
+          if constexpr (NF > 2) {
+            if (fsel == 2) run(std::integral_constant<int, 2>{});
+          }
+        }
+      }
+    }
+  }
+  if constexpr (NF > 0 && !kSplit && sizeof(R) == 8) {
     __syncthreads();
     // the pointwise stage and step 1 of the forward transforms: task (xl, k1,
     // forward line f) for operators that read no base state, f slowest (with
@@ -454,32 +507,36 @@ __global__ void __launch_bounds__(zline_threads(P1* P2, XF))
   if constexpr (NF > 0) {
     __syncthreads();
     // step 2 of the forward transforms: task (xl, line f, m2), outputs m = P2 m1 + m2
-    auto load = [&](int lf, int m2, C(&v)[P1]) {
-      const int xl = lf / NF;
-      const C* e = fx + ((xl * LF + lf - xl * NF) * P2 + m2) * S1;
-#pragma unroll
-      for (int n1 = 0; n1 < P1; ++n1) v[n1] = e[n1];
-      dft_reg<P1, P, C, R>(v, (R)-1, twl);
-    };
-    auto store = [&](int lf, int m2, const C(&v)[P1]) {
-      C* o = ex1 + lf * P;
-#pragma unroll
-      for (int m1 = 0; m1 < P1; ++m1) o[P2 * m1 + m2] = v[m1];
-    };
     if constexpr (IP) {
-      const int m2 = tid % P2, lf = tid / P2;
-      const bool act = lf < XL * NF && lf / NF < nxl;
+      const int m2 = tid % P2, lf = tid / P2, xl = lf / NF;
+      const bool act = lf < XL * NF && xl < nxl;
       C v[P1];
-      if (act) load(lf, m2, v);
+      if (act) {
+        const C* e = fx + ((xl * LF + lf - xl * NF) * P2 + m2) * S1;
+#pragma unroll
+        for (int n1 = 0; n1 < P1; ++n1) v[n1] = e[n1];
+        dft_reg<P1, P, C, R>(v, (R)-1, twl);
+      }
       __syncthreads();
-      if (act) store(lf, m2, v);
+      if (act) {
+        C* o = ex1 + lf * P;
+#pragma unroll
+        for (int m1 = 0; m1 < P1; ++m1) o[P2 * m1 + m2] = v[m1];
+      }
     } else {
       for (int task = tid; task < XL * NF * P2; task += NTH) {
-        const int m2 = task % P2, lf = task / P2;
-        if (lf / NF < nxl) {
+        const int m2 = task % P2;
+        const int lf = task / P2;
+        const int xl = lf / NF;
+        if (xl < nxl) {
+          const C* e = ex2 + (lf * P2 + m2) * S1;
           C v[P1];
-          load(lf, m2, v);
-          store(lf, m2, v);
+#pragma unroll
+          for (int n1 = 0; n1 < P1; ++n1) v[n1] = e[n1];
+          dft_reg<P1, P, C, R>(v, (R)-1, twl);
+          C* o = ex1 + lf * P;
+#pragma unroll
+          for (int m1 = 0; m1 < P1; ++m1) o[P2 * m1 + m2] = v[m1];
         }
       }
     }
