@@ -248,6 +248,210 @@ __global__ void __launch_bounds__(64)
 }
 
 // ---------------------------------------------------------------------------
+// stokes_solve_adj of the mixed-precision VJP: the same steps with their operands in LDS,
+// E elements of a chain per lane from its own first coefficient. The transforms that follow
+// round the result to FP32, and where that falls depends on the last bits of these FP64
+// sums (a relative 1e-9 to 6e-9 of the VJP from ny = 43 on), so this precision keeps
+// their order: 15.4 us at 48x65x48, where the registers' takes 9.9.
+// ---------------------------------------------------------------------------
+#define SP_ROW_PAR(par, body)                       \
+  _Pragma("unroll") for (int e_ = 0; e_ < E; ++e_) { \
+    const int n = (par) + 2 * (l * E + e_);          \
+    if (n <= N) {                                    \
+      body                                           \
+    }                                                \
+  }
+
+template <int E>
+__global__ void __launch_bounds__(64)
+    k_stokes_solve_adj_lds(const double2* __restrict__ w, double2* __restrict__ out,
+                       const double* __restrict__ modedata, const double* __restrict__ hw_g,
+                       int stride, int nx, int ny, int nzh, double alpha, double gamma, double re,
+                       double inv_dt) {
+  extern __shared__ unsigned char smem_raw[];
+  const int N = ny - 1;
+  const int n1 = ny;
+  double* rec = reinterpret_cast<double*>(smem_raw);
+  double* hw = rec + stride;
+  cd* Upb = reinterpret_cast<cd*>(hw + 3 * n1);  // adjoint of u_par
+  cd* Ub = Upb + n1;                              // adjoint of u_perp
+  cd* Vb = Ub + n1;                               // adjoint of v
+  cd* A = Vb + n1;
+  cd* Tm = A + n1;
+  cd* W = Tm + n1;    // scratch of rows 0, 1
+  cd* W2 = W + n1;    // scratch of rows 2, 3
+  cd* Rb = W2 + n1;
+  cd* Rb2 = Rb + n1;
+  cd* Pb = Rb2 + n1;
+  cd* Db = Pb + n1;
+  cd* Fpb = Db + n1;
+  cd* Fpp = Fpb + n1;
+  cd* Fvb = Fpp + n1;
+  cd* Dm = Fvb + n1;  // output of the idle rows
+
+  const int mode = blockIdx.x;
+  const int i = mode / nzh;
+  const int j = mode - i * nzh;
+  const int tid = threadIdx.x;
+  const int row = tid >> 4;
+  const int l = tid & 15;
+  const size_t cs = (size_t)nx * nzh * ny;
+  const size_t mo = ((size_t)i * nzh + j) * ny;
+  const bool nyq = (i == nx / 2) || (j == nzh - 1);
+  if (nyq) {
+    for (int n = tid; n < n1; n += 64) {
+      out[mo + n] = make_double2(0.0, 0.0);
+      out[cs + mo + n] = make_double2(0.0, 0.0);
+      out[2 * cs + mo + n] = make_double2(0.0, 0.0);
+    }
+    return;
+  }
+  const int mxv = (i < nx / 2) ? i : i - nx;
+  const double kx = alpha * mxv;
+  const double kz = gamma * j;
+  const double k2 = kx * kx + kz * kz;
+  const bool mean = (i == 0 && j == 0);
+  const double k = sqrt(k2);
+  const double ik = mean ? 0.0 : 1.0 / k;
+  const double lam = k2 + re * inv_dt;
+  double2 wa[3], wb[3], wc[3];
+  // packed-Euclidean -> Parseval weights: the (0,0) mode counts twice
+  const double wscale = mean ? 2.0 : 1.0;
+#pragma unroll
+  for (int t = 0; t < 3; ++t) {  // clamped loads, masked after (no per-load branches)
+    const int n = tid + 64 * t;
+    const int nc = n < n1 ? n : N;
+    const double keep = n < n1 ? wscale : 0.0;
+    wa[t] = w[mo + nc];
+    wb[t] = w[cs + mo + nc];
+    wc[t] = w[2 * cs + mo + nc];
+    wa[t] = make_double2(wa[t].x * keep, wa[t].y * keep);
+    wb[t] = make_double2(wb[t].x * keep, wb[t].y * keep);
+    wc[t] = make_double2(wc[t].x * keep, wc[t].y * keep);
+  }
+  // mode record and weights (contiguous in LDS: hw = rec + stride) in one round
+  // trip: all loads are issued before the first LDS store
+  {
+    constexpr int RPL = solve_record_loads(E);
+    const double* src = modedata + (size_t)mode * stride;
+    const int tot = stride + 3 * n1;
+    double rv[RPL];
+#pragma unroll
+    for (int q = 0; q < RPL; ++q) {
+      const int t = tid + 64 * q;
+      const int tc = t < tot ? t : tot - 1;
+      rv[q] = (tc < stride) ? src[tc] : hw_g[tc - stride];
+    }
+#pragma unroll
+    for (int q = 0; q < RPL; ++q) {
+      const int t = tid + 64 * q;
+      if (t < tot) rec[t] = rv[q];
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < 3; ++t) {
+    const int n = tid + 64 * t;
+    if (n < n1) {
+      const cd ub(wa[t].x, wa[t].y), vb(wb[t].x, wb[t].y), wbv(wc[t].x, wc[t].y);
+      if (mean) {
+        Upb[n] = ub;
+        Ub[n] = wbv;
+      } else {
+        Upb[n] = (ub * kx + wbv * kz) * ik;
+        Ub[n] = (ub * kz - wbv * kx) * ik;
+      }
+      Vb[n] = vb;
+      Pb[n] = cd(0.0);
+      Fvb[n] = cd(0.0);
+      Fpb[n] = cd(0.0);
+      Fpp[n] = cd(0.0);
+    }
+  }
+  __syncthreads();
+  const ModeLayout L{n1};
+  const SweepRec helm(rec + L.helm(), n1, lam);
+  const SweepRec pois(rec + L.pois(), n1, k2);
+  const bool vrow = row < 2;
+  const int pv = row & 1;  // v parity (rows 0, 1), u_perp / w parity (rows 2, 3)
+  const int po = 1 - pv;
+  if (mean) {
+    wsweep_T<E>(helm, hw, N, pv, vrow ? Upb : Ub, vrow ? Rb : Rb2, vrow ? W : W2, l);
+    if (vrow)
+      SP_ROW_PAR(pv, Fpb[n] = -Rb[n];)
+    else
+      SP_ROW_PAR(pv, Fpp[n] = -Rb2[n];)
+  } else {
+    // u_par = i D v / k (transposed): A = conj(i) u_par_bar / k on parity po
+    if (vrow) SP_ROW_PAR(po, A[n] = mul_i(-Upb[n]) * ik;)
+    __syncthreads();
+    wderiv_T<E>(N, po, vrow ? A : Ub, vrow ? Tm : Dm, vrow ? W : W2, l);
+    __syncthreads();
+    if (vrow) SP_ROW_PAR(pv, Vb[n] = Vb[n] + Tm[n];)
+    __syncthreads();
+    // v = v_p + c_delta v_delta + c_b v_b, (c_delta, c_b) = -Minv (l_a, l_b)
+    const double* vdel = rec + L.vdel();
+    const double* vbs = rec + L.vb();
+    cd ca(0.0), cbb(0.0);
+    SP_ROW_PAR(pv, ca = ca + Vb[n] * vdel[n]; cbb = cbb + Vb[n] * vbs[n];)
+    ca = row_sum(ca);
+    cbb = row_sum(cbb);
+    const double* Mi = rec + L.minv() + 4 * pv;
+    const cd la = -(ca * Mi[0] + cbb * Mi[2]);
+    const cd lb = -(ca * Mi[1] + cbb * Mi[3]);
+    const int m = (N % 2 == pv) ? N : N - 1;
+    __syncthreads();
+    if (vrow) {
+      SP_ROW_PAR(pv, Vb[n] = Vb[n] + la * ((double)n * n) + ((n == m) ? lb * lam : cd(0.0));)
+      SP_ROW_PAR(po, if (n == N && m == N - 1) Pb[n] = Pb[n] + lb * (2.0 * N);)
+    }
+    __syncthreads();
+    // v_p = H(D P - F_v) on rows 0, 1; u_perp = H(-F_perp) on rows 2, 3
+    wsweep_T<E>(helm, hw, N, pv, vrow ? Vb : Ub, vrow ? Rb : Rb2, vrow ? W : W2, l);
+    if (vrow)
+      SP_ROW_PAR(pv, Fvb[n] = -Rb[n];)
+    else
+      SP_ROW_PAR(pv, Fpp[n] = -Rb2[n];)
+    __syncthreads();
+    wderiv_T<E>(N, pv, vrow ? Rb : Ub, vrow ? Tm : Dm, vrow ? W : W2, l);
+    __syncthreads();
+    if (vrow) SP_ROW_PAR(po, Pb[n] = Pb[n] + Tm[n];)
+    __syncthreads();
+    // P = Pois(div F), div F = i k F_par + D F_v
+    // the rows' operator chosen field by field (a per-lane choice between two
+    // records would be made through scratch memory)
+    const SweepRec pois_or_helm(rec + (vrow ? L.pois() : L.helm()), n1, vrow ? k2 : lam);
+    wsweep_T<E>(pois_or_helm, hw, N, vrow ? po : pv, vrow ? Pb : Ub, vrow ? Db : Dm,
+                vrow ? W : W2, l);
+    if (vrow) SP_ROW_PAR(po, Fpb[n] = mul_i(-Db[n]) * k;)
+    __syncthreads();
+    wderiv_T<E>(N, po, vrow ? Db : Ub, vrow ? Tm : Dm, vrow ? W : W2, l);
+    __syncthreads();
+    if (vrow) SP_ROW_PAR(pv, Fvb[n] = Fvb[n] + Tm[n];)
+  }
+  __syncthreads();
+  // n1 <= 32 E coefficients: a fixed, unrolled pass count
+#pragma unroll
+  for (int q = 0; q < (32 * E + 63) / 64; ++q) {
+    const int n = tid + 64 * q;
+    if (n >= n1) break;
+    cd gu, gv, gw;
+    if (n <= N - 2) {
+      if (mean) {
+        gu = Fpb[n] * re;
+        gw = Fpp[n] * re;
+      } else {
+        gu = (Fpb[n] * kx + Fpp[n] * kz) * (re * ik);
+        gw = (Fpb[n] * kz - Fpp[n] * kx) * (re * ik);
+        gv = Fvb[n] * re;
+      }
+    }
+    out[mo + n] = make_double2(gu.re, gu.im);
+    out[cs + mo + n] = make_double2(gv.re, gv.im);
+    out[2 * cs + mo + n] = make_double2(gw.re, gw.im);
+  }
+}
+
+// ---------------------------------------------------------------------------
 // adj_z: per (y, x) z-line, in place on xp. Reads the three adjoint product
 // fields lam (z spectral), forms them in physical space (Hermitian-extended
 // inverse FFT of the pair (lam_x + i lam_y) and of lam_z), applies the
@@ -355,6 +559,25 @@ hipError_t launch_stokes_solve_adj(sp_plan* p, const double2* w, double2* out) {
   const Dims& d = p->d;
   const size_t rec = ((size_t)p->mode_stride + 3 * hwp_row(d.ny) + 1) / 2 * 2;
   const size_t sh = rec * sizeof(double) + 3 * (size_t)d.ny * sizeof(cd);
+  if (p->precision == SP_MIXED) {
+    const size_t shl = ((size_t)p->mode_stride + 3 * (size_t)d.ny) * sizeof(double) +
+                       15 * (size_t)d.ny * sizeof(cd);
+    SP_PROF_BEGIN(p, KID_SOLVE_ADJ);
+#define SP_SOLVE_ADJ_LDS(EV)                                                                    \
+  hipLaunchKernelGGL((k_stokes_solve_adj_lds<EV>), dim3(d.nx * d.nzh), dim3(64), shl, p->stream, \
+                     w, out, p->d_mode, p->d_hw, p->mode_stride, d.nx, d.ny, d.nzh, d.alpha,    \
+                     d.gamma, d.re, d.inv_dt)
+    switch (solve_lanes_per_chain(d.ny)) {
+      case 1: SP_SOLVE_ADJ_LDS(1); break;
+      case 2: SP_SOLVE_ADJ_LDS(2); break;
+      case 3: SP_SOLVE_ADJ_LDS(3); break;
+      case 4: SP_SOLVE_ADJ_LDS(4); break;
+      default: SP_SOLVE_ADJ_LDS(5); break;
+    }
+#undef SP_SOLVE_ADJ_LDS
+    SP_PROF_END(p, KID_SOLVE_ADJ);
+    return hipGetLastError();
+  }
   SP_PROF_BEGIN(p, KID_SOLVE_ADJ);
 #define SP_SOLVE_ADJ_LAUNCH(EV)                                                                \
   hipLaunchKernelGGL((k_stokes_solve_adj<EV>), dim3(d.nx * d.nzh), dim3(64), sh, p->stream, w, \

@@ -196,6 +196,14 @@ sp_status build_mode_data(sp_plan* p) {
                              hipMemcpyHostToDevice),
                 "upload mode data");
   if (s) return s;
+  if (!p->d_hw) {
+    s = hip_check(p, hipMalloc(&p->d_hw, hw.size() * sizeof(double)), "hipMalloc(hw)");
+    if (s) return s;
+    s = hip_check(p, hipMemcpy(p->d_hw, hw.data(), hw.size() * sizeof(double),
+                               hipMemcpyHostToDevice),
+                  "upload hw");
+    if (s) return s;
+  }
   if (!p->d_hwp) {
     std::vector<double> hwp(3 * hwp_row(n1), 0.0);
     for (int w = 0; w < 3; ++w)
@@ -211,7 +219,8 @@ sp_status build_mode_data(sp_plan* p) {
     // the solve kernels stage record + weights with solve_record_loads(E)
     // doubles per lane (E = elements per lane and parity chain, at most 5)
     const int E = solve_reg_elems(p->d.ny);
-    if (E > 5 || stride + 3 * hwp_row(p->d.ny) > 64 * solve_record_loads(E))
+    if (E > 5 || stride + 3 * p->d.ny > 64 * solve_record_loads(solve_lanes_per_chain(p->d.ny)) ||
+        stride + 3 * hwp_row(p->d.ny) > 64 * solve_record_loads(E))
       return set_error(p, SP_ERR_SHAPE, "mode record does not fit the solve kernels' loads");
   }
   p->mode_stride = stride;
@@ -232,7 +241,7 @@ static std::vector<F> convert(const std::vector<D>& v) {
 }
 
 static void free_plan(sp_plan* p) {
-  void* ptrs[] = {p->d_T,   p->d_TD,  p->d_Tinv, p->d_G,    p->d_hwp,  p->d_mode, p->d_twx,
+  void* ptrs[] = {p->d_T,   p->d_TD,  p->d_Tinv, p->d_G,    p->d_hwp,  p->d_hw, p->d_mode, p->d_twx,
                   p->d_twz, p->f_twx, p->f_twz,  p->f_T,    p->f_TD,   p->f_Tinv, p->d_scratch,
                   p->d_yfrag, p->f_yfrag, p->d_tinv_th, p->f_tinv_th, p->d_yfold};
   for (void* q : ptrs)

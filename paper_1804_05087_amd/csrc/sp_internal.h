@@ -153,7 +153,8 @@ struct sp_plan {
   double* d_TD = nullptr;     // [ny][ny] T . D (values of d/dy)
   double* d_Tinv = nullptr;   // [ny][ny] analysis
   double* d_G = nullptr;      // [ny][ny] Gram matrix int T_n T_m
-  double* d_hwp = nullptr;    // Helmholtz right-hand-side weights, zero padded, [3][ny + 2]
+  double* d_hw = nullptr;     // [3][ny] Helmholtz right-hand-side weights
+  double* d_hwp = nullptr;    // the same zero padded, [3][ny + 2] (solve_reg.h)
   double* d_mode = nullptr;   // per-mode solve records
   int mode_stride = 0;
   double2* d_twx = nullptr;   // [px] exp(-2 pi i k / px)
@@ -244,6 +245,8 @@ size_t noalloc_bytes_needed(const Dims& d);
 sp_status set_error(sp_plan* p, sp_status s, const std::string& msg);
 sp_status hip_check(sp_plan* p, hipError_t e, const char* what);
 sp_status build_mode_data(sp_plan* p);
+// elements per lane of a 16-lane row covering one parity chain (ny <= 129: at most 5)
+constexpr int solve_lanes_per_chain(int ny) { return ((ny - 1) / 2 + 1 + 15) / 16; }
 
 // kernel launchers (kernels.hip); all enqueue on p->stream
 hipError_t launch_synth_y(sp_plan* p, const double2* u, bool fp32);
