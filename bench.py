@@ -52,7 +52,7 @@ CAL_COPY_BYTES = 256 * 1024 * 1024
 # sources (KERNEL_SOURCES) the counters were taken with: a changed source
 # reports traffic null.
 KERNEL_SOURCES = {
-    "k_stokes_solve": ["kernels.hip", "solve_row.h", "solve_core.h", "device_common.h"],
+    "k_stokes_solve": ["kernels.hip", "solve_reg.h", "solve_row.h", "solve_core.h", "device_common.h"],
     "k_z_product": ["zline.hip", "device_common.h"],
 }
 MEASURED_TRAFFIC = {
