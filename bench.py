@@ -57,16 +57,16 @@ KERNEL_SOURCES = {
 }
 MEASURED_TRAFFIC = {
     "couette_48x65x48_re1000_dt100": {
-        # 256 MiB copy: FETCH_SIZE 131095.3 KiB, WRITE_SIZE 262144.0 KiB
+        # 256 MiB copy: FETCH_SIZE 131092.5 KiB, WRITE_SIZE 262144.0 KiB
         "k_stokes_solve": {
-            "fetch_kib": 5611.6, "write_kib": 3674.3,
-            "fetch_factor": 262144.0 / 131095.3, "write_factor": 1.0,
-            "sources_sha256": "6d8eab5a02c7bee69b1cf019c8fb8eb0cc3333c2d80294df2cb5a5525c6c53f6",
+            "fetch_kib": 5591.2, "write_kib": 3674.3,
+            "fetch_factor": 262144.0 / 131092.5, "write_factor": 1.0,
+            "sources_sha256": "3ea95296af943aa9563fa13bdc6dcd603c9a1c857cb680b3232615244a08c9ba",
         },
         "k_z_product": {
-            "fetch_kib": 3337.1, "write_kib": 5265.0,
-            "fetch_factor": 262144.0 / 131095.3, "write_factor": 1.0,
-            "sources_sha256": "9a914b3f355c42eb20a1920283f7ef6e70b740bf1c393267c7e68a08b5f87e08",
+            "fetch_kib": 3332.0, "write_kib": 5265.0,
+            "fetch_factor": 262144.0 / 131092.5, "write_factor": 1.0,
+            "sources_sha256": "ef1a3ee6448b5b10cf3b397cd78b44da0e41c2f9e9f858e707190973bd77447e",
         },
     },
 }
