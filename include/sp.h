@@ -234,7 +234,10 @@ sp_status sp_unpack(sp_plan* plan, const double* packed, double* canonical);
  * of one group runs on the plan's stream; of several, up to nstreams (1..8) groups
  * run concurrently (3 fill, with the plan's own stream, the 4 hardware queues a
  * process gets by default), each with its own intermediates and stream. These
- * are allocated on first use and kept
+ * are allocated on first use for the members of that call's groups, anew where a
+ * later call has larger ones (the smaller buffers stay: a captured graph may use
+ * them; in all less than twice the largest), in smaller groups and on fewer
+ * streams where the device is short of memory or the call is captured, and kept
  * until sp_plan_destroy; the plan's stream waits for all members before the
  * call returns its work, so results are ordered like those of single calls and
  * equal to them bit for bit. SP_ERR_INVALID for count < 0, nstreams outside
@@ -256,9 +259,10 @@ sp_status sp_jvp_lin_batch(sp_plan* plan, int32_t op, int32_t count, int32_t nst
  * with one BEFE step, no laminar advection) the columns run in groups as in
  * sp_jvp_lin_batch (3 streams where there are several), each group with its own
  * unit fields; the multi-step chain forms them one after another.
- * The plan's stream waits for all of them. Buffers are allocated on first use
- * and kept until sp_plan_destroy (SP_ERR_NOMEM if that fails). SP_ERR_INVALID for a bad
- * op, a range outside [0, packed_n), ld < packed_n or no base state. */
+ * The plan's stream waits for all of them. Buffers (two canonical fields for each
+ * member of a group beside its intermediates; two fields and a packed vector where
+ * the columns are formed one after another) are allocated and kept as for the
+ * batched calls (SP_ERR_NOMEM if that fails). SP_ERR_INVALID for a bad op, a range outside [0, packed_n), ld < packed_n or no base state. */
 sp_status sp_jacobian_columns(sp_plan* plan, int32_t op, int64_t first, int64_t count, double* J,
                               int64_t ld);
 

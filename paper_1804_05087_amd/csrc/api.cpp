@@ -457,7 +457,33 @@ static int group_members(const sp_plan* p) {
   return n < 1 ? 1 : (n > kGroupMost ? (int)kGroupMost : (int)n);
 }
 
-static sp_status ensure_batch(sp_plan* p, int nsets) {
+// Grows a buffer of cap members, unit bytes each, to hold want; at least doubled, within
+// most, so that the blocks given up add up to less than the one in use. Those stay
+// allocated until the plan is destroyed (old): a graph captured from an earlier call may
+// still replay on them. With less, half as many and so on if the device is short of memory.
+static void grow_members(BatchSet& b, void** mem, int* cap, size_t unit, int want, int most,
+                         bool less) {
+  if (*cap >= want) return;
+  if (want < 2 * *cap) want = 2 * *cap < most ? 2 * *cap : most;
+  for (; want > *cap; want = less ? want / 2 : 0) {
+    void* q = nullptr;
+    if (hipMalloc(&q, unit * (size_t)want) != hipSuccess) {
+      (void)hipGetLastError();
+      continue;
+    }
+    if (*mem) b.old.push_back(*mem);
+    *mem = q;
+    *cap = want;
+    return;
+  }
+}
+
+// Up to *nsets buffer sets that hold groups of *members members, with the unit fields of
+// Jacobian columns if columns: what the call needs, not the largest group. Where the
+// device is short of memory, or the call is being captured into a graph (and may not
+// allocate), smaller groups on the first set and fewer sets, one set of one member at
+// least. On return *nsets and *members are what there is.
+static sp_status ensure_batch(sp_plan* p, int* nsets, int* members, bool columns) {
   if (!p->bstart && hipEventCreateWithFlags(&p->bstart, hipEventDisableTiming) != hipSuccess) {
     p->bstart = nullptr;
     return set_error(p, SP_ERR_HIP, "cannot create the batch event");
@@ -465,30 +491,48 @@ static sp_status ensure_batch(sp_plan* p, int nsets) {
   Members m;
   member_strides(p, m);
   const size_t sizes[4] = {m.yv, m.xp, m.np, m.nv};
-  const size_t G = group_members(p);
-  size_t total = 0;
-  for (size_t b : sizes) total += (b * G * sizeof(double2) + 255) / 256 * 256;
-  while ((int)p->bsets.size() < nsets) {
-    BatchSet b;
-    if (hipMalloc(&b.mem, total) != hipSuccess) {
-      (void)hipGetLastError();
-      return set_error(p, SP_ERR_NOMEM, "cannot allocate the intermediates of a batch");
+  auto lines = [](size_t n) { return (n * sizeof(double2) + 255) / 256 * 256; };
+  size_t unit = 0;  // of a member, each array a whole number of 256-byte lines
+  for (size_t n : sizes) unit += lines(n);
+  const size_t field = canon_count(p) * sizeof(double2);
+  const int most = group_members(p);
+  int ready = 0;
+  for (; ready < *nsets; ++ready) {
+    const bool first = ready == 0;
+    if (ready == (int)p->bsets.size()) p->bsets.push_back(BatchSet());
+    BatchSet& b = p->bsets[ready];
+    auto have = [&] { return columns && b.cols < b.cap ? b.cols : b.cap; };
+    bool fixed = false;
+    if (have() < *members) {
+      hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+      if (hipStreamIsCapturing(p->stream, &st) != hipSuccess) (void)hipGetLastError();
+      fixed = st != hipStreamCaptureStatusNone && (!first || have() > 0);
     }
-    if (hipStreamCreateWithFlags(&b.s, hipStreamNonBlocking) != hipSuccess ||
-        hipEventCreateWithFlags(&b.done, hipEventDisableTiming) != hipSuccess) {
-      (void)hipGetLastError();
-      if (b.s) (void)hipStreamDestroy(b.s);
-      (void)hipFree(b.mem);
-      return set_error(p, SP_ERR_HIP, "cannot create the stream of a batch");
+    if (!fixed) {
+      if (!b.s && (hipStreamCreateWithFlags(&b.s, hipStreamNonBlocking) != hipSuccess ||
+                   hipEventCreateWithFlags(&b.done, hipEventDisableTiming) != hipSuccess)) {
+        (void)hipGetLastError();
+        if (b.s) (void)hipStreamDestroy(b.s);
+        b.s = nullptr;
+        return set_error(p, SP_ERR_HIP, "cannot create the stream of a batch");
+      }
+      grow_members(b, &b.mem, &b.cap, unit, *members, most, first);
+      if (columns)
+        grow_members(b, (void**)&b.fin, &b.cols, 2 * field, *members, most, first);
     }
+    if (have() < (first ? 1 : *members)) break;
+    if (have() < *members) *members = have();
     void** dst[4] = {&b.yv, &b.xp, &b.np, &b.nv};
     size_t off = 0;
     for (int k = 0; k < 4; ++k) {
       *dst[k] = (char*)b.mem + off;
-      off += (sizes[k] * G * sizeof(double2) + 255) / 256 * 256;
+      off += lines(sizes[k]) * b.cap;
     }
-    p->bsets.push_back(b);
+    if (b.fin) b.fout = b.fin + canon_count(p) * b.cols;
   }
+  if (ready == 0)
+    return set_error(p, SP_ERR_NOMEM, "cannot allocate the intermediates of a batch");
+  *nsets = ready;
   return SP_OK;
 }
 
@@ -520,14 +564,15 @@ struct BatchView {
 
 // group(first, members, set) issues the launches of members first .. first + members - 1.
 template <typename F>
-static sp_status run_batch(sp_plan* p, int count, int nstreams, F group) {
+static sp_status run_batch(sp_plan* p, int count, int nstreams, F group, bool columns = false) {
   if (count == 0) return SP_OK;
   const int most = group_members(p);
-  const int groups = (count + most - 1) / most;
-  const int G = (count + groups - 1) / groups;  // evened out
-  const int S = nstreams < groups ? nstreams : groups;
-  sp_status s = ensure_batch(p, S);
+  int groups = (count + most - 1) / most;
+  int G = (count + groups - 1) / groups;  // evened out
+  int S = nstreams < groups ? nstreams : groups;
+  sp_status s = ensure_batch(p, &S, &G, columns);
   if (s) return s;
+  groups = (count + G - 1) / G;
   if (groups == 1) {
     BatchView v(p, p->bsets[0], p->stream, count);
     return group(0, count, p->bsets[0]);
@@ -568,23 +613,19 @@ extern "C" sp_status sp_jacobian_columns(sp_plan* p, int32_t op, int64_t first, 
       sp_status s = base_at(p, 0);
       if (s) return s;
     }
-    const size_t nc = canon_count(p);
-    return run_batch(p, (int)count, 3, [&](int c0, int members, BatchSet& set) -> sp_status {
-      if (!set.fin) {
-        const size_t cb = nc * sizeof(double2) * group_members(p);
-        if (hipMalloc((void**)&set.fin, 2 * cb) != hipSuccess) {
-          (void)hipGetLastError();
-          set.fin = nullptr;
-          return set_error(p, SP_ERR_NOMEM, "cannot allocate the Jacobian column buffers");
-        }
-        set.fout = set.fin + nc * group_members(p);
-      }
-      SP_TRY_HIP(launch_unit_fields(p, first + c0, members, set.fin), "unit vectors");
-      sp_status st = jvp_lin(p, op, set.fin, set.fout);
-      if (st) return st;
-      SP_TRY_HIP(launch_pack_rows(p, set.fout, members, J + (size_t)c0 * (size_t)ld, ld), "pack");
-      return SP_OK;
-    });
+    const sp_status s = run_batch(
+        p, (int)count, 3,
+        [&](int c0, int members, BatchSet& set) -> sp_status {
+          SP_TRY_HIP(launch_unit_fields(p, first + c0, members, set.fin), "unit vectors");
+          sp_status st = jvp_lin(p, op, set.fin, set.fout);
+          if (st) return st;
+          SP_TRY_HIP(launch_pack_rows(p, set.fout, members, J + (size_t)c0 * (size_t)ld, ld),
+                     "pack");
+          return SP_OK;
+        },
+        true);
+    // no memory for a group of one: one after another, on the plan's own intermediates
+    if (s != SP_ERR_NOMEM) return s;
   }
   if (!p->jc_e) {
     const size_t cb = canon_count(p) * sizeof(double2);

@@ -251,6 +251,7 @@ static void free_plan(sp_plan* p) {
   for (auto& b : p->bsets) {
     if (b.s) (void)hipStreamSynchronize(b.s);
     if (b.mem) (void)hipFree(b.mem);
+    for (void* q : b.old) (void)hipFree(q);
     if (b.fin) (void)hipFree(b.fin);  // fin and fout are one allocation
     if (b.s) (void)hipStreamDestroy(b.s);
     if (b.done) (void)hipEventDestroy(b.done);

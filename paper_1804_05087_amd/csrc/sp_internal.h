@@ -126,6 +126,9 @@ struct Members {
 
 // Intermediates and stream of one group of members of a batched call (see api.cpp).
 struct BatchSet {
+  int cap = 0;   // members that mem holds
+  int cols = 0;  // members that fin and fout hold
+  std::vector<void*> old;  // blocks that larger ones took the place of
   void* mem = nullptr;
   void* yv = nullptr;
   void* xp = nullptr;
