@@ -130,6 +130,26 @@ def algorithmic_bytes(w, fp32=False, jvp=False, fused=False):
     return ab
 
 
+def roofline_bytes(kernel, w, fused=False):
+    """What the roofline line says of one FP64 stage kernel: its compulsory bytes per
+    launch, the rule they follow (a sum of named sizes, then the sizes) and the bytes
+    of plan records read besides (the solve's; None for the others)."""
+    nx, ny, nzm = w["nx"], w["ny"], w["nz"] // 2
+    sizes = {"S": spectral_field_bytes(w), "U": nx * nzm * ny * 16,
+             "X": ny * (3 * nx // 2) * nzm * 16}
+    rule, what = {
+        "k_synth_y": ("3 U + 5 U", "reads the state, writes five y-valued fields"),
+        "k_fft_x_inv": ("5 U + 6 X", "reads five y-valued fields, writes six x-physical ones"),
+        "k_z_product": ("5 U + 3 X", "reads five y-valued fields, writes three product fields")
+        if fused else ("6 X + 3 X", "reads six x-physical fields, writes three product fields"),
+        "k_fft_x_fwd": ("3 X + 3 U", "reads three product fields, writes them y-valued"),
+        "k_stokes_solve": ("9 S", "reads the three product fields and u, writes Phi"),
+    }[kernel]
+    used = ", ".join(f"{n} = {b} B" for n, b in sizes.items() if n in rule)
+    return (algorithmic_bytes(w, fused=fused)[kernel], f"{rule} ({what}), {used}",
+            record_bytes(w) if kernel == "k_stokes_solve" else None)
+
+
 def record_bytes(w):
     """Per-mode solve records (sweep factors of the two operators, influence
     solutions, 2x2 inverse influence matrices: 6 (N+1) + 12 doubles) and the
@@ -1117,7 +1137,7 @@ def main():
                              "achieved_GBs": round(ab[name] / (avg_us * 1e-6) / 1e9, 1)}
     dom = max(kernels, key=lambda k: kernels[k]["avg_us"])
     dom_us = kernels[dom]["avg_us"]
-    alg = kernels[dom]["alg_bytes"]
+    alg, rule, record = roofline_bytes(dom, w, fused)
     achieved = round(alg / (dom_us * 1e-6) / 1e9, 1)
     traffic = None
     mt = MEASURED_TRAFFIC.get(args.workload, {}).get(dom)
@@ -1128,9 +1148,7 @@ def main():
     roofline = {"bound": "hbm", "kernel": dom, "achieved": achieved, "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": traffic, "bytes_per_launch": alg,
-                "bytes_rule": "9 S (reads the three product fields and u, writes Phi), "
-                              f"S = {S} B",
-                "record_bytes_per_launch": record_bytes(w),
+                "bytes_rule": rule, "record_bytes_per_launch": record,
                 "avg_us": round(dom_us, 3),
                 "timing": f"hip events around {reps} back-to-back launches (sp_time_stage)",
                 "step": {"bytes": 27 * S, "us": round(ms_per_step * 1000.0, 3),
