@@ -428,26 +428,20 @@ __global__ void __launch_bounds__(zline_threads(P1* P2, XF))
           run(std::integral_constant<int, 0>{});
         } else {
           if (fsel == 0) run(std::integral_constant<int, 0>{});
-          if constexpr (NF > 1) {
-            if (fsel == 1) run(std::integral_constant<int, 1>{});
-          }
-          if constexpr (NF > 2) {
-            if (fsel == 2) run(std::integral_constant<int, 2>{});
-          }
+          static_assert(Op::kBase || NF == 2, "two forward lines");
+          if (fsel == 1) run(std::integral_constant<int, 1>{});
         }
       }
     }
   }
   if constexpr (NF > 0 && !kSplit && sizeof(R) == 8) {
     __syncthreads();
-    // the pointwise stage and step 1 of the forward transforms: task (xl, k1,
-    // forward line f) for operators that read no base state, f slowest (with
-    // XL * P1 a multiple of 64 it is uniform over a wave), else (xl, k1) with
-    // every f in one task, so the base state is read once per point
-    constexpr int NFT = Op::kBase ? 1 : NF;  // forward lines per task split
-    constexpr int NFL = NF / NFT;            // forward lines of a task
-    // lines F0 .. F0 + NFL - 1 (compile-time, so pout stays in registers)
-    auto products = [&](auto f0, int xl, int k1, C(&fw)[NFL][P2]) {
+    // the pointwise stage and step 1 of the forward transforms: task (xl, k1, forward line
+    // f), f slowest (with XL * P1 a multiple of 64 it is uniform over a wave). Operators
+    // with a base state have their own stage above: their products always fit the slots
+    static_assert(!Op::kBase && NF == 2, "two forward lines, no base state");
+    // line F0 (compile-time, so pout stays in registers)
+    auto products = [&](auto f0, int xl, int k1, C(&fw)[P2]) {
       constexpr int F0 = decltype(f0)::value;
       const size_t bo0 = line_of(xl) * P + k1;
       const Op op{};
@@ -457,49 +451,37 @@ __global__ void __launch_bounds__(zline_threads(P1* P2, XF))
 #pragma unroll
         for (int i = 0; i < NI; ++i) pin[i] = ex1[((xl * LS + i) * P2 + k2) * S1 + k1];
         op(pin, pout, base, bs, bo0 + (size_t)P1 * k2);
-#pragma unroll
-        for (int q = 0; q < NFL; ++q) fw[q][k2] = pout[F0 + q];
+        fw[k2] = pout[F0];
       }
+      dft_reg<P2, P, C, R>(fw, (R)-1, twl);
 #pragma unroll
-      for (int q = 0; q < NFL; ++q) {
-        dft_reg<P2, P, C, R>(fw[q], (R)-1, twl);
-#pragma unroll
-        for (int m2 = 1; m2 < P2; ++m2)
-          if (k1 != 0) fw[q][m2] = cmul(fw[q][m2], wpow<P, P, C, R>(k1 * m2, (R)-1, twl));
-      }
+      for (int m2 = 1; m2 < P2; ++m2)
+        if (k1 != 0) fw[m2] = cmul(fw[m2], wpow<P, P, C, R>(k1 * m2, (R)-1, twl));
     };
-    auto load = [&](int fsel, int xl, int k1, C(&fw)[NFL][P2]) {
-      if (NFT == 1 || fsel == 0) products(std::integral_constant<int, 0>{}, xl, k1, fw);
-      if constexpr (NFT > 1) {
-        if (fsel == 1) products(std::integral_constant<int, 1>{}, xl, k1, fw);
-      }
-      if constexpr (NFT > 2) {
-        if (fsel == 2) products(std::integral_constant<int, 2>{}, xl, k1, fw);
-      }
+    auto load = [&](int f, int xl, int k1, C(&fw)[P2]) {
+      if (f == 0) products(std::integral_constant<int, 0>{}, xl, k1, fw);
+      if (f == 1) products(std::integral_constant<int, 1>{}, xl, k1, fw);
     };
-    auto store = [&](int fsel, int xl, int k1, const C(&fw)[NFL][P2]) {
+    auto store = [&](int f, int xl, int k1, const C(&fw)[P2]) {
+      C* e = fx + ((xl * LF + f) * P2) * S1 + k1;
 #pragma unroll
-      for (int q = 0; q < NFL; ++q) {
-        C* e = fx + ((xl * LF + (NFL > 1 ? q : fsel)) * P2) * S1 + k1;
-#pragma unroll
-        for (int m2 = 0; m2 < P2; ++m2) e[m2 * S1] = fw[q][m2];
-      }
+      for (int m2 = 0; m2 < P2; ++m2) e[m2 * S1] = fw[m2];
     };
-    constexpr int NT = XL * P1 * NFT;
+    constexpr int NT = XL * P1 * NF;
     if constexpr (IP) {
-      const int k1 = tid % P1, xl = (tid / P1) % XL, fsel = tid / (XL * P1);
+      const int k1 = tid % P1, xl = (tid / P1) % XL, f = tid / (XL * P1);
       const bool act = tid < NT && xl < nxl;
-      C fw[NFL][P2];
-      if (act) load(fsel, xl, k1, fw);
-      if constexpr (NFT > 1) __syncthreads();  // (a task of every line owns its column)
-      if (act) store(fsel, xl, k1, fw);
+      C fw[P2];
+      if (act) load(f, xl, k1, fw);
+      __syncthreads();
+      if (act) store(f, xl, k1, fw);
     } else {
       for (int task = tid; task < NT; task += NTH) {
-        const int k1 = task % P1, xl = (task / P1) % XL, fsel = task / (XL * P1);
+        const int k1 = task % P1, xl = (task / P1) % XL, f = task / (XL * P1);
         if (xl < nxl) {
-          C fw[NFL][P2];
-          load(fsel, xl, k1, fw);
-          store(fsel, xl, k1, fw);
+          C fw[P2];
+          load(f, xl, k1, fw);
+          store(f, xl, k1, fw);
         }
       }
     }
