@@ -227,7 +227,11 @@ struct Gmres {
     if (hrec) (void)hipHostFree(hrec);
   }
   sp_status init() {
-    SP_TRY_HIP(hipHostMalloc((void**)&hrec, 2 * (K + 5) * sizeof(double)), "hipHostMalloc");
+    // coherent by request (the default follows the environment): a kernel's stores must be
+    // visible to the host when the event after it has passed
+    SP_TRY_HIP(hipHostMalloc((void**)&hrec, 2 * (K + 5) * sizeof(double),
+                             hipHostMallocMapped | hipHostMallocCoherent),
+               "hipHostMalloc");
     SP_TRY_HIP(hipHostGetDevicePointer((void**)&hrec_dev, hrec, 0), "hipHostGetDevicePointer");
     for (hipEvent_t& e : ev)
       SP_TRY_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming), "hipEventCreate");
