@@ -117,8 +117,9 @@ sp_status sp_plan_set_steps(sp_plan* plan, int32_t nsteps);
  * trajectory (du_{-1} = du_0 = du). SBDF2 needs FP64 actions and the Stokes
  * implicit operator (SP_ERR_INVALID from the residual, linearisation and
  * Jacobian calls otherwise); sp_befe_step and SP_OP_PHI actions stay one BEFE
- * step. The first switch to 1 allocates a canonical field and one y-valued
- * nonlinear term (SP_ERR_NOMEM if that fails). Invalidates the base state.
+ * step. The first switch to 1 allocates a canonical field and the previous step's
+ * nonlinear term, 3 [ny][nz/2][3 nx/2] complex values (y-valued, or with its x
+ * transform begun; SP_ERR_NOMEM if that fails). Invalidates the base state.
  * Synchronises. */
 sp_status sp_plan_set_scheme(sp_plan* plan, int32_t scheme);
 /* Laminar advection in the implicit operator (the remedy proposed in Sec. 3.6):
@@ -262,7 +263,8 @@ sp_status sp_jvp_lin_batch(sp_plan* plan, int32_t op, int32_t count, int32_t nst
  * The plan's stream waits for all of them. Buffers (two canonical fields for each
  * member of a group beside its intermediates; two fields and a packed vector where
  * the columns are formed one after another) are allocated and kept as for the
- * batched calls (SP_ERR_NOMEM if that fails). SP_ERR_INVALID for a bad op, a range outside [0, packed_n), ld < packed_n or no base state. */
+ * batched calls (SP_ERR_NOMEM if that fails). SP_ERR_INVALID for a bad op, a range
+ * outside [0, packed_n), ld < packed_n or no base state. */
 sp_status sp_jacobian_columns(sp_plan* plan, int32_t op, int64_t first, int64_t count, double* J,
                               int64_t ld);
 

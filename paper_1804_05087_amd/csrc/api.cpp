@@ -442,12 +442,15 @@ static void member_strides(const sp_plan* p, Members& m) {
 }
 
 // Members per group: as many as keep a group's intermediates within 128 MiB (half of
-// the Infinity Cache), one at least, 256 at most. Measured, us per member, one
-// stream: 24 fields of 32x33x32 in groups within 8, 32, 64, 128 and 256 MiB (with
-// x-physical fields, twice the bytes) 26.6, 9.1, 7.4, 6.4 and 4.8; 64 of 48x65x48
-// 41.9, 41.9, 31.1, 24.1, 21.1; 512 Jacobian columns of 16x17x16 2.3, 1.0, 0.95,
-// 0.89, 0.88 (19.6 one member at a time on three streams). With groups of one
-// (96x97x96) the streams overlap members: 231 us on one stream, 191 on two.
+// the Infinity Cache), one at least, 256 at most. Measured, us per member, groups within
+// 8, 32, 64, 128, 256 and 512 MiB: batches of 128 of 16x17x16 1.31, 0.97, 0.78, 0.78, 0.78,
+// 0.78; 24 of 32x33x32 8.4, 6.1, 5.7, 4.7, 4.7, 4.8; 32 of 48x65x48 21.8, 20.1, 18.6, 19.6,
+// 19.2, 18.7; with the inverse x transform apart, 24 of 36x33x36 19.2, 8.0, 7.1, 7.0, 6.2,
+// 6.1 (mixed 15.7, 7.9, 6.6, 6.5, 5.6, 5.5), 24 of 54x50x36 20.7, 21.2, 14.5, 15.8, 14.5,
+// 14.4, 12 of 72x49x72 36.4, 36.2, 37.3, 35.6, 36.2, 36.0; 512 Jacobian columns of 16x17x16
+// 1.22, 0.90, 0.90, 0.86, 0.86, 0.86. Past 128 MiB only a batch that then fits one group
+// gains, a tenth, for twice the memory. At 96x97x96 a member is a group (137 us on three
+// streams, 157 alone).
 static constexpr size_t kGroupBytes = (size_t)128 << 20;
 static constexpr size_t kGroupMost = 256;
 static int group_members(const sp_plan* p) {

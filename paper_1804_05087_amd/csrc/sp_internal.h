@@ -209,10 +209,10 @@ struct sp_plan {
   double2* traj = nullptr;
   bool traj_valid = false;
   int base_step = 0;  // trajectory index of the cached base state
-  // laminar advection in the implicit operator: dense real solution operators of the
-  // mode pairs, [nx/2][nzm][3(N-1)][3 ny, even], and the (0,0) mode's wall response
   bool stages_apart = false;  // stage timing: every stage as a kernel of its own
   bool symmetric = false;  // Newton drivers confined to the shift-reflect subspace
+  // laminar advection in the implicit operator: dense real solution operators of the
+  // mode pairs, [nx/2][nzm][3(N-1)][3 ny, even], and the (0,0) mode's wall response
   bool advect = false;
   bool adv_host = false;  // build the advected operators on the host (reference) or the device
   double* d_adv = nullptr;

@@ -643,7 +643,8 @@ bool zline_fuses_x_inverse(const sp_plan* p, bool fp32, int nfields) {
 // (16x65x16), 20.9, 19.4 (32x33x32, Q = 6), 26.1, 24.6 (32x65x32), 29.3, 28.3 (48x33x48,
 // Q = 9), 38.4, 40.0 (48x65x48), 36.5, 38.3 (64x33x64, Q = 12); members of a batch, which
 // the gather's cache lines bound: 0.74, 0.78 (16x17x16), 4.5, 4.6 (32x33x32), 20.5, 22.6
-// (48x65x48). FP32 keeps the transform of its own (the order of its sums).
+// (48x65x48); they take it all the same, since a member equals the single call bit for bit
+// and the two forms sum in different orders. FP32 keeps the transform of its own (the order of its sums).
 bool solve_takes_x_forward(const sp_plan* p, bool fp32) {
   return !fp32 && !p->stages_apart && zline_fuses_x_inverse(p, false, 5) &&
          p->d.px / kZXL <= 6;
