@@ -57,16 +57,16 @@ KERNEL_SOURCES = {
 }
 MEASURED_TRAFFIC = {
     "couette_48x65x48_re1000_dt100": {
-        # 256 MiB copy: FETCH_SIZE 131092.5 KiB, WRITE_SIZE 262144.0 KiB
+        # 256 MiB copy: FETCH_SIZE 131096 KiB, WRITE_SIZE 262144.0 KiB
         "k_stokes_solve": {
             "fetch_kib": 5591.2, "write_kib": 3674.3,
-            "fetch_factor": 262144.0 / 131092.5, "write_factor": 1.0,
+            "fetch_factor": 262144.0 / 131096, "write_factor": 1.0,
             "sources_sha256": "3ea95296af943aa9563fa13bdc6dcd603c9a1c857cb680b3232615244a08c9ba",
         },
         "k_z_product": {
             "fetch_kib": 3332.0, "write_kib": 5265.0,
-            "fetch_factor": 262144.0 / 131092.5, "write_factor": 1.0,
-            "sources_sha256": "ef1a3ee6448b5b10cf3b397cd78b44da0e41c2f9e9f858e707190973bd77447e",
+            "fetch_factor": 262144.0 / 131096, "write_factor": 1.0,
+            "sources_sha256": "248393a6f815e8501abe1a718d7cdeeecc9c09b639cdd355afbb76f94417a8dc",
         },
     },
 }
